@@ -620,14 +620,9 @@ static E2fBwdWs bwd_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, size_t at
     Bw.Gu = (float*)take((size_t)3 * E2F_MAX_N * E2F_MAX_N * 4);
     Bw.pWb = (float*)take((size_t)N * ctx->cfg.H * ctx->cfg.B * 4);
     Bw.pwp = (float*)take((size_t)N * 32 * 4);
-    Bw.wT = ctx->cfg.feat_dtype == E2F_BF16
-                ? (uint16_t*)take((size_t)5 * (ctx->cfg.L_max + 1) * ctx->cfg.C * ctx->cfg.C * 2) : nullptr;
-    Bw.tbuf = Bw.wpart = nullptr;
-    if (with_W) {
-        const size_t C = ctx->cfg.C, L1 = ctx->cfg.L_max + 1;
-        Bw.tbuf = (float*)take((size_t)5 * N * ctx->n * C * 4);
-        Bw.wpart = (float*)take((size_t)8 * L1 * L1 * 5 * C * C * 4);   // 8 (L_max+1)^2 slices of partial sums
-    }
+    const size_t C = ctx->cfg.C, L1 = ctx->cfg.L_max + 1;
+    Bw.wT = take((size_t)5 * L1 * C * C * (ctx->cfg.feat_dtype == E2F_BF16 ? 2 : 4));
+    Bw.wpart = with_W ? (float*)take((size_t)e2f_wgrad_split(ctx->cfg.L_max) * L1 * L1 * 5 * C * C * 4) : nullptr;
     Bw.bytes = off;
     return Bw;
 }
@@ -638,26 +633,24 @@ static bool backward_in_tile_form(const e2f_ctx* ctx, bool wgrad) {
     return ctx->use_tile_attn && (!wgrad || e2f_backward_tile_weight_gradients_supported(ctx));
 }
 
-size_t e2f_attn_backward_workspace_bytes(const e2f_ctx* ctx, int32_t N) {
-    if (!ctx || N < 0) return 0;
-    size_t bytes = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 0).bytes, false).bytes;
+// Never less than the forward pass wants, so that a training step can run both in the one workspace.
+static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_W) {
+    size_t bytes = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 0).bytes, with_W).bytes;
     if (backward_in_tile_form(ctx, false)) {   // either form may run, depending on the gradients asked for
-        const size_t b2 = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 2).bytes, false).bytes;
+        const size_t b2 = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 2).bytes, with_W).bytes;
         const size_t b3 = e2f_bwd_tile_ws_layout(ctx, N, nullptr, b2).bytes;
         if (b3 > bytes) bytes = b3;
     }
-    return bytes;
+    const size_t fwd = e2f_attn_workspace_bytes(ctx, N);
+    return bytes > fwd ? bytes : fwd;
+}
+
+size_t e2f_attn_backward_workspace_bytes(const e2f_ctx* ctx, int32_t N) {
+    return ctx && N >= 0 ? backward_workspace_bytes(ctx, N, false) : 0;
 }
 
 size_t e2f_attn_backward_weights_workspace_bytes(const e2f_ctx* ctx, int32_t N) {
-    if (!ctx || N < 0) return 0;
-    size_t bytes = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 0).bytes, true).bytes;
-    if (backward_in_tile_form(ctx, false)) {
-        const size_t b2 = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 2).bytes, true).bytes;
-        const size_t b3 = e2f_bwd_tile_ws_layout(ctx, N, nullptr, b2).bytes;
-        if (b3 > bytes) bytes = b3;
-    }
-    return bytes;
+    return ctx && N >= 0 ? backward_workspace_bytes(ctx, N, true) : 0;
 }
 
 // saved: the workspace still holds what the forward pass wrote (projections, candidate lists, axis operators)

@@ -1,0 +1,462 @@
+// Backward pass through the l-wise linear maps: dL/dh and the gradients of the five projection matrices from dL/dq,
+// dL/dk, dL/dv (all in the caller's atom order).  With p_k = W_k x for a row x = h[atom][l, m], the invariants
+// q[l] = sum_m p_0 p_1, k[l] = sum_m p_2 p_3 and v = p_4 (Eq. qk) give the row factors
+//     t = (dq[l] p_1, dq[l] p_0, dk[l] p_3, dk[l] p_2, dv[l, m])
+// and from them  dx = sum_k W_k^T t_k  and  dW_k = sum over rows of t_k (x) x.
+//
+// A degree's rows (atoms x orders) are one long list of N (2l+1) rows, cut into units of equal size, so that both
+// kernels are matrix products over row tiles on the matrix cores, for bf16 features (16-bit operands, fp32 sums) and
+// fp32 features (binary32 operands) alike.  Neither kernel stores the row factors: the weight-gradient kernel forms them again from h
+// (two fifths of its matrix work), where writing and reading five fp32 rows per row of h took 100 us of a training step at 4 000
+// atoms and 128 channels.
+#include <type_traits>
+
+#include "e2f_device.h"
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
+}
+
+// The matrix operands of a feature type.  A fragment is 16 bytes of one row per lane: EPF elements of the contraction
+// index.  Which index an element stands for is free as long as both operands agree; a half-wave (32-row tiles) or a
+// quarter-wave (16-row tiles) takes the next EPF elements of the row, so that a lane's load is contiguous.
+template <typename T>
+struct Mat;
+template <>
+struct Mat<uint16_t> {
+    static constexpr int EPF = 8;
+    static __device__ __forceinline__ f32x16 mma32(u32x4 a, u32x4 b, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+template <>
+struct Mat<float> {
+    static constexpr int EPF = 4;
+    static __device__ __forceinline__ f32x16 mma32(u32x4 a, u32x4 b, f32x16 c) {
+        const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s], fb[s], c, 0, 0, 0);
+        return c;
+    }
+    static __device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c) {
+        const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[s], fb[s], c, 0, 0, 0);
+        return c;
+    }
+};
+
+template <typename T>
+struct MapWeights {
+    const T* W[5];   // WQ1, WQ2, WK1, WK2, WV: [L+1][C out][C in]
+};
+
+// WT[k][l][ci][co] = W_k[l][co][ci], so that the transposed products read their weights by rows too; one workgroup
+// per (k, l, 16 x 16 tile).
+template <typename T>
+__global__ __launch_bounds__(256) void k_transpose_weights(MapWeights<T> mw, int L1, int C, T* __restrict__ WT) {
+    __shared__ T s[16][17];
+    const int tiles = C / 16, t = blockIdx.x % (tiles * tiles), kl = blockIdx.x / (tiles * tiles);
+    const int k = kl / L1, l = kl % L1, tr = t / tiles, tc = t % tiles;
+    const T* W = k == 0 ? mw.W[0] : k == 1 ? mw.W[1] : k == 2 ? mw.W[2] : k == 3 ? mw.W[3] : mw.W[4];
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    s[r][c] = W[((size_t)l * C + 16 * tr + r) * C + 16 * tc + c];
+    __syncthreads();
+    WT[(((size_t)k * L1 + l) * C + 16 * tc + r) * C + 16 * tr + c] = s[c][r];
+}
+
+// Workgroups [first[d], first[d + 1]) own the rows of degree L - d, the degree with the most rows first.
+struct DegreeMap {
+    int first[E2F_MAX_L + 2];
+};
+
+// ---- dL/dh.  A workgroup owns 32 RT rows of one degree and all channels: the rows x stay in LDS, and for each of the
+// five maps the factors t_k = (dq or dk) (W x) go through LDS as one more operand of the same shape (bf16 features: rounded to
+// bf16, the counterpart of the forward pass rounding the projected values).  Wave w owns 32 output channels of the first
+// product, written with the channels as rows, so that a lane holds four consecutive channels of its row (16-byte loads of
+// dq and dk, 8- or 16-byte stores to LDS), and the same 32 input channels of the second one, written with the data rows as
+// rows, so that a store of the result covers whole 128-byte lines.  The weights are read once per workgroup, by
+// fragments straight into registers, eight of them (one chunk) ahead of the products: they stay in the L2s (five 128-channel
+// degrees are 1.5 MB with their transposes), and no channel count is too wide for the registers.
+// Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
+// the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
+// kernels before (one thread per channel on the vector ALUs; at 128 bf16 channels weights held in registers, one
+// degree's slabs per workgroup) in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4 x 256: 189 us
+// (2 818), x 128 with weight gradients: 66 us (150).
+// CP: channels padded up to a multiple of 32 (PAD: C < CP; the missing ones read as zero).
+template <typename T, int CP, int RT, bool PAD>
+__global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_rows(
+    const T* __restrict__ h, MapWeights<T> mw, const T* __restrict__ WT, const float* __restrict__ gq,
+    const float* __restrict__ gk, const float* __restrict__ gv, float* __restrict__ gh, int L, int C_, int N,
+    DegreeMap map) {
+    constexpr int EPF = Mat<T>::EPF, ROWS = 32 * RT, THREADS = 2 * CP;
+    constexpr int ROW = CP + EPF;              // LDS row pitch: 16 bytes of padding against bank conflicts
+    constexpr int NF = CP / (2 * EPF);         // fragments of a whole contraction
+    constexpr int CF = NF < 8 ? NF : 8;        // fragments per chunk
+    constexpr int CPS = NF / CF;               // chunks per product
+    static_assert(NF % CF == 0, "whole chunks");
+    __shared__ __attribute__((aligned(16))) T s_X[ROWS * ROW], s_T[ROWS * ROW];
+    __shared__ __attribute__((aligned(16))) int s_row[ROWS];   // row -> atom * n + component
+    __shared__ int s_inv[ROWS];                                // row -> atom * (L + 1) + degree
+    const int C = PAD ? C_ : CP;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i = lane & 31, hf = lane >> 5;
+    const int n = (L + 1) * (L + 1);
+    int d = 0;
+    while (d < L && (int)blockIdx.x >= map.first[d + 1]) ++d;
+    const int l = L - d, nl = 2 * l + 1;
+    const int rows = N * nl, r0 = ((int)blockIdx.x - map.first[d]) * ROWS;
+    for (int x = tid; x < ROWS; x += THREADS) {
+        const int r = min(r0 + x, rows - 1), atom = r / nl;   // the rows after the last repeat it and are not stored
+        s_row[x] = atom * n + l * l + (r - atom * nl);
+        s_inv[x] = atom * (L + 1) + l;
+    }
+    __syncthreads();
+    // stage 2k + 0 .. of the sequence below: second product of map 4, then first and second product of maps 0 .. 3
+    const size_t wl = (size_t)l * C * C, kstride = (size_t)(L + 1) * C * C;
+    u32x4 buf[2][CF];
+    auto load_chunk = [&](int q, u32x4 (&dst)[CF]) {   // q: chunk of the whole sequence
+        const int st = q / CPS, c = q % CPS;
+        // stage 0: WT[4]; stage 1 + 2k: the map whose product enters t_k (1, 0, 3, 2); stage 2 + 2k: WT[k]
+        const T* base = st == 0 ? WT + 4 * kstride + wl : (st & 1) ? mw.W[((st - 1) / 2) ^ 1] + wl : WT + ((st - 2) / 2) * kstride + wl;
+        const int row = 32 * w + i;
+#pragma unroll
+        for (int f = 0; f < CF; ++f) {
+            const int col = (c * CF + f) * 2 * EPF + EPF * hf;
+            dst[f] = (!PAD || (row < C && col < C)) ? *reinterpret_cast<const u32x4*>(base + (size_t)row * C + col) : (u32x4){0u, 0u, 0u, 0u};
+        }
+    };
+    load_chunk(0, buf[0]);
+    {   // x and dv of the unit's rows
+        constexpr int PX = ROWS * CP / EPF / THREADS;   // 16-byte pieces of x per thread
+#pragma unroll
+        for (int j = 0; j < PX; ++j) {
+            const int e = tid + THREADS * j, rr = e / (CP / EPF), c = EPF * (e % (CP / EPF));
+            *reinterpret_cast<u32x4*>(s_X + rr * ROW + c) =
+                (!PAD || c < C) ? *reinterpret_cast<const u32x4*>(h + (size_t)s_row[rr] * C + c) : (u32x4){0u, 0u, 0u, 0u};
+        }
+        constexpr int PV = ROWS * CP / 4 / THREADS;     // 16-byte pieces of dv per thread
+#pragma unroll
+        for (int j = 0; j < PV; ++j) {
+            const int e = tid + THREADS * j, rr = e / (CP / 4), c = 4 * (e % (CP / 4));
+            const f32x4 v = (!PAD || c < C) ? *reinterpret_cast<const f32x4*>(gv + (size_t)s_row[rr] * C + c) : (f32x4){0.f, 0.f, 0.f, 0.f};
+            if constexpr (EPF == 8) *reinterpret_cast<u32x2*>(s_T + rr * ROW + c) = (u32x2){pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            else *reinterpret_cast<f32x4*>(s_T + rr * ROW + c) = v;
+        }
+    }
+    f32x16 dx[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) dx[rt] = (f32x16)(0.0f);
+    __syncthreads();
+    auto frag = [&](const T* s, int rt, int f) {
+        return *reinterpret_cast<const u32x4*>(s + (32 * rt + i) * ROW + 2 * EPF * f + EPF * hf);
+    };
+#pragma unroll
+    for (int st = 0; st < 9; ++st) {
+        if (st == 0 || !(st & 1)) {   // dx[row][channel 32 w + i] += sum over co of t[row][co] W[co][ci]
+#pragma unroll
+            for (int c = 0; c < CPS; ++c) {
+                const int q = st * CPS + c;
+                if (q + 1 < 9 * CPS) load_chunk(q + 1, buf[(q + 1) & 1]);
+#pragma unroll
+                for (int f = 0; f < CF; ++f)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) dx[rt] = Mat<T>::mma32(frag(s_T, rt, c * CF + f), buf[q & 1][f], dx[rt]);
+            }
+        } else {   // p[channel][row] of the map, then t
+            f32x16 p[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) p[rt] = (f32x16)(0.0f);
+#pragma unroll
+            for (int c = 0; c < CPS; ++c) {
+                const int q = st * CPS + c;
+                if (q + 1 < 9 * CPS) load_chunk(q + 1, buf[(q + 1) & 1]);
+#pragma unroll
+                for (int f = 0; f < CF; ++f)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) p[rt] = Mat<T>::mma32(buf[q & 1][f], frag(s_X, rt, c * CF + f), p[rt]);
+            }
+            const float* g = st < 4 ? gq : gk;   // stages 1, 3: dq; 5, 7: dk
+            __syncthreads();   // the factors of the map before have been read
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const float* grow = g + (size_t)s_inv[32 * rt + i] * C + 32 * w + 4 * hf;
+                T* trow = s_T + (32 * rt + i) * ROW + 32 * w + 4 * hf;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {   // channels 32 w + 8 j + 4 hf + 0 .. 3
+                    const f32x4 gg = (!PAD || 32 * w + 8 * j < C) ? *reinterpret_cast<const f32x4*>(grow + 8 * j) : (f32x4){0.f, 0.f, 0.f, 0.f};
+                    const f32x4 t = {gg[0] * p[rt][4 * j], gg[1] * p[rt][4 * j + 1], gg[2] * p[rt][4 * j + 2], gg[3] * p[rt][4 * j + 3]};
+                    if constexpr (EPF == 8) *reinterpret_cast<u32x2*>(trow + 8 * j) = (u32x2){pack_bf16(t[0], t[1]), pack_bf16(t[2], t[3])};
+                    else *reinterpret_cast<f32x4*>(trow + 8 * j) = t;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    const int ci = 32 * w + i;
+    if (PAD && ci >= C) return;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int rr = 32 * rt + 8 * j + 4 * hf;
+            const int4 at = *reinterpret_cast<const int4*>(s_row + rr);
+            const int ats[4] = {at.x, at.y, at.z, at.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (r0 + rr + r < rows) gh[(size_t)ats[r] * C + ci] = dx[rt][4 * j + r];
+        }
+}
+
+// ---- dL/dW.  A workgroup owns a slice of a degree's rows, one of the five maps and 16 output channels per wave (up to
+// eight waves), with all input channels; it walks its rows 64 at a time.  The rows x of a step are shared by the waves
+// through LDS; a wave forms the products p of its own channels with the weights in registers, written with the data rows as
+// rows, which leaves the factors t in the register layout that the second product wants as its A operand (contraction
+// over the data rows), so they never leave the wave.  bf16 features: the factors as two bf16 (leading part and
+// remainder, 16 significant bits), and a second copy of x turned in LDS, with the eight rows that a lane takes of one
+// channel side by side.  fp32 features: the rows of x as they are (a lane takes one row of 16 channels per step of the
+// fp32 instruction).  One map per workgroup: two (sharing dq or dk and the rows of x) take 200 registers, which
+// leaves one workgroup per CU and a half-empty second round of them (bf16 98 us, fp32 154 us).
+// Measured, the sum over the slices included, with the kernels that read stored factors in brackets: bf16 4 000 atoms L = 4 x 128:
+// 75 us (195), fp32 2 240 atoms L = 2 x 128: 91 us (227).
+constexpr int WSTEP = 64;   // rows per step
+
+template <typename T, int CP, int NW, bool PAD>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CP <= 128 ? 4 : 2))) void k_bwd_wgrad(
+    const T* __restrict__ h, MapWeights<T> mw, const float* __restrict__ gq, const float* __restrict__ gk,
+    const float* __restrict__ gv, int L, int C_, int N, int split, float* __restrict__ part) {
+    constexpr int EPF = Mat<T>::EPF, THREADS = 64 * NW;
+    constexpr bool BF = EPF == 8;
+    constexpr int ROW = CP + EPF, TROW = WSTEP + 8;
+    constexpr int NF = CP / (4 * EPF);      // fragments of a contraction over the channels
+    constexpr int CT = CP / 16;             // tiles of input channels
+    constexpr int UNITS = WSTEP / 4 * CP / 4 / THREADS;   // units of loading per thread: four rows x four channels
+    static_assert(UNITS >= 1, "whole units");
+    __shared__ __attribute__((aligned(16))) T s_X[WSTEP * ROW];
+    __shared__ __attribute__((aligned(16))) T s_Xt[BF ? CP * TROW : 1];
+    __shared__ int s_row[2 * WSTEP], s_inv[2 * WSTEP];   // two sets, used in turn
+    const int C = PAD ? C_ : CP;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i = lane & 15, g = lane >> 4;
+    const int n = (L + 1) * (L + 1), slice = blockIdx.x;
+    int l = 0;   // degree l has split * (2l+1) slices
+    while (split * (l + 1) * (l + 1) <= slice) ++l;
+    const int nl = 2 * l + 1, rows = N * nl, slices = split * nl, mine = slice - split * l * l;
+    const int steps = (rows + WSTEP - 1) / WSTEP;
+    const int s_lo = (int)((long long)steps * mine / slices), s_hi = (int)((long long)steps * (mine + 1) / slices);
+    const int k = blockIdx.y % 5, cb = blockIdx.y / 5;
+    const int co0 = 16 * (cb * NW + w), co = co0 + i;   // this wave's and this lane's output channel
+    const bool value = k == 4;                          // dv itself: no first product
+    const float* gr = value ? gv : k < 2 ? gq : gk;
+    u32x4 W[NF];
+    if (!value) {   // the map whose product enters t_k: 1, 0, 3, 2
+        const T* base = (k == 0 ? mw.W[1] : k == 1 ? mw.W[0] : k == 2 ? mw.W[3] : mw.W[2]) + (size_t)l * C * C + (size_t)co * C;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const int col = 4 * EPF * f + EPF * g;
+            W[f] = (!PAD || (co < C && col < C)) ? *reinterpret_cast<const u32x4*>(base + col) : (u32x4){0u, 0u, 0u, 0u};
+        }
+    }
+    f32x4 acc[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    typedef typename std::conditional<BF, u32x2, u32x4>::type piece;   // four channels of a row
+    piece xr[UNITS][4];
+    f32x4 gn[WSTEP / 16];   // dq, dk or dv of the lane's channel: rows 16 S + 4 g + 0 .. 3 of the step fetched last
+    auto table = [&](int s) {   // where the rows of step s are (factors beyond the last row: -1, read as zero)
+        for (int x = tid; x < WSTEP; x += THREADS) {
+            const int r = s * WSTEP + x, rc = min(r, rows - 1), atom = rc / nl, at = atom * n + l * l + (rc - atom * nl);
+            s_row[(s & 1) * WSTEP + x] = at;
+            s_inv[(s & 1) * WSTEP + x] = r < rows ? (value ? at : atom * (L + 1) + l) : -1;
+        }
+    };
+    auto fetch_g = [&](int s, int S) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int at = s_inv[(s & 1) * WSTEP + 16 * S + 4 * g + r];
+            gn[S][r] = (at >= 0 && (!PAD || co < C)) ? gr[(size_t)at * C + co] : 0.0f;
+        }
+    };
+    auto fetch_x = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int e = tid + THREADS * u, rq = e / (CP / 4), c = 4 * (e % (CP / 4));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int at = s_row[(s & 1) * WSTEP + 4 * rq + j];
+                xr[u][j] = (!PAD || c < C) ? *reinterpret_cast<const piece*>(h + (size_t)at * C + c) : (piece)(0u);
+            }
+        }
+    };
+    auto store_x = [&]() {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int e = tid + THREADS * u, rq = e / (CP / 4), c = 4 * (e % (CP / 4));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<piece*>(s_X + (4 * rq + j) * ROW + c) = xr[u][j];
+            if constexpr (BF) {
+                // rows 4 rq .. + 3 of four channels, turned.  Row 32 P + 16 S + 4 g + j of a step sits at position
+                // 32 P + 8 g + 4 S + j of its channel: what quarter-wave g contracts over in one instruction.
+                // (16-byte pieces permuted by channel, so that neither the turned stores nor the loads pile up in few banks)
+                const int at = 8 * ((4 * (rq >> 3) + (rq & 3)) ^ ((c >> 2) & 7)) + 4 * ((rq >> 2) & 1);
+                const u32x2 a = xr[u][0], b = xr[u][1], cc = xr[u][2], dd = xr[u][3];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const uint32_t sel = (x & 1) ? 0x07060302u : 0x05040100u;   // upper or lower half of both words
+                    const u32x2 v = {__builtin_amdgcn_perm(b[x >> 1], a[x >> 1], sel), __builtin_amdgcn_perm(dd[x >> 1], cc[x >> 1], sel)};
+                    *reinterpret_cast<u32x2*>(s_Xt + (c + x) * TROW + at) = v;
+                }
+            }
+        }
+    };
+    if (s_lo < s_hi) {
+        table(s_lo);
+        __syncthreads();
+        fetch_x(s_lo);
+#pragma unroll
+        for (int S = 0; S < WSTEP / 16; ++S) fetch_g(s_lo, S);
+    }
+    for (int s = s_lo; s < s_hi; ++s) {
+        __syncthreads();   // the rows of the step before have been read
+        store_x();
+        const int sn = min(s + 1, s_hi - 1);   // (the last step fetches itself once more: no branch around the requests)
+        if (sn != s) table(sn);
+        __syncthreads();
+        fetch_x(sn);
+        auto factors = [&](int S) {   // t[r]: row 16 S + 4 g + r, channel co
+            const f32x4 gs = gn[S];
+            fetch_g(sn, S);
+            if (value) return gs;
+            f32x4 p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                p = Mat<T>::mma16(*reinterpret_cast<const u32x4*>(s_X + (16 * S + i) * ROW + 4 * EPF * f + EPF * g), W[f], p);
+            return gs * p;
+        };
+        if constexpr (BF) {
+#pragma unroll
+            for (int P = 0; P < WSTEP / 32; ++P) {
+                u32x4 hi, lo;
+#pragma unroll
+                for (int S = 0; S < 2; ++S) {
+                    const f32x4 t = factors(2 * P + S);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const uint32_t v = pack_bf16(t[2 * x], t[2 * x + 1]);
+                        hi[2 * S + x] = v;
+                        lo[2 * S + x] = pack_bf16(t[2 * x] - __uint_as_float(v << 16), t[2 * x + 1] - __uint_as_float(v & 0xffff0000u));
+                    }
+                }
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    const u32x4 X = *reinterpret_cast<const u32x4*>(s_Xt + (16 * ct + i) * TROW + 8 * ((4 * P + g) ^ ((4 * ct + (i >> 2)) & 7)));
+                    acc[ct] = Mat<T>::mma16(lo, X, Mat<T>::mma16(hi, X, acc[ct]));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int S = 0; S < WSTEP / 16; ++S) {
+                const f32x4 t = factors(S);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[r], reinterpret_cast<const float*>(s_X)[(16 * S + 4 * g + r) * ROW + 16 * ct + i], acc[ct], 0, 0, 0);
+            }
+        }
+    }
+    // part[slice][k][co][ci]: lane (i, g) holds rows co = 4 g + r of column ci = i of every tile
+    if (PAD && co0 >= C) return;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+        if (!PAD || 16 * ct < C)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[(((size_t)slice * 5 + k) * C + co0 + 4 * g + r) * C + 16 * ct + i] = acc[ct][r];
+}
+
+// out[k][l][co][ci] = sum over the slices of degree l, in a fixed order; a thread sums four neighbouring elements.
+__global__ __launch_bounds__(64) void k_sum_slices(const float* __restrict__ part, int L, int C, int split, float* __restrict__ out) {
+    const size_t CC = (size_t)C * C, M = (size_t)5 * (L + 1) * CC;
+    const size_t e4 = 4 * ((size_t)blockIdx.x * 64 + threadIdx.x);
+    if (e4 >= M) return;
+    const int k = (int)(e4 / ((L + 1) * CC)), l = (int)((e4 / CC) % (L + 1));
+    const float* p = part + ((size_t)split * l * l * 5 + k) * CC + e4 % CC;
+    const int m = split * (2 * l + 1);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int c = 0; c < m; ++c) s += *reinterpret_cast<const f32x4*>(p + (size_t)c * 5 * CC);
+    *reinterpret_cast<f32x4*>(out + e4) = s;
+}
+
+template <typename T, int CP, int RT, bool PAD>
+void launch_rows(const MapWeights<T>& mw, const T* WT, const T* h, const float* gq, const float* gk, const float* gv,
+                 float* gh, int L, int C, int N, hipStream_t st) {
+    DegreeMap map;
+    map.first[0] = 0;
+    for (int d = 0; d <= L; ++d) map.first[d + 1] = map.first[d] + (N * (2 * (L - d) + 1) + 32 * RT - 1) / (32 * RT);
+    k_bwd_rows<T, CP, RT, PAD><<<map.first[L + 1], 2 * CP, 0, st>>>(h, mw, WT, gq, gk, gv, gh, L, C, N, map);
+}
+
+template <typename T, int CP, bool PAD>
+void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const float* gk, const float* gv, float* gh,
+              float* grad_W, float* part, int L, int C, int N, hipStream_t st) {
+    if (gh) {
+        const int t16 = C / 16;
+        k_transpose_weights<T><<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
+        // Rows per workgroup: 128 (bf16) or 64 (fp32) while that leaves two workgroups per CU, else half of it
+        constexpr int RT = sizeof(T) == 2 ? 4 : 2;
+        const bool wide = (long long)N * (L + 1) * (L + 1) >= 512ll * 32 * RT;
+        if (wide) launch_rows<T, CP, RT, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+        else launch_rows<T, CP, RT / 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+    }
+    if (grad_W) {
+        constexpr int NW = CP / 16 < 8 ? CP / 16 : 8;
+        const int split = e2f_wgrad_split(L);
+        const dim3 grid(split * (L + 1) * (L + 1), 5 * (CP / 16 / NW));
+        k_bwd_wgrad<T, CP, NW, PAD><<<grid, 64 * NW, 0, st>>>(h, mw, gq, gk, gv, L, C, N, split, part);
+        const size_t M = (size_t)5 * (L + 1) * C * C;
+        k_sum_slices<<<(unsigned)((M / 4 + 63) / 64), 64, 0, st>>>(part, L, C, split, grad_W);
+    }
+}
+
+template <typename T>
+e2f_status launch_T(const e2f_ctx* ctx, int N, const e2f_weights* w, const void* h, const float* gq, const float* gk,
+                    const float* gv, float* gh, float* grad_W, const E2fBwdWs& bw, hipStream_t st) {
+    const MapWeights<T> mw = {{(const T*)w->WQ1, (const T*)w->WQ2, (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV}};
+    const int L = ctx->cfg.L_max, C = ctx->cfg.C;
+    T* WT = reinterpret_cast<T*>(bw.wT);
+#define E2F_C(CP, PAD) launch_C<T, CP, PAD>(mw, WT, (const T*)h, gq, gk, gv, gh, grad_W, bw.wpart, L, C, N, st)
+    switch (C) {
+        case 16: E2F_C(32, true); break;
+        case 32: E2F_C(32, false); break;
+        case 48: E2F_C(64, true); break;
+        case 64: E2F_C(64, false); break;
+        case 128: E2F_C(128, false); break;
+        case 256: E2F_C(256, false); break;
+        default: return E2F_ERR_UNSUPPORTED;   // (192 channels: no head width that is a power of two)
+    }
+#undef E2F_C
+    E2F_HIP_CHECK(hipGetLastError());
+    return E2F_OK;
+}
+
+}  // namespace
+
+e2f_status e2f_launch_backward_maps(const e2f_ctx* ctx, int N, const e2f_weights* w, const void* h, const float* grad_q,
+                                    const float* grad_k, const float* grad_v, float* grad_h, float* grad_W,
+                                    const E2fBwdWs& bw, hipStream_t st) {
+    if (N == 0) return E2F_OK;
+    return ctx->cfg.feat_dtype == E2F_BF16 ? launch_T<uint16_t>(ctx, N, w, h, grad_q, grad_k, grad_v, grad_h, grad_W, bw, st)
+                                           : launch_T<float>(ctx, N, w, h, grad_q, grad_k, grad_v, grad_h, grad_W, bw, st);
+}

@@ -117,10 +117,9 @@ struct E2fBwdWs {
     float* Gu;       // [3][25][25]
     float* pWb;      // [N][H][B]
     float* pwp;      // [N][32]
-    uint16_t* wT;    // [5][L+1][C in][C out] the projection matrices transposed (bf16 features: chain rule on the matrix cores)
+    void* wT;        // [5][L+1][C in][C out] the projection matrices transposed, feature type
     // for the gradients of the projection matrices (only in the larger workspace of that form of the call)
-    float* tbuf;     // [5][N][n][C] row factors
-    float* wpart;    // [8 (L+1)^2 slices][5][C][C] partial sums
+    float* wpart;    // [e2f_wgrad_split(L) (L+1)^2 slices][5][C][C] partial sums
     size_t bytes;
 };
 
@@ -146,6 +145,10 @@ struct E2fFactWs {
     float* a0;   // [N][n][C] aggregated values
     size_t bytes;
 };
+
+// Slices of rows per component in the sums of the projection matrices' gradients: about 100 slices in all, five maps
+// each, which is one round of two workgroups per CU.
+static inline int e2f_wgrad_split(int L) { return (100 + (L + 1) * (L + 1) / 2) / ((L + 1) * (L + 1)); }
 
 static inline size_t e2f_align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 // Cell edge: a hair above the cutoff, since the binary32 predicate can accept a pair whose exact |dx| exceeds the
@@ -225,6 +228,11 @@ e2f_status e2f_launch_backward(const e2f_ctx* ctx, const E2fCellsView& cv, const
                                float* grad_q, float* grad_k, float* grad_v, const void* h, float* grad_h,
                                float* grad_Wb, float* grad_w_path, float* grad_W, const E2fBwdTileWs* tw, hipStream_t st,
                                bool lists_ready = false);
+// The chain rule through the l-wise maps (e2f_bwd_project.hip): dL/dh and the gradients of the projection matrices
+// (either may be null) from dL/dq, dL/dk, dL/dv in the caller's atom order.
+e2f_status e2f_launch_backward_maps(const e2f_ctx* ctx, int N, const e2f_weights* w, const void* h, const float* grad_q,
+                                    const float* grad_k, const float* grad_v, float* grad_h, float* grad_W,
+                                    const E2fBwdWs& bw, hipStream_t st);
 // cw[comp][t] = P coefficient with every path weight one.
 e2f_status e2f_launch_unit_cw(const e2f_ctx* ctx, float* cw, hipStream_t st);
 // table: the caller's padded neighbour table [N][table_K], or null (every atom within the cutoff is a neighbour)

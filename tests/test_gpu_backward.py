@@ -125,8 +125,7 @@ def test_backward_tile_form_with_12_radial_functions(torch_cuda):
 
 
 def test_backward_tile_form_256_channels(torch_cuda):
-    """A channel count the tile-layout projection is not built for: plain projection, relayout, tile kernels; the chain
-    rule through the projections on the vector-ALU kernel."""
+    """The channel count of the paper's model table, 16 heads."""
     wl = custom(22, (200, 60), 2, 256, 16, 8, "bf16", 4.5, 11.0)
     run_backward(torch_cuda, wl)
 
@@ -190,6 +189,56 @@ def test_backward_after_forward_reuses_the_workspace(torch_cuda):
                 assert torch_cuda.equal(a, b)
         finally:
             P.close()
+
+
+@pytest.mark.parametrize("dtype,L,C,H,N", [
+    ("f32", 1, 16, 2, 1), ("f32", 1, 48, 3, 33), ("f32", 2, 32, 2, 130), ("f32", 3, 64, 4, 65), ("f32", 2, 128, 8, 50),
+    ("f32", 4, 256, 16, 29), ("f32", 2, 32, 2, 3700), ("f32", 1, 128, 8, 8200),
+    ("bf16", 1, 32, 2, 3), ("bf16", 2, 64, 4, 127), ("bf16", 4, 128, 8, 41), ("bf16", 3, 256, 16, 100),
+    ("bf16", 2, 32, 1, 7400), ("bf16", 4, 64, 4, 2700), ("bf16", 4, 256, 16, 2650),
+])
+def test_backward_through_the_maps(torch_cuda, dtype, L, C, H, N):
+    """dL/dh and the gradients of the projection matrices against the same chain rule in float64, from the call's own
+    dL/dq, dL/dk, dL/dv: every channel count, row units with remainders, and both unit sizes (the longer ones from 512
+    units on).  Bounds: fp32 products and sums of at most 5 C (dL/dh) or N (2L+1) (weights) terms, 1e-5; bf16 features
+    round each row factor to 8 bits for dL/dh (rms error 2^-9 / sqrt 3 = 1.1e-3 of its term, independent from term to term)
+    and keep 16 bits of it for the weights (2^-17, below the fp32 sums' own rounding)."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    rng = np.random.default_rng(N + C)
+    cfg = dict(L=L, C=C, H=H, B=4, lf=1, cutoff=2.5, dtype=dtype)
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        plain = P.backward(g)[4]
+        _, gq, gk, gv, gh, _, _, gW = P.backward(g, with_weights=True)
+        torch.cuda.synchronize()
+        h = P.h.double()
+        Wd = [P.weights[k].double() for k in ("WQ1", "WQ2", "WK1", "WK2", "WV")]
+        ref_h, ref_W = torch.zeros_like(h), torch.zeros(gW.shape, dtype=torch.float64, device=P.device)
+        for l in range(L + 1):
+            x = h[:, l * l:(l + 1) ** 2].reshape(-1, C)
+            p = [x @ w[l].T for w in Wd[:4]]
+            dq, dk = (t[:, l:l + 1].double().expand(N, 2 * l + 1, C).reshape(-1, C) for t in (gq, gk))
+            t = [dq * p[1], dq * p[0], dk * p[3], dk * p[2], gv[:, l * l:(l + 1) ** 2].double().reshape(-1, C)]
+            ref_h[:, l * l:(l + 1) ** 2] = sum(a @ w[l] for a, w in zip(t, Wd)).reshape(N, 2 * l + 1, C)
+            for k in range(5):
+                ref_W[k, l] = t[k].T @ x
+        tol_h, tol_W = (1e-5, 1e-5) if dtype == "f32" else (4e-3, 5e-5)
+        for got, ref, tol in ((plain, ref_h, tol_h), (gh, ref_h, tol_h), (gW, ref_W, tol_W)):
+            assert torch.isfinite(got).all()
+            scale = max(float(ref.norm()), 1e-30)
+            err = float((got.double() - ref).norm()) / scale
+            assert err <= tol, (err, tol)
+            # no row or block hides in the norm over all of them
+            rows = (got.double() - ref).flatten(0, -2).norm(dim=1)
+            assert float(rows.max()) <= 10 * tol * float(ref.flatten(0, -2).norm(dim=1).max())
+    finally:
+        P.close()
 
 
 def test_backward_rejects_what_it_does_not_cover(torch_cuda):
