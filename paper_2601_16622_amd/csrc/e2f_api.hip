@@ -1,4 +1,5 @@
 // C ABI of libe2f.so: argument checks, workspace layout, and the sequence of launches per entry point.
+#include <algorithm>
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -622,7 +623,13 @@ static E2fBwdWs bwd_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, size_t at
     Bw.pwp = (float*)take((size_t)N * 32 * 4);
     const size_t C = ctx->cfg.C, L1 = ctx->cfg.L_max + 1;
     Bw.wT = take((size_t)5 * L1 * C * C * (ctx->cfg.feat_dtype == E2F_BF16 ? 2 : 4));
-    Bw.wpart = with_W ? (float*)take((size_t)e2f_wgrad_split(ctx->cfg.L_max) * L1 * L1 * 5 * C * C * 4) : nullptr;
+    Bw.wpart = nullptr;
+    if (with_W) {
+        // the partial sums need e2f_wgrad_split(L_max) (L_max+1)^2 slices; the call's documented size (five row arrays and
+        // 8 (L_max+1)^2 slices, which an older form of the sums filled) stays what it was
+        take((size_t)5 * N * ctx->n * C * 4);
+        Bw.wpart = (float*)take((size_t)std::max(8, e2f_wgrad_split(ctx->cfg.L_max)) * L1 * L1 * 5 * C * C * 4);
+    }
     Bw.bytes = off;
     return Bw;
 }
