@@ -141,6 +141,14 @@ E2fAttnWs e2f_attn_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, int v_layo
     L.lists_ent = nullptr;
     L.lists_pos = nullptr;
     L.lists_mask = nullptr;
+    auto take_lists = [&](size_t n_tiles) {   // positions, masks, entries of all tiles, one behind the other
+        static_assert(E2F_TILE_LCAP * (3 * sizeof(float4) + 8 + 4) <= E2F_TILE_LIST_BYTES, "the three arrays fit a tile's share");
+        char* p = take(n_tiles * E2F_TILE_LIST_BYTES);
+        if (!p) return;
+        L.lists_pos = (float4*)p;
+        L.lists_mask = (unsigned long long*)(p + n_tiles * E2F_TILE_LCAP * 3 * sizeof(float4));
+        L.lists_ent = (int*)(L.lists_mask + n_tiles * E2F_TILE_LCAP);
+    };
     if (v_layout == 2) {
         const size_t H = ctx->cfg.H, DKP = ((size_t)(ctx->cfg.L_max + 1) * 16 + 31) / 32 * 32;
         const size_t N4 = ((size_t)N + 3) / 4 * 4;
@@ -150,9 +158,7 @@ E2fAttnWs e2f_attn_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, int v_layo
         L.G = (float*)take((size_t)(3 * E2F_MAX_N * E2F_MAX_N + 256) * 4);   // full form, then the packed non-zeros
         const size_t n_tiles = ((size_t)N + 15) / 16;
         L.lists_hdr = (int4*)take(n_tiles * sizeof(int4));
-        L.lists_ent = (int*)take(n_tiles * E2F_TILE_LCAP * 4);
-        L.lists_pos = (float4*)take(n_tiles * E2F_TILE_LCAP * 4 * sizeof(float4));
-        L.lists_mask = (unsigned long long*)take(n_tiles * E2F_TILE_LCAP * 8);
+        take_lists(n_tiles);
         if (!e2f_tile_layouts_direct(ctx)) {   // the projection's plain layouts, turned into the ones above by a relayout kernel
             L.q = (float*)take((size_t)N * (ctx->cfg.L_max + 1) * ctx->cfg.C * 4);
             L.k = (float*)take((size_t)N * (ctx->cfg.L_max + 1) * ctx->cfg.C * 4);
@@ -167,9 +173,7 @@ E2fAttnWs e2f_attn_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, int v_layo
             L.G = (float*)take((size_t)(3 * E2F_MAX_N * E2F_MAX_N + 256) * 4);
             const size_t n_tiles = ((size_t)N + 15) / 16;
             L.lists_hdr = (int4*)take(n_tiles * sizeof(int4));
-            L.lists_ent = (int*)take(n_tiles * E2F_TILE_LCAP * 4);
-            L.lists_pos = (float4*)take(n_tiles * E2F_TILE_LCAP * 4 * sizeof(float4));
-            L.lists_mask = (unsigned long long*)take(n_tiles * E2F_TILE_LCAP * 8);
+            take_lists(n_tiles);
         }
         L.q = (float*)take((size_t)N * (ctx->cfg.L_max + 1) * ctx->cfg.C * 4);
         L.k = (float*)take((size_t)N * (ctx->cfg.L_max + 1) * ctx->cfg.C * 4);

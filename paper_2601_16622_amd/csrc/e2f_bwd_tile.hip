@@ -188,13 +188,15 @@ __global__ __launch_bounds__(256) void k_bwd_relayout_g(BwdTileParams P) {
 // not written (whole workgroup).  Ends with a barrier.
 __device__ __forceinline__ int load_list(const BwdTileParams& P, int tile, int tid, const float4& tp, int* s_ent,
                                          unsigned long long* s_mask, float4* s_pos) {
-    static_assert(LCAP * 4 == 3 * 256 && LCAP <= 256, "one request per thread");
+    static_assert(LCAP <= 256, "one request per thread");
     const int4 hd = P.lists_hdr[tile];
-    const int ent_mine = tid < LCAP ? P.lists_ent[(size_t)tile * LCAP + tid] : 0;
-    const unsigned long long mask_mine = tid < LCAP ? P.lists_mask[(size_t)tile * LCAP + tid] : 0ull;
+    // (clamped, not conditional: a condition that falls back to a loaded value would wait for that value first)
+    const int ent_mine = P.lists_ent[(size_t)tile * LCAP + min(tid, LCAP - 1)];
+    const unsigned long long mask_mine = P.lists_mask[(size_t)tile * LCAP + min(tid, LCAP - 1)];
     float4 pos_mine[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) pos_mine[j] = P.lists_pos[(size_t)tile * LCAP * 4 + tid + 256 * j];
+    for (int j = 0; j < 3; ++j)
+        pos_mine[j] = P.lists_pos[(size_t)tile * LCAP * 3 + min(tid + 256 * j, LCAP * 3 - 1)];
     const int cnt = hd.x;
     if (cnt < 0) return -1;
     if (tid < LCAP) {
@@ -207,11 +209,13 @@ __device__ __forceinline__ int load_list(const BwdTileParams& P, int tile, int t
     }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {   // (selected by value: a select between two register arrays would move both to scratch)
-        const bool in_list = ((tid + 256 * j) >> 2) < cnt;
-        s_pos[tid + 256 * j] = make_float4(in_list ? pos_mine[j].x : tp.x, in_list ? pos_mine[j].y : tp.y,
-                                           in_list ? pos_mine[j].z : tp.z, in_list ? pos_mine[j].w : tp.w);
+        const bool in_list = tid + 256 * j < 3 * cnt;
+        const float4 far = splat_xyz(tp, (tid + 256 * j) % 3);
+        s_pos[tid + 256 * j] = make_float4(in_list ? pos_mine[j].x : far.x, in_list ? pos_mine[j].y : far.y,
+                                           in_list ? pos_mine[j].z : far.z, in_list ? pos_mine[j].w : far.w);
     }
-    if (tid < (LENT - LCAP) * 4) s_pos[LCAP * 4 + tid] = tp;
+    static_assert(3 * LENT >= 3 * 256 && 3 * (LENT - 256) <= 256, "the rows above reach entry 255, the next line the end");
+    if (tid < 3 * (LENT - 256)) s_pos[3 * 256 + tid] = splat_xyz(tp, tid % 3);
     __syncthreads();
     return cnt;
 }
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
     static_assert(16 * (DKP / 8) <= 256, "one request per thread");
     __shared__ int s_ent[LENT];
     __shared__ unsigned long long s_mask[LENT];
-    __shared__ float4 s_pos[LENT * 4];
+    __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_q[16 * DKP];
     __shared__ float s_m[NW][16], s_zz[NW][16], s_D[16];
     const int HG = P.H / P.hpw;
@@ -295,10 +299,10 @@ __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
             for (int mt = 0; mt < 2; ++mt) {
                 const int ei = 8 * c + 4 * mt + g;
                 const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));
+                const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float4 pc = s_pos[ei * 4 + r];
-                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                     const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                     const float d = __builtin_amdgcn_sqrtf(d2);
                     float bias = bias_value<NB>(cb, d, d2, c_u, c_g, P.rbf_step);
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     static_assert(16 * (DKP / 8) <= 256, "one request per thread");
     __shared__ int s_ent[LENT];
     __shared__ unsigned long long s_mask[LENT];
-    __shared__ float4 s_pos[LENT * 4];
+    __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_rows[16 * DKP];
     __shared__ float s_gp[NW][16][3];
     __shared__ float s_wb[NW][8];
@@ -550,11 +554,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             auto scalars = [&](int mt) {
                 const int ei = 8 * c + 4 * mt + g;
                 const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));
+                const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int u = 4 * mt + r;
-                    const float4 pc = s_pos[ei * 4 + r];
-                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                     const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                     const float d = __builtin_amdgcn_sqrtf(d2);
                     float bias, dbias;   // the bias in base-2 units, its derivative in natural units
@@ -589,14 +593,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             float ds[8];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
-                const int ei = 8 * c + 4 * mt + g;
+                const SlotPos pc = slot_pos(s_pos, 8 * c + 4 * mt + g);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int u = 4 * mt + r;
-                    const float4 pc = s_pos[ei * 4 + r];
                     // r_ij = pos_j - pos_i: candidate minus tile atom for targets, the reverse for sources
-                    const float rx = SRC ? tp.x - pc.x : pc.x - tp.x, ry = SRC ? tp.y - pc.y : pc.y - tp.y,
-                                rz = SRC ? tp.z - pc.z : pc.z - tp.z;
+                    const float rx = SRC ? tp.x - pc.x[r] : pc.x[r] - tp.x, ry = SRC ? tp.y - pc.y[r] : pc.y[r] - tp.y,
+                                rz = SRC ? tp.z - pc.z[r] : pc.z[r] - tp.z;
                     const float d2 = rx * rx + ry * ry + rz * rz;
                     const float rd = p[u] > 0.0f ? __builtin_amdgcn_rsqf(d2) : 0.0f;
                     const float u0 = U[0][mt][r], u1 = U[1][mt][r], u2 = U[2][mt][r];
@@ -706,7 +709,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     static_assert(16 * (DKP / 8) <= 256, "one request per thread");
     __shared__ int s_ent[LENT];
     __shared__ unsigned long long s_mask[LENT];
-    __shared__ float4 s_pos[LENT * 4];
+    __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_rows[16 * DKP];
     __shared__ float s_G[AXIS_NNZ];
     __shared__ float s_Gu[WGR ? AXIS_NNZ : 1];
@@ -820,12 +823,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int u = 0; u < 8; u += 2) {
                     float pg[2], rx[2], ry[2], rz[2];
+                    const int mt = u >> 2, ei = 8 * cm + 4 * mt + g;
+                    const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));
+                    const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
                     for (int dd = 0; dd < 2; ++dd) {
-                        const int uu_ = u + dd, mt = uu_ >> 2, r = uu_ & 3, ei = 8 * cm + 4 * mt + g;
-                        const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));
-                        const float4 pc = s_pos[ei * 4 + r];
-                        const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                        const int r = (u + dd) & 3;
+                        const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                         const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                         const float d = __builtin_amdgcn_sqrtf(d2);
                         float bias = bias_value<NB>(cb, d, d2, c_u, c_g, P.rbf_step);
@@ -833,9 +837,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         const float lse = r == 0 ? st[mt][0].x : r == 1 ? st[mt][0].z : r == 2 ? st[mt][1].x : st[mt][1].z;
                         const float p = ok ? __builtin_amdgcn_exp2f(S[mt][r] + bias - lse) : 0.0f;
                         pg[dd] = p * e2f::radial_gate(d, P.cutoff);
-                        rx[dd] = tp.x - pc.x;   // r_ij = pos_j - pos_i with j the tile's atom
-                        ry[dd] = tp.y - pc.y;
-                        rz[dd] = tp.z - pc.z;
+                        rx[dd] = tp.x - pc.x[r];   // r_ij = pos_j - pos_i with j the tile's atom
+                        ry[dd] = tp.y - pc.y[r];
+                        rz[dd] = tp.z - pc.z[r];
                     }
                     wp[0][u >> 1] = pack_bf16(pg[0] * rx[0], pg[1] * rx[1]);
                     wp[1][u >> 1] = pack_bf16(pg[0] * ry[0], pg[1] * ry[1]);

@@ -91,7 +91,7 @@ struct E2fAttnWs {
     // candidate lists of the tile kernel, one per tile of 16 sorted slots (see TileParams)
     int4* lists_hdr;     // [ceil(N/16)]
     int* lists_ent;      // [ceil(N/16)][E2F_TILE_LCAP]
-    float4* lists_pos;   // [ceil(N/16)][E2F_TILE_LCAP][4]
+    float4* lists_pos;   // [ceil(N/16)][E2F_TILE_LCAP][3] x, y and z of the four slots
     unsigned long long* lists_mask;   // [ceil(N/16)][E2F_TILE_LCAP] the (target, slot) pairs of an entry that count
     // layout of the fp32 tile kernel (v_layout 3: beside the plain q, k, v)
     float* qf;           // [N][H][DK] q * tau * log2(e)
@@ -99,7 +99,10 @@ struct E2fAttnWs {
     float* vf;           // [ceil(N/4)][H][n][16 channels][4 slots]
     size_t bytes;
 };
-#define E2F_TILE_LCAP 192
+// A tile's list: 60 bytes an entry (group 4, slot positions 48, pair mask 8).  The 16 tiles of largest count among some
+// 3 700 of bulk cells at 0.1 atoms per cubic Angstrom and a 6 Angstrom cutoff have 180 to 196 entries (mean 119).
+#define E2F_TILE_LCAP 240
+#define E2F_TILE_LIST_BYTES 14592
 // v_layout: 0 plain [N][n][C], 1 component tiles of the per-pair MFMA kernel, 2 slot groups of the tile kernel,
 // 3 plain plus the fp32 tile kernel's layouts and lists
 E2fAttnWs e2f_attn_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, int v_layout);

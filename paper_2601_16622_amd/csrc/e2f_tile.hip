@@ -32,7 +32,7 @@ struct TileParams {
     const int32_t* cap_idx;
     float* out;
     // candidate lists built once per tile for all heads, or null: header (entries or -1 = build the list in the
-    // kernel; pass of every target, 4 bits each), entries, positions of the entries' four slots (images included)
+    // kernel; pass of every target, 4 bits each), entries, x, y and z of the entries' four slots (images included)
     int4* lists_hdr;
     int* lists_ent;
     float4* lists_pos;
@@ -98,7 +98,7 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
     constexpr int LU = 64 / NW / 4;     // steps of 16 slot groups per wave and batch (256 groups per batch)
     constexpr int DK = (L + 1) * 16, KS = (DK + 31) / 32, DKP = KS * 32;
     // LDS: the list and the weights while streaming; the same bytes hold the partial outputs at the end
-    constexpr int LIST_BYTES = (CAPG + PADE) * 4 + (CAPG + PADE) * 4 * 16, W_BYTES = NW * 3 * 64 * 16;
+    constexpr int LIST_BYTES = (CAPG + PADE) * 4 + (CAPG + PADE) * 3 * 16, W_BYTES = NW * 3 * 64 * 16;
     constexpr int PO_BYTES = n * 64 * 16;   // one mu of the accumulators of all waves
     constexpr int MAIN_BYTES = LIST_BYTES + W_BYTES > PO_BYTES ? LIST_BYTES + W_BYTES : PO_BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char s_raw[MAIN_BYTES];
@@ -107,16 +107,22 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
     __shared__ float s_cmax[NW][16];
     __shared__ float s_z[NW][16];
     __shared__ int s_cnt[NW];
-    // which (target, slot) pairs of a list entry count, bit 4 * target + slot: the valid slots for every target of the
-    // entry's pass, or, with a neighbour table, the listed atoms
+    // Which (target, slot) pairs of a list entry count, bit 4 * target + slot: the valid slots for every target of the
+    // entry's pass, or, with a neighbour table, the listed atoms, or, with a cap, the pairs under the targets' threshold
+    // keys (the cap's test needs the candidate's atom index, which the lists in memory do not carry; the cutoff is tested
+    // where the distance is needed: done here for every slot it took 7 us more per launch and gave the heads nothing).
     __shared__ unsigned long long s_mask[CAPG + PADE];
-    __shared__ float4 s_tgt[16];   // the pass's targets: position and squared reach (0: not in this pass)
+    // the pass's targets: position and squared reach (0: not in this pass); with a cap the position as it is (at
+    // infinity: not in this pass) and the threshold keys beside it
+    __shared__ float4 s_tgt[16];
+    __shared__ int2 s_tcap[CAP ? 16 : 1];
     // periodic boundaries: the pass's candidate runs (first and last slot, slot groups before the run, translation)
     constexpr int NRUN = PBC ? 27 : 9;
     __shared__ int s_rlo[32], s_rhi[32], s_rpre[32];
     __shared__ float4 s_rsh[PBC ? 32 : 1];
     int* s_ent = reinterpret_cast<int*>(s_raw);
-    float4* s_pos = reinterpret_cast<float4*>(s_raw + (CAPG + PADE) * 4);
+    float4* s_pos = reinterpret_cast<float4*>(s_raw + (CAPG + PADE) * 4);   // x, y, z of an entry's four slots
+    float* s_posf = reinterpret_cast<float*>(s_pos);
     u32x4* s_W = reinterpret_cast<u32x4*>(s_raw + LIST_BYTES);   // [chunk of the group][mu][lane]
     f32x4* s_po = reinterpret_cast<f32x4*>(s_raw);
 
@@ -205,13 +211,16 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
         {
             __syncthreads();   // every wave has finished with the previous pass's table
             if (threadIdx.x < 16) {
-                // |p - t|^2 < reach^2 as |q|^2 + q.(-2u) + (|u|^2 - reach^2) < 0 with q = p - o, u = t - o around the
-                // tile's first target o (small numbers, so the expanded square keeps its accuracy); with a
-                // neighbour cap a target reaches no further than its threshold distance
-                const float reach2 = capd == 0xffffffffu ? P.rc2 : fminf(P.rc2, __uint_as_float(capd));
-                const float ux = tp.x - read_lane(tp.x, 0), uy = tp.y - read_lane(tp.y, 0), uz = tp.z - read_lane(tp.z, 0);
-                s_tgt[threadIdx.x] = make_float4(-2.0f * ux, -2.0f * uy, -2.0f * uz,
-                                                 t_active ? ux * ux + uy * uy + uz * uz - reach2 * 1.001f : INFINITY);
+                if constexpr (CAP) {
+                    s_tgt[threadIdx.x] = make_float4(t_active ? tp.x : INFINITY, tp.y, tp.z, 0.0f);
+                    s_tcap[threadIdx.x] = make_int2((int)capd, capi);
+                } else {
+                    // |p - t|^2 < rc^2 as |q|^2 + q.(-2u) + (|u|^2 - rc^2) < 0 with q = p - o, u = t - o around the
+                    // tile's first target o (small numbers, so the expanded square keeps its accuracy)
+                    const float ux = tp.x - origin.x, uy = tp.y - origin.y, uz = tp.z - origin.z;
+                    s_tgt[threadIdx.x] = make_float4(-2.0f * ux, -2.0f * uy, -2.0f * uz,
+                                                     t_active ? ux * ux + uy * uy + uz * uz - P.rc2 * 1.001f : INFINITY);
+                }
             }
             // shape of the pass's grid from the first target's record; box lengths (periodic only) from the grid
             struct { int nx, ny, nz, base; float lx, ly, lz; } G;
@@ -278,7 +287,8 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
             int cnt = 0;
             {
             int grp[LU];
-            unsigned near4[LU], valid4[LU];
+            unsigned valid4[LU], mlo[CAP ? LU : 1], mhi[CAP ? LU : 1];   // with a cap: the pairs of targets 0..7 and 8..15
+            bool keep[LU];
             unsigned long long leaders[LU];
             float4 pj[LU];
             {
@@ -311,31 +321,55 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                         pj[u].z += sh.z;
                     }
                 }
-                bool nearby[LU];
-                float qx[LU], qy[LU], qz[LU], qq[LU];
-#pragma unroll
-                for (int u = 0; u < LU; ++u) {
-                    nearby[u] = false;
-                    qx[u] = pj[u].x - origin.x;
-                    qy[u] = pj[u].y - origin.y;
-                    qz[u] = pj[u].z - origin.z;
-                    qq[u] = qx[u] * qx[u] + qy[u] * qy[u] + qz[u] * qz[u];
-                }
-#pragma unroll
-                for (int tt = 0; tt < 16; ++tt) {
-                    const float4 tg = s_tgt[tt];
-#pragma unroll
-                    for (int u = 0; u < LU; ++u)
-                        nearby[u] |= qx[u] * tg.x + (qy[u] * tg.y + (qz[u] * tg.z + (qq[u] + tg.w))) < 0.0f;
-                }
                 int mine = 0;
 #pragma unroll
+                for (int u = 0; u < LU; ++u) valid4[u] = (unsigned)(__ballot(valid[u]) >> (lane & ~3)) & 0xFu;
+                if constexpr (CAP) {
+                    // (the target itself is at distance zero, an image of it at a box length: neither passes)
+#pragma unroll
+                    for (int u = 0; u < LU; ++u) mlo[u] = mhi[u] = 0u;
+#pragma unroll
+                    for (int tt = 0; tt < 16; ++tt) {
+                        const float4 tg = s_tgt[tt];
+                        const int2 tc = s_tcap[tt];
+#pragma unroll
+                        for (int u = 0; u < LU; ++u) {
+                            const float d2 = e2f::dist2_exact(tg.x, tg.y, tg.z, pj[u].x, pj[u].y, pj[u].z);
+                            const bool ok = (d2 < P.rc2) & (d2 > 0.0f) & e2f::under_cap(d2, pj[u].w, (uint32_t)tc.x, tc.y);
+                            (tt < 8 ? mlo[u] : mhi[u]) |= ok ? 1u << (4 * (tt & 7)) : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < LU; ++u) {
+                        mlo[u] = quad_or(valid[u] ? mlo[u] << (lane & 3) : 0u);
+                        mhi[u] = quad_or(valid[u] ? mhi[u] << (lane & 3) : 0u);
+                        keep[u] = (mlo[u] | mhi[u]) != 0u;
+                    }
+                } else {
+                    bool nearby[LU];
+                    float qx[LU], qy[LU], qz[LU], qq[LU];
+#pragma unroll
+                    for (int u = 0; u < LU; ++u) {
+                        nearby[u] = false;
+                        qx[u] = pj[u].x - origin.x;
+                        qy[u] = pj[u].y - origin.y;
+                        qz[u] = pj[u].z - origin.z;
+                        qq[u] = qx[u] * qx[u] + qy[u] * qy[u] + qz[u] * qz[u];
+                    }
+#pragma unroll
+                    for (int tt = 0; tt < 16; ++tt) {
+                        const float4 tg = s_tgt[tt];
+#pragma unroll
+                        for (int u = 0; u < LU; ++u)
+                            nearby[u] |= qx[u] * tg.x + (qy[u] * tg.y + (qz[u] * tg.z + (qq[u] + tg.w))) < 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < LU; ++u)
+                        keep[u] = ((__ballot(valid[u] && nearby[u]) >> (lane & ~3)) & 0xFull) != 0ull;
+                }
+#pragma unroll
                 for (int u = 0; u < LU; ++u) {
-                    const bool near = valid[u] && nearby[u];
-                    const int sh = lane & ~3;
-                    near4[u] = (unsigned)(__ballot(near) >> sh) & 0xFu;
-                    valid4[u] = (unsigned)(__ballot(valid[u]) >> sh) & 0xFu;
-                    leaders[u] = __ballot(near4[u] != 0u && (lane & 3) == 0);
+                    leaders[u] = __ballot(keep[u] && (lane & 3) == 0);
                     mine += __popcll(leaders[u]);
                 }
                 if (lane == 0) s_cnt[wave] = mine;
@@ -352,17 +386,21 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
             for (int u = 0; u < LU; ++u) {
                 const int sh = lane & ~3;
                 const int e = e0 + __popcll(leaders[u] & ((1ull << sh) - 1ull));
-                if (near4[u] != 0u) {
+                if (keep[u]) {
                     if ((lane & 3) == 0) {
                         s_ent[e] = (int)(((unsigned)grp[u] << 8) | ((MODE == 1 ? (unsigned)pidx : 0u) << 4) | valid4[u]);
-                        s_mask[e] = P.table ? 0ull : (unsigned long long)valid4[u] * pass_nibbles;
+                        if constexpr (CAP) s_mask[e] = ((unsigned long long)mhi[u] << 32) | mlo[u];
+                        else s_mask[e] = P.table ? 0ull : (unsigned long long)valid4[u] * pass_nibbles;
                     }
-                    s_pos[e * 4 + (lane & 3)] = pj[u];
+                    float* sp = s_posf + e * 12 + (lane & 3);
+                    sp[0] = pj[u].x;
+                    sp[4] = pj[u].y;
+                    sp[8] = pj[u].z;
                 }
                 e0 += __popcll(leaders[u]);
             }
             }
-            if (P.table) {
+            if (!CAP && P.table) {   // (a call has a cap or a table)
                 // ---- neighbour table: the listed atoms of the pass's targets, looked up in the batch (an atom outside
                 // the cutoff has no entry there and is skipped, like an empty table entry or the target itself)
                 __syncthreads();
@@ -387,9 +425,9 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                 if (out_cnt + cnt > LCAP) overflow = true;
                 if (!overflow) {
                     int* ge = P.lists_ent + (size_t)tile * LCAP + out_cnt;
-                    float4* gp = P.lists_pos + ((size_t)tile * LCAP + out_cnt) * 4;
+                    float4* gp = P.lists_pos + ((size_t)tile * LCAP + out_cnt) * 3;
                     for (int i = threadIdx.x; i < cnt; i += 64 * NW) ge[i] = s_ent[i];
-                    for (int i = threadIdx.x; i < 4 * cnt; i += 64 * NW) gp[i] = s_pos[i];
+                    for (int i = threadIdx.x; i < 3 * cnt; i += 64 * NW) gp[i] = s_pos[i];
                     for (int i = threadIdx.x; i < cnt; i += 64 * NW) P.lists_mask[(size_t)tile * LCAP + out_cnt + i] = s_mask[i];
                     out_cnt += cnt;
                 }
@@ -400,7 +438,7 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                 s_ent[cnt + i] = 0;
                 s_mask[cnt + i] = 0ull;
             }
-            for (int i = threadIdx.x; i < PADE * 4; i += 64 * NW) s_pos[cnt * 4 + i] = tp;
+            for (int i = threadIdx.x; i < PADE * 3; i += 64 * NW) s_pos[cnt * 3 + i] = splat_xyz(tp, i % 3);
             __syncthreads();
             const int nch = (cnt + 7) >> 3, ngr = (nch + NW - 1) / NW;
             if (ngr > 0) {
@@ -453,15 +491,14 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                     for (int mt = 0; mt < 2; ++mt) {
                         const int ei = 8 * cm + 4 * mt + g;
                         const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));   // this target's four slots of the entry
+                        const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int u = 4 * mt + r;
-                            const float4 pc = s_pos[ei * 4 + r];
-                            const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                            const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                             // (bitwise on purpose: the eight candidates are evaluated side by side; the target itself
                             // is at distance zero, an image of it at a box length: neither passes)
-                            const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f) &
-                                            (!CAP || e2f::under_cap(d2, pc.w, capd, capi));
+                            const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                             const float d = __builtin_amdgcn_sqrtf(d2);
                             float bias = bias_value<NB>(cb, d, d2, c_u, c_g, P.rbf_step);
                             // (evaluated for every candidate, not under its predicate: otherwise each of the eight
@@ -508,15 +545,15 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
 #pragma unroll
                         for (int u = 0; u < 8; u += 2) {
                             float pg[2], rx[2], ry[2], rz[2];
+                            const SlotPos pc = slot_pos(s_pos, 8 * cm + 4 * (u >> 2) + g);
 #pragma unroll
                             for (int d = 0; d < 2; ++d) {
                                 const float p = __builtin_amdgcn_exp2f(s2[u + d] - m_ref);
                                 z += p;
                                 pg[d] = p * gate[u + d];
-                                const float4 pc = s_pos[(8 * cm + 4 * ((u + d) >> 2) + g) * 4 + ((u + d) & 3)];
-                                rx[d] = pc.x - tp.x;
-                                ry[d] = pc.y - tp.y;
-                                rz[d] = pc.z - tp.z;
+                                rx[d] = pc.x[(u + d) & 3] - tp.x;
+                                ry[d] = pc.y[(u + d) & 3] - tp.y;
+                                rz[d] = pc.z[(u + d) & 3] - tp.z;
                             }
                             wp[0][u >> 1] = pack_bf16(pg[0] * rx[0], pg[1] * rx[1]);
                             wp[1][u >> 1] = pack_bf16(pg[0] * ry[0], pg[1] * ry[1]);
@@ -576,8 +613,8 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
             // workgroup runs the tile's heads itself, one after the other, building the lists per head.  The axis
             // operators of this launch may not be there yet (another workgroup forms them), so it forms its own
             // copy in the tile's list area, which stays unused.
-            float* own_G = reinterpret_cast<float*>(P.lists_pos + (size_t)tile * LCAP * 4);
-            static_assert((size_t)LCAP * 4 * sizeof(float4) >= (AXIS_PACKED_AT + AXIS_NNZ) * sizeof(float), "room for the operators");
+            float* own_G = reinterpret_cast<float*>(P.lists_pos + (size_t)tile * LCAP * 3);
+            static_assert((size_t)LCAP * 3 * sizeof(float4) >= (AXIS_PACKED_AT + AXIS_NNZ) * sizeof(float), "room for the operators");
             axis_ops<L>(P.cw, own_G, threadIdx.x, true);
             __threadfence_block();
             __syncthreads();
@@ -668,7 +705,7 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
 // the axis operators) is fetched once, all of it requested before any of it is used, and stays in LDS for every head;
 // what belongs to a head (its queries, its radial weights, the key and value rows of the first chunks) is requested
 // while the head before it is in its epilogue.  The streaming loop and the epilogue are those of tile_item.
-template <int L, bool CAP, int NB>
+template <int L, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_tile_heads(TileParams P) {
     constexpr int NW = 4, n = (L + 1) * (L + 1), NX = (n + NW - 1) / NW;
     constexpr int DK = (L + 1) * 16, KS = (DK + 31) / 32, DKP = KS * 32;
@@ -676,7 +713,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int W_BYTES = NW * 3 * 64 * 16, PO_BYTES = n * 64 * 16;
     __shared__ int s_ent[LENT];
     __shared__ unsigned long long s_mask[LENT];
-    __shared__ float4 s_pos[LENT * 4];
+    __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_q[16 * DKP];
     __shared__ float s_G[AXIS_NNZ];
     __shared__ float s_cmax[NW][16];
@@ -686,7 +723,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(16))) unsigned char s_raw[W_BYTES > PO_BYTES ? W_BYTES : PO_BYTES];
     u32x4* s_W = reinterpret_cast<u32x4*>(s_raw);
     f32x4* s_po = reinterpret_cast<f32x4*>(s_raw);
-    static_assert(LCAP * 4 == 3 * 256 && LCAP <= 256 && 16 * (DKP / 8) <= 256 && AXIS_NNZ <= 256, "one request per thread");
+    static_assert(LCAP <= 256 && 16 * (DKP / 8) <= 256 && AXIS_NNZ <= 256, "one request per thread");
 
     const int HG = P.H / P.hpw;
     int tile, hg;
@@ -708,15 +745,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- everything the tile needs, requested together
     const int4 hd = P.lists_hdr[tile];
     const float4 tp = P.spos[tslot];
-    const uint32_t capd = CAP ? P.cap_d2[tslot] : 0xffffffffu;
-    const int capi = CAP ? P.cap_idx[tslot] : INT_MAX;
     const int orow_mine = tid < 16 ? (t0 + tid < N ? P.cv.perm[t0 + tid] : -1) : 0;   // output rows of the targets
     const float g_mine = tid < AXIS_NNZ ? P.G[AXIS_PACKED_AT + tid] : 0.0f;
-    const int ent_mine = tid < LCAP ? P.lists_ent[(size_t)tile * LCAP + tid] : 0;
-    const unsigned long long mask_mine = tid < LCAP ? P.lists_mask[(size_t)tile * LCAP + tid] : 0ull;
+    // (clamped, not conditional: a condition that falls back to a loaded value would wait for that value first)
+    const int ent_mine = P.lists_ent[(size_t)tile * LCAP + min(tid, LCAP - 1)];
+    const unsigned long long mask_mine = P.lists_mask[(size_t)tile * LCAP + min(tid, LCAP - 1)];
     float4 pos_mine[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) pos_mine[j] = P.lists_pos[(size_t)tile * LCAP * 4 + tid + 256 * j];
+    for (int j = 0; j < 3; ++j)
+        pos_mine[j] = P.lists_pos[(size_t)tile * LCAP * 3 + min(tid + 256 * j, LCAP * 3 - 1)];
     // queries (16 targets x DKP binary16 of one head: one 16-byte piece per thread) and radial weights of a head
     auto fetch_q = [&](int head) -> u32x4 {
         const int tq = tid / (DKP / 8), f8 = tid % (DKP / 8);
@@ -742,11 +779,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int j = 0; j < 3; ++j) {   // (selected by value, component by component: the compiler would otherwise choose
         // between the addresses of two register arrays and move both into scratch memory)
-        const bool in_list = ((tid + 256 * j) >> 2) < cnt;
-        s_pos[tid + 256 * j] = make_float4(in_list ? pos_mine[j].x : tp.x, in_list ? pos_mine[j].y : tp.y,
-                                           in_list ? pos_mine[j].z : tp.z, in_list ? pos_mine[j].w : tp.w);
+        const bool in_list = tid + 256 * j < 3 * cnt;
+        const float4 far = splat_xyz(tp, (tid + 256 * j) % 3);
+        s_pos[tid + 256 * j] = make_float4(in_list ? pos_mine[j].x : far.x, in_list ? pos_mine[j].y : far.y,
+                                           in_list ? pos_mine[j].z : far.z, in_list ? pos_mine[j].w : far.w);
     }
-    if (tid < (LENT - LCAP) * 4) s_pos[LCAP * 4 + tid] = tp;
+    static_assert(3 * LENT >= 3 * 256 && 3 * (LENT - 256) <= 256, "the rows above reach entry 255, the next line the end");
+    if (tid < 3 * (LENT - 256)) s_pos[3 * 256 + tid] = splat_xyz(tp, tid % 3);
     if (tid < AXIS_NNZ) s_G[tid] = g_mine;
     if (tid < 16) s_orow[tid] = orow_mine;
     if (tid < 16 * (DKP / 8)) reinterpret_cast<u32x4*>(s_q)[tid] = q_mine;
@@ -827,15 +866,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int mt = 0; mt < 2; ++mt) {
                 const int ei = 8 * cm + 4 * mt + g;
                 const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));   // this target's four slots of the entry
+                const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int u = 4 * mt + r;
-                    const float4 pc = s_pos[ei * 4 + r];
-                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                    const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                     // (bitwise on purpose: the eight candidates are evaluated side by side; the target itself is at
                     // distance zero, an image of it at a box length: neither passes)
-                    const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f) &
-                                    (!CAP || e2f::under_cap(d2, pc.w, capd, capi));
+                    const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                     const float d = __builtin_amdgcn_sqrtf(d2);
                     float bias = bias_value<NB>(cb, d, d2, c_u, c_g, P.rbf_step);
                     // (evaluated for every candidate, not under its predicate: otherwise each of the eight
@@ -881,15 +919,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int u = 0; u < 8; u += 2) {
                     float pg[2], rx[2], ry[2], rz[2];
+                    const SlotPos pc = slot_pos(s_pos, 8 * cm + 4 * (u >> 2) + g);
 #pragma unroll
                     for (int d = 0; d < 2; ++d) {
                         const float p = __builtin_amdgcn_exp2f(s2[u + d] - m_ref);
                         z += p;
                         pg[d] = p * gate[u + d];
-                        const float4 pc = s_pos[(8 * cm + 4 * ((u + d) >> 2) + g) * 4 + ((u + d) & 3)];
-                        rx[d] = pc.x - tp.x;
-                        ry[d] = pc.y - tp.y;
-                        rz[d] = pc.z - tp.z;
+                        rx[d] = pc.x[(u + d) & 3] - tp.x;
+                        ry[d] = pc.y[(u + d) & 3] - tp.y;
+                        rz[d] = pc.z[(u + d) & 3] - tp.z;
                     }
                     wp[0][u >> 1] = pack_bf16(pg[0] * rx[0], pg[1] * rx[1]);
                     wp[1][u >> 1] = pack_bf16(pg[0] * ry[0], pg[1] * ry[1]);
@@ -1041,7 +1079,7 @@ void launch_L(const TileParams& P, const float* cw, float* G, int what, hipStrea
         constexpr bool PBC = decltype(pbc)::value, CAP = decltype(capped)::value;
         if (P.B > 8) {
             if (what == 1) k_tile<L, 4, PBC, 1, CAP, 16><<<P.n_tiles + 1, 256, 0, st>>>(P);
-            else if (what == 2) k_tile_heads<L, CAP, 16><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
+            else if (what == 2) k_tile_heads<L, 16><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
             else {
                 k_axis_ops<L><<<1, 128, 0, st>>>(cw, G, true);
                 k_tile<L, 4, PBC, 0, CAP, 16><<<grid, 256, 0, st>>>(P);
@@ -1051,7 +1089,7 @@ void launch_L(const TileParams& P, const float* cw, float* G, int what, hipStrea
         if (what == 1) {
             k_tile<L, 4, PBC, 1, CAP, 8><<<P.n_tiles + 1, 256, 0, st>>>(P);
         } else if (what == 2) {
-            k_tile_heads<L, CAP, 8><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
+            k_tile_heads<L, 8><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
         } else {
             k_axis_ops<L><<<1, 128, 0, st>>>(cw, G, true);
             k_tile<L, 4, PBC, 0, CAP, 8><<<grid, 256, 0, st>>>(P);

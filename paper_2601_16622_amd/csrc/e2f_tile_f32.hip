@@ -77,7 +77,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int W_BYTES = NW * 3 * 2 * 64 * 16, PO_BYTES = n * 64 * 16;
     __shared__ int s_ent[LENT8];
     __shared__ unsigned long long s_mask[LENT8];
-    __shared__ float4 s_pos[LENT8 * 4];
+    __shared__ float4 s_pos[LENT8 * 3];
     __shared__ __attribute__((aligned(16))) float s_q[16 * DK];
     __shared__ float s_G[AXIS_NNZ];
     __shared__ float s_cmax[NW][16];
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     f32x4* s_W = reinterpret_cast<f32x4*>(s_raw);   // [chunk of the group][mu][half][lane]
     f32x4* s_po = reinterpret_cast<f32x4*>(s_raw);
     static_assert(LCAP <= NT && 16 * DK / 4 <= 2 * NT && AXIS_NNZ <= NT, "one request per thread (two for the queries)");
-    constexpr int NPOS = (LENT8 * 4 + NT - 1) / NT;   // slot positions per thread
+    constexpr int NPOS = (LENT8 * 3 + NT - 1) / NT;   // slot positions per thread
 
     int tile, head;
     if (!tile_xcd_remap(blockIdx.x, P.n_tiles, P.blk, P.H, tile, head)) return;   // whole workgroup
@@ -105,12 +105,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const float4 tp = P.spos[tslot];
     const int orow_mine = tid < 16 ? (t0 + tid < N ? P.cv.perm[t0 + tid] : -1) : 0;
     const float g_mine = tid < AXIS_NNZ ? P.G[AXIS_PACKED_AT + tid] : 0.0f;
-    const int ent_mine = tid < LCAP ? P.lists_ent[(size_t)tile * LCAP + tid] : 0;
-    const unsigned long long mask_mine = tid < LCAP ? P.lists_mask[(size_t)tile * LCAP + tid] : 0ull;
+    // (clamped, not conditional: a condition that falls back to a loaded value would wait for that value first)
+    const int ent_mine = P.lists_ent[(size_t)tile * LCAP + min(tid, LCAP - 1)];
+    const unsigned long long mask_mine = P.lists_mask[(size_t)tile * LCAP + min(tid, LCAP - 1)];
     float4 pos_mine[NPOS];
 #pragma unroll
     for (int j = 0; j < NPOS; ++j)
-        pos_mine[j] = tid + NT * j < LCAP * 4 ? P.lists_pos[(size_t)tile * LCAP * 4 + tid + NT * j] : tp;
+        pos_mine[j] = P.lists_pos[(size_t)tile * LCAP * 3 + min(tid + NT * j, LCAP * 3 - 1)];
     f32x4 q_mine[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -134,10 +135,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int j = 0; j < NPOS; ++j) {   // (selected by value, component by component)
         const int at = tid + NT * j;
-        const bool in_list = (at >> 2) < cnt;
-        if (at < LENT8 * 4)
-            s_pos[at] = make_float4(in_list ? pos_mine[j].x : tp.x, in_list ? pos_mine[j].y : tp.y,
-                                    in_list ? pos_mine[j].z : tp.z, in_list ? pos_mine[j].w : tp.w);
+        const bool in_list = at < 3 * cnt;
+        const float4 far = splat_xyz(tp, at % 3);
+        if (at < LENT8 * 3)
+            s_pos[at] = make_float4(in_list ? pos_mine[j].x : far.x, in_list ? pos_mine[j].y : far.y,
+                                    in_list ? pos_mine[j].z : far.z, in_list ? pos_mine[j].w : far.w);
     }
     if (tid < AXIS_NNZ) s_G[tid] = g_mine;
     if (tid < 16) s_orow[tid] = orow_mine;
@@ -219,11 +221,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int mt = 0; mt < 2; ++mt) {
             const int ei = 8 * cm + 4 * mt + g;
             const unsigned mine4 = (unsigned)(s_mask[ei] >> (4 * tn));   // this target's four slots of the entry
+            const SlotPos pc = slot_pos(s_pos, ei);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int u = 4 * mt + r;
-                const float4 pc = s_pos[ei * 4 + r];
-                const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x, pc.y, pc.z);
+                const float d2 = e2f::dist2_exact(tp.x, tp.y, tp.z, pc.x[r], pc.y[r], pc.z[r]);
                 // (bitwise on purpose; the target itself is at distance zero, an image of it at a box length)
                 const bool ok = (((mine4 >> r) & 1u) != 0u) & (d2 < P.rc2) & (d2 > 0.0f);
                 const float d = __builtin_amdgcn_sqrtf(d2);
@@ -267,16 +269,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
             f32x4 wx, wy, wz;
+            const SlotPos pc = slot_pos(s_pos, 8 * cm + 4 * mt + g);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int u = 4 * mt + r;
                 const float p = __builtin_amdgcn_exp2f(s2[u] - m_ref);
                 z += p;
                 const float pg = p * gate[u];
-                const float4 pc = s_pos[(8 * cm + 4 * mt + g) * 4 + r];
-                wx[r] = pg * (pc.x - tp.x);
-                wy[r] = pg * (pc.y - tp.y);
-                wz[r] = pg * (pc.z - tp.z);
+                wx[r] = pg * (pc.x[r] - tp.x);
+                wy[r] = pg * (pc.y[r] - tp.y);
+                wz[r] = pg * (pc.z[r] - tp.z);
             }
             s_W[((wave * 3 + 0) * 2 + mt) * 64 + lane] = wx;
             s_W[((wave * 3 + 1) * 2 + mt) * 64 + lane] = wy;

@@ -172,6 +172,25 @@ __device__ __forceinline__ bool tile_xcd_remap(int bid, int n_tiles, int blk, in
     return tile < n_tiles;
 }
 
+// x, y and z of the four slots of list entry e: three 16-byte LDS reads.
+struct SlotPos {
+    f32x4 x, y, z;
+};
+__device__ __forceinline__ SlotPos slot_pos(const float4* s_pos, int e) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(s_pos) + 3 * e;
+    return {p[0], p[1], p[2]};
+}
+// What a slot position array reads behind its list: coordinate c (0, 1, 2 = x, y, z) of the point p in all four slots.
+__device__ __forceinline__ float4 splat_xyz(const float4& p, int c) {
+    const float v = c == 0 ? p.x : c == 1 ? p.y : p.z;
+    return make_float4(v, v, v, v);
+}
+// OR over the four lanes of a quad.
+__device__ __forceinline__ unsigned quad_or(unsigned x) {
+    x |= (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true);   // lanes 1 0 3 2
+    return x | (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true);   // lanes 2 3 0 1
+}
+
 // Position of every entry of the non-zero pattern in a packed list of the 216 (order: mu, x_out, x_in); the epilogue
 // of the attention kernel reads the operators from that list (0.9 KB per workgroup instead of 7.5 KB).
 struct AxisIndex {

@@ -407,6 +407,18 @@ def test_tile_kernel_with_lists_longer_than_the_shared_list_area(torch_cuda):
     run_case(torch_cuda, wl, check_materialized=False)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [767, 769, 957, 960, 961])
+def test_tile_lists_at_the_capacity(torch_cuda, n, dtype):
+    """A ball of atoms that all see each other, in one cell: every tile's list has ceil(n / 4) entries, 192, 193 and 240
+    (the capacity) of them, the last two sizes with a group of one slot; 961 atoms leave no tile a list that fits."""
+    from paper_2601_16622_amd import workloads as W
+    rng = np.random.default_rng(n)
+    cfg = dict(L=1, C=32, H=2, B=8, lf=1, cutoff=6.0, dtype=dtype)
+    pos = rng.uniform(-1.7, 1.7, size=(n, 3)).astype(np.float32)   # diagonal 5.9
+    run_case(torch_cuda, W._pack(cfg, [pos], rng, elements=False), check_materialized=False)
+
+
 def test_result_is_deterministic_and_order_equivariant(torch_cuda):
     from paper_2601_16622_amd import binding as B, workloads as W
     wl = W.small_molecules(2, n_mol=6)
