@@ -36,47 +36,48 @@ __global__ void k_cells_bbox(const float* __restrict__ pos, const int32_t* __res
         atom_seg[a] = s;
         x = pos[3 * a]; y = pos[3 * a + 1]; z = pos[3 * a + 2];
     }
-    // One set of atomics per workgroup when all of it sits in one segment (the common case: few, large segments),
-    // else one per wave that does, else one per atom.
+    // One set of atomics per workgroup when all of it sits in one segment (the common case: few, large segments), else
+    // one per wave and segment.  Atoms come segment by segment, so a segment's atoms are neighbouring lanes and six steps
+    // reduce all of a wave's segments, each into its first lane.  (One set per atom of a mixed wave, 384 atomics on
+    // a handful of addresses, took 66 to 70 us for 64 molecules of 10 to 60 atoms and 25 us for 16 of 150 to 350.)
     __shared__ float s_box[16][6];
     __shared__ int s_seg[16];
-    const int s0 = __shfl(s, 0), wave = threadIdx.x >> 6, n_waves = (blockDim.x + 63) >> 6;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = (blockDim.x + 63) >> 6;
+    const int sl = live ? s : -1, s0 = __shfl(sl, 0);
     const bool uniform = __all(live && s == s0);
-    float mnx = x, mny = y, mnz = z, mxx = x, mxy = y, mxz = z;
-    if (uniform) {
-        for (int off = 32; off > 0; off >>= 1) {
-            mnx = fminf(mnx, __shfl_xor(mnx, off)); mny = fminf(mny, __shfl_xor(mny, off));
-            mnz = fminf(mnz, __shfl_xor(mnz, off)); mxx = fmaxf(mxx, __shfl_xor(mxx, off));
-            mxy = fmaxf(mxy, __shfl_xor(mxy, off)); mxz = fmaxf(mxz, __shfl_xor(mxz, off));
+    float v[6] = {x, y, z, x, y, z};   // min x, y, z; max x, y, z
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const bool same = __shfl_down(sl, off) == sl && lane + off < 64;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const float o = __shfl_down(v[k], off);
+            if (same) v[k] = k < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
         }
     }
-    if ((threadIdx.x & 63) == 0) {
+    const int before = __shfl_up(sl, 1);
+    const bool first = live && (lane == 0 || before != sl);   // first lane of its segment in this wave
+    if (lane == 0) {
         s_seg[wave] = uniform ? s0 : -1;
-        s_box[wave][0] = mnx; s_box[wave][1] = mny; s_box[wave][2] = mnz;
-        s_box[wave][3] = mxx; s_box[wave][4] = mxy; s_box[wave][5] = mxz;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_box[wave][k] = v[k];
     }
     __syncthreads();
     bool block_uniform = s_seg[0] >= 0;
     for (int w = 1; w < n_waves; ++w) block_uniform = block_uniform && s_seg[w] == s_seg[0];
+    auto publish = [&](int seg, int k, float val) {
+        if (k < 3) atomicMin(&bbox[seg * 6 + k], float_to_ordered(val));
+        else atomicMax(&bbox[seg * 6 + k], float_to_ordered(val));
+    };
     if (block_uniform) {
         if (threadIdx.x < 6) {
-            float v = s_box[0][threadIdx.x];
-            for (int w = 1; w < n_waves; ++w) v = threadIdx.x < 3 ? fminf(v, s_box[w][threadIdx.x]) : fmaxf(v, s_box[w][threadIdx.x]);
-            if (threadIdx.x < 3)
-                atomicMin(&bbox[s_seg[0] * 6 + threadIdx.x], float_to_ordered(v));
-            else
-                atomicMax(&bbox[s_seg[0] * 6 + threadIdx.x], float_to_ordered(v));
+            float val = s_box[0][threadIdx.x];
+            for (int w = 1; w < n_waves; ++w) val = threadIdx.x < 3 ? fminf(val, s_box[w][threadIdx.x]) : fmaxf(val, s_box[w][threadIdx.x]);
+            publish(s_seg[0], threadIdx.x, val);
         }
-    } else if (uniform) {
-        if ((threadIdx.x & 63) == 0) {
-            atomicMin(&bbox[s * 6 + 0], float_to_ordered(mnx)); atomicMin(&bbox[s * 6 + 1], float_to_ordered(mny));
-            atomicMin(&bbox[s * 6 + 2], float_to_ordered(mnz)); atomicMax(&bbox[s * 6 + 3], float_to_ordered(mxx));
-            atomicMax(&bbox[s * 6 + 4], float_to_ordered(mxy)); atomicMax(&bbox[s * 6 + 5], float_to_ordered(mxz));
-        }
-    } else if (live) {
-        atomicMin(&bbox[s * 6 + 0], float_to_ordered(x)); atomicMin(&bbox[s * 6 + 1], float_to_ordered(y));
-        atomicMin(&bbox[s * 6 + 2], float_to_ordered(z)); atomicMax(&bbox[s * 6 + 3], float_to_ordered(x));
-        atomicMax(&bbox[s * 6 + 4], float_to_ordered(y)); atomicMax(&bbox[s * 6 + 5], float_to_ordered(z));
+    } else if (first) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) publish(s, k, v[k]);
     }
 }
 
