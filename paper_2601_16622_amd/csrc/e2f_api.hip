@@ -249,6 +249,7 @@ e2f_status e2f_create(const e2f_config* cfg, e2f_ctx** ctx_out) {
                 c->coefP[comp][kk] = (float)((kk % 2) ? (m > 0 ? cg : (m < 0 ? -cg : 0.0)) : cg);
             }
         }
+    e2f_unit_axis_operators(c);
     // Attention kernel: the tile kernel where it applies, else the per-pair matrix-core kernel, else the ALU kernel,
     // unless the configuration names one.
     const int pick = cfg->attention;
@@ -621,7 +622,7 @@ static E2fBwdWs bwd_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, size_t at
     Bw.lse = (float*)take((size_t)N * ctx->cfg.H * 4);
     Bw.Dn = (float*)take((size_t)N * ctx->cfg.H * 4);
     Bw.G = (float*)take((size_t)3 * E2F_MAX_N * E2F_MAX_N * 4);
-    Bw.cw_unit = (float*)take((size_t)E2F_MAX_N * E2F_NP * 4);
+    take((size_t)E2F_MAX_N * E2F_NP * 4);   // (unused: the documented size stays)
     Bw.Gu = (float*)take((size_t)3 * E2F_MAX_N * E2F_MAX_N * 4);
     Bw.pWb = (float*)take((size_t)N * ctx->cfg.H * ctx->cfg.B * 4);
     Bw.pwp = (float*)take((size_t)N * 32 * 4);

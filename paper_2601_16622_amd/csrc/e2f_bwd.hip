@@ -615,10 +615,12 @@ e2f_status e2f_launch_backward(const e2f_ctx* ctx, const E2fCellsView& cv, const
     P.tau = ctx->tau; P.rc2 = ctx->rc2; P.cutoff = ctx->cfg.cutoff; P.rbf_step = ctx->rbf_step; P.rbf_gamma = ctx->rbf_gamma;
     P.Gu = nullptr; P.pWb = nullptr; P.pwp = nullptr;
     e2f_status rc;
-    if (wgrad) {   // unit-weight path coefficients and axis operators (full form for the per-atom kernels, packed for the tile kernels)
-        if ((rc = e2f_launch_unit_cw(ctx, bw.cw_unit, st)) != E2F_OK) return rc;
-        if ((rc = e2f_launch_axis_ops(ctx, bw.cw_unit, bw.Gu, st)) != E2F_OK) return rc;
-        if (tw && (rc = e2f_launch_axis_ops(ctx, bw.cw_unit, tw->Gu, st, true)) != E2F_OK) return rc;
+    // the axis operators that no earlier launch has left: those of the per-atom kernels without a tile form, and those
+    // with unit path weights (full form for the per-atom kernels, packed for the tile kernels)
+    if ((wgrad || !tw) && (rc = e2f_launch_axis_operators(ctx, w->w_path, tw ? nullptr : bw.G, wgrad ? bw.Gu : nullptr,
+                                                          wgrad && tw ? tw->Gu : nullptr, st)) != E2F_OK)
+        return rc;
+    if (wgrad) {
         P.Gu = bw.Gu; P.pWb = bw.pWb; P.pwp = bw.pwp;
     }
     if (tw) {
@@ -640,7 +642,6 @@ e2f_status e2f_launch_backward(const e2f_ctx* ctx, const E2fCellsView& cv, const
         if (wgrad && (rc = e2f_launch_backward_tile_wsum(ctx, cv, ws, *tw, bw.pWb, bw.pwp, grad_Wb, grad_w_path, st)) != E2F_OK)
             return rc;
     }
-    if (!tw && (rc = e2f_launch_axis_ops(ctx, ws.cw, bw.G, st)) != E2F_OK) return rc;
     if (!tw) switch (ctx->cfg.L_max) {
         case 1: launch_L<1>(ctx, P, st); break;
         case 2: launch_L<2>(ctx, P, st); break;

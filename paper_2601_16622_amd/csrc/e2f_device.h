@@ -157,7 +157,7 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
 }
 
 template <int l>
-__device__ __forceinline__ void delta_align(const float* c, const float* s, float* d) {
+__host__ __device__ __forceinline__ void delta_align(const float* c, const float* s, float* d) {
     if constexpr (l == 0) e2f_delta_align_l0(c, s, d);
     if constexpr (l == 1) e2f_delta_align_l1(c, s, d);
     if constexpr (l == 2) e2f_delta_align_l2(c, s, d);
@@ -171,7 +171,7 @@ __device__ __forceinline__ void delta_align(const float* c, const float* s, floa
 // D may point into LDS: every entry is written once, as soon as it is known, so that the blocks never
 // have to be held in registers together.
 template <int l>
-__device__ __forceinline__ void align_block(const float* ck, const float* sk, const float* cm, const float* sm, float* D) {
+__host__ __device__ __forceinline__ void align_block(const float* ck, const float* sk, const float* cm, const float* sm, float* D) {
     constexpr int n = 2 * l + 1;
     float dl[n * n];
     delta_align<l>(ck, sk, dl);
@@ -196,8 +196,8 @@ __device__ __forceinline__ void align_block(const float* ck, const float* sk, co
 }
 
 template <int L, int l = 0>
-__device__ __forceinline__ void align_all_blocks(const float* ck, const float* sk, const float* cm, const float* sm,
-                                                 float* D) {
+__host__ __device__ __forceinline__ void align_all_blocks(const float* ck, const float* sk, const float* cm, const float* sm,
+                                                          float* D) {
     align_block<l>(ck, sk, cm, sm, D + d_offset(l));
     if constexpr (l < L) align_all_blocks<L, l + 1>(ck, sk, cm, sm, D);
 }
@@ -277,6 +277,22 @@ __host__ __device__ __forceinline__ int v4_role(int n, int x) {
     const int odd = nxw & 1, local = x - x0;
     if (odd && local == 0) return 0;
     return 1 + ((local - odd) & 1);
+}
+
+// Value rows of the non-linear logit's matrix-core kernel: per (slot, head) n * 16 bf16 in blocks of eight components,
+// [16 channels][8], then the n % 8 components left over as [16 channels][n % 8].  Element i of a slot's row holds
+// component x of channel ch of a head.
+__host__ __device__ __forceinline__ void nl_element(int n, int i, int& head, int& x, int& ch) {
+    head = i / (n * 16);
+    const int in = i - head * (n * 16), o = in >> 7, full = n >> 3;
+    if (o < full) {
+        x = o * 8 + (in & 7);
+        ch = (in & 127) >> 3;
+    } else {
+        const int rem = n & 7, tail = in - full * 128;
+        x = full * 8 + tail % rem;
+        ch = tail / rem;
+    }
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

@@ -67,6 +67,7 @@ struct e2f_ctx {
     // coupling coefficients of the re-indexing operator P for lf (without path weights): coefP[comp][k] multiplies
     // the aligned input of degree l_in = l_out - lf + k; even k keeps the order m, odd k takes it from -m.
     float coefP[E2F_MAX_N][E2F_NP];
+    float axis_unit[216];   // lf = 1: the axis operators with unit path weights, their non-zero entries in packed order
     // optional per-stage timing (e2f_profile_begin / e2f_profile_end)
     hipEvent_t* prof_events;  // [prof_capacity][E2F_N_STAGES + 1]
     int32_t prof_capacity, prof_calls;
@@ -116,7 +117,6 @@ struct E2fBwdWs {
     float* Dn;   // [N][H] <dL/d out_i, out_i> per head
     float* G;    // [3][25][25] axis operators of the degree-1 filter
     // for the gradients of Wb and w_path: unit-weight path coefficients and axis operators, per-atom partial sums
-    float* cw_unit;  // [n][E2F_NP]
     float* Gu;       // [3][25][25]
     float* pWb;      // [N][H][B]
     float* pwp;      // [N][32]
@@ -190,6 +190,7 @@ bool e2f_tile_f32_supported(const e2f_ctx* ctx);
 e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out, hipStream_t st);
 // The fused call with the non-linear pair feature in the logit; q1 = W_Q1 h in v's plain layout and type.
 bool e2f_nonlinear_supported(const e2f_ctx* ctx);
+void e2f_unit_axis_operators(e2f_ctx* ctx);
 e2f_status e2f_launch_fused_nonlinear(const e2f_ctx* ctx, const E2fCellsView& cv, const e2f_weights* w,
                                       const E2fAttnWs& ws, const void* q1, float* out, hipStream_t st);
 e2f_status e2f_launch_tensor_product(const e2f_ctx* ctx, const void* h, const float* r, const float* w_path, float* out,
@@ -208,9 +209,9 @@ bool e2f_tile_supported(const e2f_ctx* ctx);
 static inline bool e2f_tile_layouts_direct(const e2f_ctx* ctx) {
     return ctx->cfg.C == 32 || ctx->cfg.C == 64 || ctx->cfg.C == 128 || ctx->cfg.C == 256;
 }
-// G[mu][x_out][x_in], mu = x, y, z: the degree-1 filter's message for a unit pair vector along mu, from the path
-// coefficients cw (tile attention kernel, backward pass).
-e2f_status e2f_launch_axis_ops(const e2f_ctx* ctx, const float* cw, float* G, hipStream_t st, bool packed = false);
+// G[mu][x_out][x_in], mu = x, y, z: the degree-1 filter's message for a unit pair vector along mu, of the path weights (G)
+// and of unit weights (Gu, and Gu_packed with the packed list behind it); any of the three may be null.
+e2f_status e2f_launch_axis_operators(const e2f_ctx* ctx, const float* w_path, float* G, float* Gu, float* Gu_packed, hipStream_t st);
 // Tile form of the backward pass's pair work (e2f_bwd_tile.hip): needs the tile layouts of q, k, v and the candidate
 // lists in `ws`; tiles whose list did not fit are left to the per-atom kernels.
 E2fBwdTileWs e2f_bwd_tile_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, size_t offset);
@@ -237,7 +238,6 @@ e2f_status e2f_launch_backward_maps(const e2f_ctx* ctx, int N, const e2f_weights
                                     const float* grad_k, const float* grad_v, float* grad_h, float* grad_W,
                                     const E2fBwdWs& bw, hipStream_t st);
 // cw[comp][t] = P coefficient with every path weight one.
-e2f_status e2f_launch_unit_cw(const e2f_ctx* ctx, float* cw, hipStream_t st);
 // table: the caller's padded neighbour table [N][table_K], or null (every atom within the cutoff is a neighbour)
 e2f_status e2f_launch_tile(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, const int32_t* table,
                            int table_K, float* out, hipStream_t st);

@@ -10,7 +10,7 @@
 
 #include <type_traits>
 
-#include "e2f_device.h"
+#include "e2f_tile_shared.h"
 
 namespace {
 
@@ -30,8 +30,11 @@ struct CoefTable {
 // spos[slot] = position of the atom in that slot (w carries its index in the caller's order); cw[comp][t] = P coefficient times its path weight.
 __global__ void k_prepare(E2fCellsView cv, const float* __restrict__ pos, const float* __restrict__ w_path, int L,
                           int lf, CoefTable tab, float4* __restrict__ spos, float* __restrict__ cw,
-                          const float* __restrict__ Wb, int H, int B, float* __restrict__ wbT) {
+                          const float* __restrict__ Wb, int H, int B, float* __restrict__ wbT, AxisTable axis, float* __restrict__ G) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    // the axis operators of the tile kernels (one workgroup of the list kernel once formed them by the rotations, 17 us
+    // at L = 4, longer than the lists of a small system)
+    if (G && t < AXIS_PACKED_AT + AXIS_NNZ) G[t] = axis_full_entry(axis, w_path, L, t);
     if (t < H * B) wbT[(t % B) * H + t / B] = Wb[t];
     if (t < cv.N) {
         const int a = cv.perm[t];
@@ -54,18 +57,6 @@ __global__ void k_prepare(E2fCellsView cv, const float* __restrict__ pos, const 
         if (kk <= 2 * lf && li >= 0 && li <= L) w = w_path[li * (L + 1) + lo];
         cw[t] = w * tab.c[comp][kk];
     }
-}
-
-// cw[comp][t] = P coefficient of the path into comp with every path weight one (w_path gradients).
-__global__ void k_unit_cw(int L, int lf, CoefTable tab, float* __restrict__ cw) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = (L + 1) * (L + 1);
-    if (t >= n * E2F_NP) return;
-    const int comp = t / E2F_NP, kk = t % E2F_NP;
-    int lo = 0;
-    while ((lo + 1) * (lo + 1) <= comp) ++lo;
-    const int li = lo - lf + kk;
-    cw[t] = (kk <= 2 * lf && li >= 0 && li <= L) ? tab.c[comp][kk] : 0.0f;
 }
 
 template <typename T>
@@ -131,7 +122,8 @@ __global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* _
                                                      float* __restrict__ k, T* __restrict__ v) {
     typedef Frag<T> F;
     constexpr int NS = C / F::KSTEP;
-    const int tile = blockIdx.x, l = blockIdx.y, cg = blockIdx.z;
+    // (the degrees with the most orders start first, so that the launch does not end on its longest waves)
+    const int tile = blockIdx.x, cg = blockIdx.y, l = L - (int)blockIdx.z;
     const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
     const int N = cv.N, n = (L + 1) * (L + 1), nl = 2 * l + 1;
     const int slot_i = min(tile * 16 + i, N - 1);            // clamped rows are computed and not stored
@@ -933,7 +925,7 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
         const int waves_ct = (cv.N + 15) / 16 * (ctx->cfg.L_max + 1) * (C / 16 / CT);
         auto go = [&](auto ct_tag) {
             constexpr int ct = decltype(ct_tag)::value;
-            const dim3 grid((cv.N + 15) / 16, ctx->cfg.L_max + 1, C / 16 / ct);
+            const dim3 grid((cv.N + 15) / 16, C / 16 / ct, ctx->cfg.L_max + 1);
             if (tiled)
                 k_project_mfma<T, C, MG, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
@@ -1113,17 +1105,9 @@ e2f_status e2f_launch_prepare(const e2f_ctx* ctx, const E2fCellsView& cv, const 
         for (int t = 0; t < E2F_NP; ++t) tab.c[x][t] = ctx->coefP[x][t];
     int work = cv.N > ctx->n * E2F_NP ? cv.N : ctx->n * E2F_NP;
     if (ctx->cfg.H * ctx->cfg.B > work) work = ctx->cfg.H * ctx->cfg.B;
+    if (ws.G && AXIS_PACKED_AT + AXIS_NNZ > work) work = AXIS_PACKED_AT + AXIS_NNZ;
     k_prepare<<<(work + 255) / 256, 256, 0, st>>>(cv, pos, w->w_path, ctx->cfg.L_max, ctx->cfg.lf, tab, ws.spos, ws.cw,
-                                                 w->Wb, ctx->cfg.H, ctx->cfg.B, ws.wbT);
-    E2F_HIP_CHECK(hipGetLastError());
-    return E2F_OK;
-}
-
-e2f_status e2f_launch_unit_cw(const e2f_ctx* ctx, float* cw, hipStream_t st) {
-    CoefTable tab;
-    for (int x = 0; x < E2F_MAX_N; ++x)
-        for (int t = 0; t < E2F_NP; ++t) tab.c[x][t] = ctx->coefP[x][t];
-    k_unit_cw<<<1, 256, 0, st>>>(ctx->cfg.L_max, ctx->cfg.lf, tab, cw);
+                                                 w->Wb, ctx->cfg.H, ctx->cfg.B, ws.wbT, axis_table(ctx), ws.G);
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;
 }

@@ -43,37 +43,20 @@ struct TileParams {
     int table_K;
     int hpw;           // heads per workgroup of k_tile_heads
     int lists_only;    // the list kernel leaves crowded tiles to the caller instead of running their heads itself
-    const float* cw;   // the list kernel's first workgroup forms the axis operators instead: G_out from cw
-    float* G_out;
     int C, H, B, n_tiles, blk;   // blk: tiles per XCD chunk (tile_blk)
     float rc2, cutoff, rbf_step, rbf_gamma;
 };
 
-// The three axis operators, column by column: G[mu][x_out][x_in] = (e_{x_in} (x) R^(1)(e_mu))[x_out]; with `packed`
-// also as the list of their pattern's entries, behind the full form.
-template <int L>
-__device__ __forceinline__ void axis_ops(const float* __restrict__ cw, float* __restrict__ G, int tid, bool packed) {
-    constexpr int n = (L + 1) * (L + 1), DS = e2f::d_offset(L + 1);
-    if (tid >= 3 * n) return;
-    const int mu = tid / n, xi = tid % n;
-    float D[DS];
-    e2f::align_D<L>(mu == 0 ? 1.0f : 0.0f, mu == 1 ? 1.0f : 0.0f, mu == 2 ? 1.0f : 0.0f, 1.0f, D);
-    float v[n][1], acc[n][1];
-#pragma unroll
-    for (int x = 0; x < n; ++x) {
-        v[x][0] = x == xi ? 1.0f : 0.0f;
-        acc[x][0] = 0.0f;
-    }
-    e2f::eaas_accumulate<L, 1, 1>(v, D, cw, 1.0f, acc);
-#pragma unroll
-    for (int xo = 0; xo < n; ++xo) {
-        G[(mu * E2F_MAX_N + xo) * E2F_MAX_N + xi] = acc[xo][0];
-        if (packed && ((E2F_AXIS_NZ[mu][xo] >> xi) & 1u)) G[AXIS_PACKED_AT + AXIS_INDEX.v[mu][xo][xi]] = acc[xo][0];
-    }
-}
-template <int L>
-__global__ void k_axis_ops(const float* __restrict__ cw, float* __restrict__ G, bool packed) {
-    axis_ops<L>(cw, G, threadIdx.x, packed);
+// Axis operators: those of the path weights into G (full form), those of unit weights into Gu (full form) and Gu_packed
+// (full form and packed list); any may be null.
+__global__ __launch_bounds__(256) void k_axis_operators(AxisTable tab, const float* __restrict__ w_path, int L, float* __restrict__ G,
+                                                        float* __restrict__ Gu, float* __restrict__ Gu_packed) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= AXIS_PACKED_AT + AXIS_NNZ) return;
+    const float u = axis_full_entry(tab, nullptr, L, t);
+    if (G && t < AXIS_PACKED_AT) G[t] = axis_full_entry(tab, w_path, L, t);
+    if (Gu && t < AXIS_PACKED_AT) Gu[t] = u;
+    if (Gu_packed) Gu_packed[t] = u;
 }
 
 // One workgroup of NW waves per (tile of 16 targets, head).  The waves share the candidate list and the softmax
@@ -610,18 +593,9 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
         }
         if (overflow && !P.lists_only) {
             // (uniform) A crowded tile: its list does not fit the shared area, k_tile_heads will skip it.  This
-            // workgroup runs the tile's heads itself, one after the other, building the lists per head.  The axis
-            // operators of this launch may not be there yet (another workgroup forms them), so it forms its own
-            // copy in the tile's list area, which stays unused.
-            float* own_G = reinterpret_cast<float*>(P.lists_pos + (size_t)tile * LCAP * 3);
-            static_assert((size_t)LCAP * 3 * sizeof(float4) >= (AXIS_PACKED_AT + AXIS_NNZ) * sizeof(float), "room for the operators");
-            axis_ops<L>(P.cw, own_G, threadIdx.x, true);
-            __threadfence_block();
-            __syncthreads();
-            TileParams Q = P;
-            Q.G = own_G;
+            // workgroup runs the tile's heads itself, one after the other, building the lists per head.
             for (int h = 0; h < P.H; ++h) {
-                tile_item<L, NW, PBC, 0, CAP, NB>(Q, tile, h);
+                tile_item<L, NW, PBC, 0, CAP, NB>(P, tile, h);
                 __syncthreads();   // the next head reuses the shared arrays
             }
         }
@@ -1054,11 +1028,7 @@ template <int L, int NW, bool PBC, int MODE, bool CAP, int NB>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(E2F_TILE_OCC(NW), E2F_TILE_OCC(NW)))) void k_tile(TileParams P) {
     int tile, head;
     if constexpr (MODE == 1) {
-        if (blockIdx.x == 0) {   // (whole workgroup) the first workgroup forms the axis operators instead
-            axis_ops<L>(P.cw, P.G_out, threadIdx.x, true);
-            return;
-        }
-        tile = blockIdx.x - 1;
+        tile = blockIdx.x;
         head = 0;
     } else {
         if (!tile_xcd_remap(blockIdx.x, P.n_tiles, P.blk, P.H, tile, head)) return;   // whole workgroup
@@ -1066,10 +1036,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(E2F_TIL
     tile_item<L, NW, PBC, MODE, CAP, NB>(P, tile, head);
 }
 
-// what: 1 the list kernel (with the axis operators), 2 the attention kernel reading the lists, 0 the attention kernel
-// building its lists itself (after the axis-operator kernel)
+// what: 1 the list kernel, 2 the attention kernel reading the lists, 0 the attention kernel building its lists itself
 template <int L>
-void launch_L(const TileParams& P, const float* cw, float* G, int what, hipStream_t st) {
+void launch_L(const TileParams& P, int what, hipStream_t st) {
     const int grid = tile_grid(P.n_tiles, P.blk, P.H);
     // four waves per workgroup, two workgroups per CU: with eight waves the 128 registers left per wave do not
     // hold a wave's accumulators, value rows and key rows without spilling into the streaming loop
@@ -1078,20 +1047,16 @@ void launch_L(const TileParams& P, const float* cw, float* G, int what, hipStrea
     auto go = [&](auto pbc, auto capped) {
         constexpr bool PBC = decltype(pbc)::value, CAP = decltype(capped)::value;
         if (P.B > 8) {
-            if (what == 1) k_tile<L, 4, PBC, 1, CAP, 16><<<P.n_tiles + 1, 256, 0, st>>>(P);
+            if (what == 1) k_tile<L, 4, PBC, 1, CAP, 16><<<P.n_tiles, 256, 0, st>>>(P);
             else if (what == 2) k_tile_heads<L, 16><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
-            else {
-                k_axis_ops<L><<<1, 128, 0, st>>>(cw, G, true);
-                k_tile<L, 4, PBC, 0, CAP, 16><<<grid, 256, 0, st>>>(P);
-            }
+            else k_tile<L, 4, PBC, 0, CAP, 16><<<grid, 256, 0, st>>>(P);
             return;
         }
         if (what == 1) {
-            k_tile<L, 4, PBC, 1, CAP, 8><<<P.n_tiles + 1, 256, 0, st>>>(P);
+            k_tile<L, 4, PBC, 1, CAP, 8><<<P.n_tiles, 256, 0, st>>>(P);
         } else if (what == 2) {
             k_tile_heads<L, 8><<<tile_grid(P.n_tiles, P.blk, P.H / P.hpw), 256, 0, st>>>(P);
         } else {
-            k_axis_ops<L><<<1, 128, 0, st>>>(cw, G, true);
             k_tile<L, 4, PBC, 0, CAP, 8><<<grid, 256, 0, st>>>(P);
         }
     };
@@ -1101,15 +1066,33 @@ void launch_L(const TileParams& P, const float* cw, float* G, int what, hipStrea
 
 }  // namespace
 
-// packed: also the list of the pattern's entries behind the full form (G then holds 3 * 25 * 25 + 216 floats)
-e2f_status e2f_launch_axis_ops(const e2f_ctx* ctx, const float* cw, float* G, hipStream_t st, bool packed) {
-    switch (ctx->cfg.L_max) {
-        case 1: k_axis_ops<1><<<1, 128, 0, st>>>(cw, G, packed); break;
-        case 2: k_axis_ops<2><<<1, 128, 0, st>>>(cw, G, packed); break;
-        case 3: k_axis_ops<3><<<1, 128, 0, st>>>(cw, G, packed); break;
-        case 4: k_axis_ops<4><<<1, 128, 0, st>>>(cw, G, packed); break;
-        default: return E2F_ERR_UNSUPPORTED;
+// The axis operators with unit path weights, G_mu = D(R_mu)^T P D(R_mu), the entries of their pattern in packed order.
+void e2f_unit_axis_operators(e2f_ctx* ctx) {
+    static_assert(sizeof(ctx->axis_unit) == AXIS_NNZ * sizeof(float), "one entry each");
+    const int L = ctx->cfg.L_max;
+    for (int mu = 0; mu < 3; ++mu) {
+        // angles of the axis: theta = 90, 90, 0 degrees, phi = 0, 90, 0; cosines and sines of their multiples
+        static const float cos4[5] = {1, 0, -1, 0, 1}, sin4[5] = {0, 1, 0, -1, 0}, one[5] = {1, 1, 1, 1, 1}, zero[5] = {0, 0, 0, 0, 0};
+        float D[e2f::d_offset(E2F_MAX_L + 1)];
+        e2f::align_all_blocks<E2F_MAX_L>(mu < 2 ? cos4 : one, mu < 2 ? sin4 : zero, mu == 1 ? cos4 : one, mu == 1 ? sin4 : zero, D);
+        for (int xo = 0; xo < E2F_MAX_N; ++xo)
+            for (int xi = 0; xi < E2F_MAX_N; ++xi) {
+                if (!((E2F_AXIS_NZ[mu][xo] >> xi) & 1u)) continue;
+                const int lo = AxisPaths::degree(xo), li = AxisPaths::degree(xi), k = li - lo + 1;
+                float sum = 0.0f;
+                for (int m = -lo; m <= lo && lo <= L && li <= L; ++m) {
+                    if (abs(m) > li || ((k & 1) && m == 0)) continue;
+                    const int ms = (k & 1) ? -m : m;
+                    sum += D[e2f::d_offset(lo) + (lo + m) * (2 * lo + 1) + xo - lo * lo] * ctx->coefP[lo * lo + lo + m][k] *
+                           D[e2f::d_offset(li) + (li + ms) * (2 * li + 1) + xi - li * li];
+                }
+                ctx->axis_unit[AXIS_INDEX.v[mu][xo][xi]] = sum;
+            }
     }
+}
+
+e2f_status e2f_launch_axis_operators(const e2f_ctx* ctx, const float* w_path, float* G, float* Gu, float* Gu_packed, hipStream_t st) {
+    k_axis_operators<<<(AXIS_PACKED_AT + AXIS_NNZ + 255) / 256, 256, 0, st>>>(axis_table(ctx), w_path, ctx->cfg.L_max, G, Gu, Gu_packed);
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;
 }
@@ -1135,8 +1118,6 @@ static e2f_status launch_tile(const e2f_ctx* ctx, const E2fCellsView& cv, const 
     P.lists_mask = ws.lists_mask;
     P.table = table;
     P.table_K = table_K;
-    P.cw = ws.cw;
-    P.G_out = ws.G;
     P.lists_only = lists_only ? 1 : 0;
     P.C = ctx->cfg.C; P.H = ctx->cfg.H; P.B = ctx->cfg.B; P.n_tiles = (cv.N + 15) / 16; P.blk = tile_blk(P.n_tiles);
     // heads per workgroup of the attention kernel: up to four, as long as about eight rounds of workgroups are left
@@ -1146,10 +1127,10 @@ static e2f_status launch_tile(const e2f_ctx* ctx, const E2fCellsView& cv, const 
     while (P.hpw < 4 && P.H % (P.hpw * 2) == 0 && (long)P.n_tiles * P.H / (P.hpw * 2) >= 4096) P.hpw *= 2;
     P.rc2 = ctx->rc2; P.cutoff = ctx->cfg.cutoff; P.rbf_step = ctx->rbf_step; P.rbf_gamma = ctx->rbf_gamma;
     switch (ctx->cfg.L_max) {
-        case 1: launch_L<1>(P, ws.cw, ws.G, what, st); break;
-        case 2: launch_L<2>(P, ws.cw, ws.G, what, st); break;
-        case 3: launch_L<3>(P, ws.cw, ws.G, what, st); break;
-        case 4: launch_L<4>(P, ws.cw, ws.G, what, st); break;
+        case 1: launch_L<1>(P, what, st); break;
+        case 2: launch_L<2>(P, what, st); break;
+        case 3: launch_L<3>(P, what, st); break;
+        case 4: launch_L<4>(P, what, st); break;
         default: return E2F_ERR_UNSUPPORTED;
     }
     E2F_HIP_CHECK(hipGetLastError());

@@ -207,4 +207,41 @@ constexpr int AXIS_NNZ = AXIS_INDEX.count;
 static_assert(AXIS_NNZ == 216, "the pattern of the degree-1 axis operators at L_max = 4");
 constexpr int AXIS_PACKED_AT = 3 * E2F_MAX_N * E2F_MAX_N;   // the packed list follows the full operators
 
+// The axis operators with unit path weights, packed (e2f_ctx::axis_unit): an argument of the kernels that need them.  An
+// entry belongs to one path, so the operators of a call are these numbers times its path weights.
+struct AxisTable {
+    float v[AXIS_NNZ];
+};
+inline AxisTable axis_table(const e2f_ctx* ctx) {
+    AxisTable t;
+    for (int i = 0; i < AXIS_NNZ; ++i) t.v[i] = ctx->axis_unit[i];
+    return t;
+}
+struct AxisPaths {
+    uint8_t v[AXIS_NNZ];               // l_in * 8 + l_out of every packed entry
+    int16_t packed[AXIS_PACKED_AT];    // position in the packed list of every entry of the full form, or -1
+    constexpr AxisPaths() : v(), packed() {
+        for (int mu = 0; mu < 3; ++mu)
+            for (int xo = 0; xo < E2F_MAX_N; ++xo)
+                for (int xi = 0; xi < E2F_MAX_N; ++xi) {
+                    const int at = AXIS_INDEX.v[mu][xo][xi];
+                    packed[(mu * E2F_MAX_N + xo) * E2F_MAX_N + xi] = (int16_t)at;
+                    if (at >= 0) v[at] = (uint8_t)(degree(xi) * 8 + degree(xo));
+                }
+    }
+    static constexpr int degree(int x) { return x >= 16 ? 4 : x >= 9 ? 3 : x >= 4 ? 2 : x >= 1 ? 1 : 0; }
+};
+__device__ constexpr AxisPaths AXIS_PATHS{};
+// Packed entry i of a call's operators (w_path null: unit weights); entries of degrees beyond L are zero.
+__device__ __forceinline__ float axis_entry(const AxisTable& tab, const float* __restrict__ w_path, int L, int i) {
+    const int li = AXIS_PATHS.v[i] >> 3, lo = AXIS_PATHS.v[i] & 7;
+    if (li > L || lo > L) return 0.0f;
+    return w_path ? tab.v[i] * w_path[li * (L + 1) + lo] : tab.v[i];
+}
+// Entry t of G: the full form [mu][x_out][x_in], then, behind it, the packed list.
+__device__ __forceinline__ float axis_full_entry(const AxisTable& tab, const float* __restrict__ w_path, int L, int t) {
+    const int at = t < AXIS_PACKED_AT ? AXIS_PATHS.packed[t] : t - AXIS_PACKED_AT;
+    return at >= 0 ? axis_entry(tab, w_path, L, at) : 0.0f;
+}
+
 }  // namespace

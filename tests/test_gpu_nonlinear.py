@@ -116,3 +116,27 @@ def test_limits_and_empty_input(torch_cuda):
         assert e.value.code == 3
     finally:
         P.close()
+
+
+@pytest.mark.parametrize("L,C,H,B", [
+    (1, 16, 1, 1),       # one head for a workgroup of four waves; one radial function
+    (2, 48, 3, 5),       # an idle wave; value rows with a single component left over (9 = 8 + 1)
+    (3, 64, 4, 16),      # value rows of whole blocks (16 components), 16 radial functions
+    (4, 192, 12, 8),     # three groups of heads; the projection without a weight-stationary kernel
+    (4, 128, 8, 8),
+])
+def test_matrix_core_kernel_at_its_edges(torch_cuda, L, C, H, B):
+    """bf16 features in heads of 16 channels, degree-1 filter: clusters that fit a ball of the cutoff, so that an atom of
+    a cluster of s has s - 1 neighbours: around a group of 16 pairs, a batch of 64, and a list (up to 512 entries,
+    256 candidates per step) that is consumed in two goes."""
+    from paper_2601_16622_amd import workloads as W
+    rng = np.random.default_rng(17 * L + C)
+    sizes = [1, 2, 16, 17, 18, 64, 65, 66, 129] + ([540] if L == 2 else [])
+    cfg = dict(L=L, C=C, H=H, B=B, lf=1, cutoff=3.0, dtype="bf16")
+    parts = []
+    for s in sizes:
+        d = rng.normal(size=(s, 3))
+        parts.append((d / np.linalg.norm(d, axis=1, keepdims=True) * 1.45 * rng.random((s, 1)) ** (1.0 / 3.0)
+                      + rng.uniform(-9, 9, 3)).astype(np.float32))
+    wl = W._pack(cfg, parts, rng, elements=False)
+    run_nonlinear(torch_cuda, wl)
