@@ -102,48 +102,42 @@ __device__ __forceinline__ float load_Dn(const BwdParams& P, int t, int head) {
 
 // Sum over the Ch threads of a head (Ch a power of two <= 64, heads aligned inside a wave).
 __device__ __forceinline__ float head_sum(float x, int Ch) {
-    for (int off = 1; off < Ch; off <<= 1) x += __shfl_xor(x, off);
-    return x;
+    float one[1] = {x};
+    e2f::group_sums(one, Ch);
+    return one[0];
 }
+// Whether the rows of a batch's next pair are requested before the current pair is worked on (both sets in registers).
+// One pair after the other, each waiting for its rows and for four sums over the head's lanes through the LDS unit, and the
+// stencil's runs in scratch memory, took 218 and 205 us for the two sides of 2 240 atoms, L = 2, 128 fp32 channels (936
+// us the training step); with the sums in the additions, the rows ahead and the runs in LDS the step takes 263 us less.
+// At L = 3 and 4 the second set does not fit the registers.
+template <int L>
+constexpr bool ROWS_AHEAD = L <= 2;
 
 // The neighbours of slot t in batches: wave 0 walks the 18 stencil runs and packs (slot, image position) of the
 // atoms inside the cutoff into LDS; every thread of the workgroup then reads the batch.
-struct ListWalk {
-    e2f::Stencil<true> st;
-    int row, base;
-    bool done;
-    __device__ void init(const E2fCellsView& cv, int t) {
-        st.init(cv, t);
-        row = 0;
-        base = st.lo[0];
-        done = false;
-    }
-};
-
 // The workgroup then evaluates what depends on the distance alone, once per pair instead of once per channel:
 // s_rad[e] = (phi, dphi/dd, d, -) and s_bias[e * H + h] = (b_h(d), db_h/dd).
-__device__ __forceinline__ int next_batch(const BwdParams& P, ListWalk& w, int t, const float4& pi, int* s_list,
+__device__ __forceinline__ int next_batch(const BwdParams& P, const e2f::RunList& runs, int& base, int t, const float4& pi, int* s_list,
                                           float4* s_pos, float4* s_rad, float2* s_bias, int* s_ctl) {
     __syncthreads();   // the previous batch has been consumed
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int cnt = 0;
-        while (!w.done && cnt + 64 <= BCAP) {
-            if (w.base >= w.st.hi[w.row]) {
-                ++w.row;
-                if (w.row == 18) { w.done = true; break; }
-                w.base = w.st.lo[w.row];
-                continue;
-            }
-            const int j = w.base + lane;
+        const int total = runs.total();
+        while (base < total && cnt + 64 <= BCAP) {
             bool ok = false;
+            int j = 0;
             float4 pj = pi;
-            if (j < w.st.hi[w.row] && j != t) {
+            if (base + lane < total) {
+                int run;
+                runs.candidate(base + lane, run, j);
+                const float4 sh = runs.sh[run];
                 pj = P.spos[j];
-                pj.x += w.st.shift_x(w.row);
-                pj.y += w.st.shift_y(w.row);
-                pj.z += w.st.shift_z(w.row);
-                ok = e2f::is_neighbor(e2f::dist2_exact(pi.x, pi.y, pi.z, pj.x, pj.y, pj.z), P.rc2);
+                pj.x += sh.x;
+                pj.y += sh.y;
+                pj.z += sh.z;
+                ok = j != t && e2f::is_neighbor(e2f::dist2_exact(pi.x, pi.y, pi.z, pj.x, pj.y, pj.z), P.rc2);
             }
             const unsigned long long mask = __ballot(ok);
             const int at = cnt + __popcll(mask & ((1ull << lane) - 1ull));
@@ -152,11 +146,11 @@ __device__ __forceinline__ int next_batch(const BwdParams& P, ListWalk& w, int t
                 s_pos[at] = pj;
             }
             cnt += __popcll(mask);
-            w.base += 64;
+            base += 64;
         }
         if (lane == 0) {
             s_ctl[0] = cnt;
-            s_ctl[1] = w.done ? 1 : 0;
+            s_ctl[1] = base >= total ? 1 : 0;
         }
     }
     __syncthreads();
@@ -227,16 +221,27 @@ __global__ __launch_bounds__(256) void k_bwd_stats(BwdParams P) {
     for (int x = 0; x < n; ++x) dsum += P.gout[((size_t)a * n + x) * C + c] * P.out[((size_t)a * n + x) * C + c];
     dsum = head_sum(dsum, P.Ch);
     float m = -INFINITY, z = 0.0f;
-    ListWalk w;
-    w.init(P.cv, t);
+    __shared__ e2f::RunList s_run;
+    if (threadIdx.x < 64) e2f::fill_runs(s_run, P.cv, t, threadIdx.x);
+    int walked = 0;   // (next_batch opens with the barrier that the runs need)
     while (true) {
-        const int cnt = next_batch(P, w, t, pi, s_list, s_pos, s_rad, s_bias, s_ctl);
-        for (int e = 0; e < cnt; ++e) {
-            const int j = s_list[e];
-            float dot = 0.0f;
+        const int cnt = next_batch(P, s_run, walked, t, pi, s_list, s_pos, s_rad, s_bias, s_ctl);
+        constexpr int PG = 4;   // pairs whose rows are requested and summed together; the last ones repeat, not counted
+        for (int e0 = 0; e0 < cnt; e0 += PG) {
+          float dots[PG];
 #pragma unroll
-            for (int l = 0; l <= L; ++l) dot += qv[l] * load_k<L, TL>(P, j, l, c);
-            dot = head_sum(dot, P.Ch);
+          for (int u = 0; u < PG; ++u) {
+            const int j = s_list[min(e0 + u, cnt - 1)];
+            dots[u] = 0.0f;
+#pragma unroll
+            for (int l = 0; l <= L; ++l) dots[u] += qv[l] * load_k<L, TL>(P, j, l, c);
+          }
+          e2f::group_sums(dots, P.Ch);
+#pragma unroll
+          for (int u = 0; u < PG; ++u) {
+            const int e = e0 + u;
+            if (e >= cnt) break;
+            const float dot = dots[u];
             if constexpr (TL) {   // base-2 units, as the tile kernels keep them
                 const float s = dot + s_bias[e * P.H + head].x * LOG2E;
                 const float mn = fmaxf(m, s);
@@ -248,6 +253,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(BwdParams P) {
                 z = z * __expf(m - mn) + __expf(s - mn);
                 m = mn;
             }
+          }
         }
         if (s_ctl[1]) break;
     }
@@ -293,8 +299,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     for (int x = 0; x < n; ++x) g[x] = P.gout[((size_t)a * n + x) * C + c];
     const float lse = load_lse<TL>(P, t, head), Dn = load_Dn<TL>(P, t, head);
     float gx = 0.0f, gy = 0.0f, gz = 0.0f;   // sum_j dL/dr_ij of this head
-    ListWalk w;
-    w.init(P.cv, t);
+    __shared__ e2f::RunList s_run;
+    if (threadIdx.x < 64) e2f::fill_runs(s_run, P.cv, t, threadIdx.x);
+    int walked = 0;   // (next_batch opens with the barrier that the runs need)
     __syncthreads();
     float gt[3][n];   // G_mu^T g_i: u_mu = <g_i, G_mu v_j> = <gt_mu, v_j>
     axis_apply<L, true>(g, s_G, gt);
@@ -304,33 +311,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         for (int i = 0; i < WB_PER_THREAD; ++i) accWb[i] = 0.0f;
     }
     while (true) {
-        const int cnt = next_batch(P, w, t, pi, s_list, s_pos, s_rad, s_bias, s_ctl);
-        for (int e = 0; e < cnt; ++e) {
+        const int cnt = next_batch(P, s_run, walked, t, pi, s_list, s_pos, s_rad, s_bias, s_ctl);
+        constexpr bool AHEAD = ROWS_AHEAD<L>;
+        float kn[L + 1], vn[n];   // the rows of the pair to come
+        auto request = [&](int e) {
             const int j = s_list[e];
+#pragma unroll
+            for (int l = 0; l <= L; ++l) kn[l] = load_k<L, TL>(P, j, l, c);
+#pragma unroll
+            for (int x = 0; x < n; ++x) vn[x] = load_v<L, VT, TL>(P, j, x, c);
+        };
+        if (AHEAD && cnt > 0) request(0);
+        for (int e = 0; e < cnt; ++e) {
+            if (!AHEAD) request(e);
             const float4 pj = s_pos[e];
             const float rx = pj.x - pi.x, ry = pj.y - pi.y, rz = pj.z - pi.z;
             const float4 rad = s_rad[e];
             const float2 bb = s_bias[e * P.H + head];
-            float kv[L + 1], dot = 0.0f;
+            float kv[L + 1], u[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // the three u_mu, then q k
 #pragma unroll
             for (int l = 0; l <= L; ++l) {
-                kv[l] = load_k<L, TL>(P, j, l, c);
-                dot += qv[l] * kv[l];
+                kv[l] = kn[l];
+                u[3] += qv[l] * kv[l];
             }
-            float u[3] = {0.0f, 0.0f, 0.0f};
-            dot = head_sum(dot, P.Ch);
-            const float p = pair_prob<TL>(P, dot, bb.x, lse);
-            const float phi = rad.x, dphi = rad.y;
 #pragma unroll
             for (int x = 0; x < n; ++x) {
-                const float vx = load_v<L, VT, TL>(P, j, x, c);
-                u[0] += gt[0][x] * vx;
-                u[1] += gt[1][x] * vx;
-                u[2] += gt[2][x] * vx;
+                u[0] += gt[0][x] * vn[x];
+                u[1] += gt[1][x] * vn[x];
+                u[2] += gt[2][x] * vn[x];
             }
-            u[0] = head_sum(u[0], P.Ch);
-            u[1] = head_sum(u[1], P.Ch);
-            u[2] = head_sum(u[2], P.Ch);
+            if (AHEAD) request(min(e + 1, cnt - 1));
+            e2f::group_sums(u, P.Ch);
+            const float p = pair_prob<TL>(P, u[3], bb.x, lse);
+            const float phi = rad.x, dphi = rad.y;
             const float wsum = rx * u[0] + ry * u[1] + rz * u[2];
             const float ds = p * (phi * wsum - Dn);
             const float alpha = p * phi;
@@ -428,43 +441,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         Y[0][x] = Y[1][x] = Y[2][x] = 0.0f;
     }
     float gx = 0.0f, gy = 0.0f, gz = 0.0f;   // sum_i dL/dr_ij of this head
-    ListWalk w;
-    w.init(P.cv, t);
+    __shared__ e2f::RunList s_run;
+    if (threadIdx.x < 64) e2f::fill_runs(s_run, P.cv, t, threadIdx.x);
+    int walked = 0;   // (next_batch opens with the barrier that the runs need)
     __syncthreads();
     float Gv[3][n];   // G_mu v_j: u_mu = <g_i, G_mu v_j>
     axis_apply<L, false>(vj, s_G, Gv);
     while (true) {
-        const int cnt = next_batch(P, w, t, pj, s_list, s_pos, s_rad, s_bias, s_ctl);
+        const int cnt = next_batch(P, s_run, walked, t, pj, s_list, s_pos, s_rad, s_bias, s_ctl);
+        constexpr bool AHEAD = ROWS_AHEAD<L>;
+        float qn[L + 1], gn[n], lse_n = 0.0f, Dn_n = 0.0f;   // the rows and statistics of the pair to come
+        auto request = [&](int e) {
+            const int i = s_list[e], ai = __float_as_int(s_pos[e].w);
+#pragma unroll
+            for (int l = 0; l <= L; ++l) qn[l] = load_q<L, TL>(P, i, l, c);
+#pragma unroll
+            for (int x = 0; x < n; ++x) gn[x] = P.gout[((size_t)ai * n + x) * C + c];
+            lse_n = load_lse<TL>(P, i, head);
+            Dn_n = load_Dn<TL>(P, i, head);
+        };
+        if (AHEAD && cnt > 0) request(0);
         for (int e = 0; e < cnt; ++e) {
-            const int i = s_list[e];           // the target, seen from j at its image s_pos[e]
-            const float4 pim = s_pos[e];
-            const int ai = __float_as_int(pim.w);
+            if (!AHEAD) request(e);
+            const float4 pim = s_pos[e];       // the target, seen from j at its image
             const float rx = pj.x - pim.x, ry = pj.y - pim.y, rz = pj.z - pim.z;   // r_ij = pos_j - pos_i
             const float4 rad = s_rad[e];
             const float2 bb = s_bias[e * P.H + head];
-            float qv[L + 1], dot = 0.0f;
+            float qv[L + 1], g[n], u[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // the three u_mu, then q k
 #pragma unroll
             for (int l = 0; l <= L; ++l) {
-                qv[l] = load_q<L, TL>(P, i, l, c);
-                dot += qv[l] * kv[l];
+                qv[l] = qn[l];
+                u[3] += qv[l] * kv[l];
             }
-            float g[n];
-            float u[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int x = 0; x < n; ++x) {
-                g[x] = P.gout[((size_t)ai * n + x) * C + c];
+                g[x] = gn[x];
                 u[0] += Gv[0][x] * g[x];
                 u[1] += Gv[1][x] * g[x];
                 u[2] += Gv[2][x] * g[x];
             }
-            dot = head_sum(dot, P.Ch);
-            u[0] = head_sum(u[0], P.Ch);
-            u[1] = head_sum(u[1], P.Ch);
-            u[2] = head_sum(u[2], P.Ch);
-            const float p = pair_prob<TL>(P, dot, bb.x, load_lse<TL>(P, i, head));
+            const float lse = lse_n, Dn = Dn_n;
+            if (AHEAD) request(min(e + 1, cnt - 1));
+            e2f::group_sums(u, P.Ch);
+            const float p = pair_prob<TL>(P, u[3], bb.x, lse);
             const float phi = rad.x, dphi = rad.y;
             const float wsum = rx * u[0] + ry * u[1] + rz * u[2];
-            const float ds = p * (phi * wsum - load_Dn<TL>(P, i, head));
+            const float ds = p * (phi * wsum - Dn);
             const float alpha = p * phi;
             const float dd = (ds * bb.y + p * wsum * dphi) / rad.z;
 #pragma unroll

@@ -129,6 +129,39 @@ __device__ __forceinline__ void stencil_run(const E2fCellsView& cv, int slot, in
     hi = have ? cv.cell_start[row + x_last + 1] : 0;
 }
 
+// The 18 runs of a slot's stencil in LDS as one list of candidates, run after run.  (Held in registers and indexed by a
+// running row they live in scratch memory, and a step that stops at the end of a run leaves most lanes idle: a run is
+// three cells, about 30 slots at 0.1 atoms per cubic Angstrom and a 6 Angstrom cutoff.)
+struct RunList {
+    int lo[18], pre[19];   // first slot of a run; candidates before it
+    float4 sh[18];         // lattice translation
+    __device__ __forceinline__ int total() const { return pre[18]; }
+    __device__ __forceinline__ void candidate(int c, int& run, int& slot) const {   // c < total()
+        run = 0;
+#pragma unroll
+        for (int r = 1; r < 18; ++r) run += c >= pre[r] ? 1 : 0;
+        slot = lo[run] + c - pre[run];
+    }
+};
+// One whole wave fills it; its readers wait for a barrier.
+__device__ __forceinline__ void fill_runs(RunList& s, const E2fCellsView& cv, int slot, int lane) {
+    int lo = 0, hi = 0;
+    float4 sh = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (lane < 18) stencil_run(cv, slot, lane, lo, hi, sh);
+    int end = hi - lo;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+        const int o = __shfl_up(end, off);
+        if (lane >= off) end += o;
+    }
+    if (lane < 18) {
+        s.lo[lane] = lo;
+        s.pre[lane + 1] = end;
+        s.sh[lane] = sh;
+    }
+    if (lane == 0) s.pre[0] = 0;
+}
+
 // The open-boundary stencil as plain arrays.
 __device__ __forceinline__ void stencil_rows(const E2fCellsView& cv, int slot, int (&lo)[9], int (&hi)[9]) {
     Stencil<false> s;
@@ -293,6 +326,36 @@ __host__ __device__ __forceinline__ void nl_element(int n, int i, int& head, int
         x = full * 8 + tail % rem;
         ch = tail / rem;
     }
+}
+
+// Sums of K values over groups of `lanes` neighbouring lanes (a power of two, at most 64; the same in every lane of the
+// wave), in every lane of the group.  Inside a row of 16 lanes the partners are reached by cross-lane operands of the
+// additions instead of shuffles through the LDS unit: exchanges at distance 1 and 2, then the mirrored half row and the
+// mirrored row, whose lanes hold the same sums as the ones at distance 4 and 8 (so the bits are those of a butterfly).
+template <int CTRL>
+__device__ __forceinline__ float lane_partner(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int K>
+__device__ __forceinline__ void group_sums(float (&x)[K], int lanes) {
+    if (lanes > 1)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += lane_partner<0xB1>(x[i]);    // lanes 1 0 3 2 of a quad
+    if (lanes > 2)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += lane_partner<0x4E>(x[i]);    // lanes 2 3 0 1 of a quad
+    if (lanes > 4)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += lane_partner<0x141>(x[i]);   // half rows mirrored
+    if (lanes > 8)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += lane_partner<0x140>(x[i]);   // rows mirrored
+    if (lanes > 16)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += __shfl_xor(x[i], 16);
+    if (lanes > 32)
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] += __shfl_xor(x[i], 32);
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

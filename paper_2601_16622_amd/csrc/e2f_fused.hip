@@ -43,6 +43,8 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
     constexpr int n = (L + 1) * (L + 1);
     constexpr int DS = e2f::d_offset(L + 1);
     constexpr int DSP = (DS + 3) & ~3;
+    constexpr int LG = 8;                      // pairs whose logits are formed side by side
+    constexpr bool AHEAD = n * CPL <= 18;      // a pair's value row is requested during the pair before, where registers allow
     __shared__ int s_list[CAP];
     __shared__ __attribute__((aligned(16))) float s_D[PB * DSP];
     __shared__ float s_bias[PB * E2F_MAX_H];
@@ -75,20 +77,19 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
     float mu = -INFINITY, z = 0.0f;
 
     // (the 18-run form also serves open boundaries: its extra runs are empty and every translation is zero)
-    e2f::Stencil<true> st;
-    st.init(P.cv, t);
+    __shared__ e2f::RunList s_run;
+    e2f::fill_runs(s_run, P.cv, t, lane);
+    __syncthreads();
     constexpr int RUN_SHIFT = 26;   // a list entry is slot | run << 26; the launcher checks N < 2^26
 
-    int row = 0, base = st.lo[0];
-    bool rows_done = false;
+    const int total = TABLE ? P.K : s_run.total();
+    int base = 0;
     const int32_t* trow = TABLE ? P.table + (size_t)P.cv.perm[t] * P.K : nullptr;
-    int tb = 0;
     while (true) {
         // ---- fill the list
         int cnt = 0;
-        while (TABLE && !rows_done && cnt + 64 <= CAP) {
-            if (tb >= P.K) { rows_done = true; break; }
-            const int aj = tb + lane < P.K ? trow[tb + lane] : -1;
+        while (TABLE && base < total && cnt + 64 <= CAP) {
+            const int aj = base + lane < P.K ? trow[base + lane] : -1;
             const int j = aj >= 0 ? P.cv.atom_slot[aj] : -1;
             bool ok = false;
             if (j >= 0 && j != t) {
@@ -98,25 +99,19 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
             const unsigned long long mask = __ballot(ok);
             if (ok) s_list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = j;
             cnt += __popcll(mask);
-            tb += 64;
+            base += 64;
         }
-        while (!TABLE && !rows_done && cnt + 64 <= CAP) {
-            if (base >= st.hi[row]) {
-                ++row;
-                if (row == 18) { rows_done = true; break; }
-                base = st.lo[row];
-                continue;
-            }
-            const int j = base + lane;
+        while (!TABLE && base < total && cnt + 64 <= CAP) {
             bool ok = false;
-            if (j < st.hi[row] && j != t) {
-                const float4 pj = P.spos[j];
-                const float d2 = e2f::dist2_exact(pi.x, pi.y, pi.z, pj.x + st.shift_x(row), pj.y + st.shift_y(row),
-                                                  pj.z + st.shift_z(row));
-                ok = e2f::is_neighbor(d2, P.rc2) && e2f::under_cap(d2, pj.w, capd, capi);
+            int j = 0, run = 0;
+            if (base + lane < total) {
+                s_run.candidate(base + lane, run, j);
+                const float4 pj = P.spos[j], sh = s_run.sh[run];
+                const float d2 = e2f::dist2_exact(pi.x, pi.y, pi.z, pj.x + sh.x, pj.y + sh.y, pj.z + sh.z);
+                ok = j != t && e2f::is_neighbor(d2, P.rc2) && e2f::under_cap(d2, pj.w, capd, capi);
             }
             const unsigned long long mask = __ballot(ok);
-            if (ok) s_list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = j | (row << RUN_SHIFT);
+            if (ok) s_list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = j | (run << RUN_SHIFT);
             cnt += __popcll(mask);
             base += 64;
         }
@@ -126,9 +121,9 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
             const int np = min(PB, cnt - p0);
             if (lane < np) {
                 const int e = s_list[p0 + lane], j = e & ((1 << RUN_SHIFT) - 1), run = e >> RUN_SHIFT;
-                const float4 pj = P.spos[j];
-                const float dx = (pj.x + st.shift_x(run)) - pi.x, dy = (pj.y + st.shift_y(run)) - pi.y;
-                const float dz = (pj.z + st.shift_z(run)) - pi.z;
+                const float4 pj = P.spos[j], sh = s_run.sh[run];
+                const float dx = (pj.x + sh.x) - pi.x, dy = (pj.y + sh.y) - pi.y;
+                const float dz = (pj.z + sh.z) - pi.z;
                 const float d = sqrtf(dx * dx + dy * dy + dz * dz);
                 if constexpr (LF != 0) e2f::align_D<L>(dx, dy, dz, d, s_D + lane * DSP);
                 for (int hh = 0; hh < H; ++hh) {
@@ -139,23 +134,33 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
                 s_wgt[lane] = e2f::radial_gate(d, P.cutoff) * e2f::pow_lf<LF>(d);
             }
             __syncthreads();
-            // logits of the chunk (Eq. kernel_score)
+            // logits of the chunk (Eq. kernel_score), LG pairs side by side: their rows are requested together and their
+            // sums over the head's lanes interleave (one pair after the other spent most of a small call waiting for
+            // rows).  A place behind the chunk's last pair repeats that pair with a logit of -inf.
             float s_arr[PB];
             float cmax = -INFINITY;
 #pragma unroll
-            for (int p = 0; p < PB; ++p) {
-                s_arr[p] = -INFINITY;
-                if (p < np) {
-                    const int j = s_list[p0 + p] & ((1 << RUN_SHIFT) - 1);
-                    const float* kj = P.k + (size_t)j * (L + 1) * C + c0;
-                    float dot = 0.0f;
+            for (int g0 = 0; g0 < PB; g0 += LG) {
 #pragma unroll
-                    for (int l = 0; l <= L; ++l)
+                for (int p = g0; p < g0 + LG; ++p) s_arr[p] = -INFINITY;
+                if (g0 < np) {
+                    float dot[LG];
 #pragma unroll
-                        for (int u = 0; u < CPL; ++u) dot += q[l][u] * kj[l * C + u];
-                    for (int off = 1; off < lanes_per_head; off <<= 1) dot += __shfl_xor(dot, off);
-                    s_arr[p] = dot * P.tau + s_bias[p * E2F_MAX_H + head];
-                    cmax = fmaxf(cmax, s_arr[p]);
+                    for (int x = 0; x < LG; ++x) {
+                        const int j = s_list[p0 + min(g0 + x, np - 1)] & ((1 << RUN_SHIFT) - 1);
+                        const float* kj = P.k + (size_t)j * (L + 1) * C + c0;
+                        dot[x] = 0.0f;
+#pragma unroll
+                        for (int l = 0; l <= L; ++l)
+#pragma unroll
+                            for (int u = 0; u < CPL; ++u) dot[x] += q[l][u] * kj[l * C + u];
+                    }
+                    e2f::group_sums(dot, lanes_per_head);
+#pragma unroll
+                    for (int x = 0; x < LG; ++x) {
+                        if (g0 + x < np) s_arr[g0 + x] = dot[x] * P.tau + s_bias[(g0 + x) * E2F_MAX_H + head];
+                        cmax = fmaxf(cmax, s_arr[g0 + x]);
+                    }
                 }
             }
             // one rescale of the running state per chunk (the updates of mu, z and A in Algorithm 1, taken chunk-wise)
@@ -167,6 +172,16 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
 #pragma unroll
                 for (int u = 0; u < CPL; ++u) A[x][u] *= scale;
             mu = mu_new;
+            auto load_v = [&](int p, float (&dst)[n][CPL]) {
+                const int j = s_list[p0 + p] & ((1 << RUN_SHIFT) - 1);
+                const VT* vj = (const VT*)P.v + (size_t)j * n * C + c0;
+#pragma unroll
+                for (int x = 0; x < n; ++x)
+#pragma unroll
+                    for (int u = 0; u < CPL; ++u) dst[x][u] = e2f::load_as_float(vj + x * C + u);
+            };
+            float vin[n][CPL], vnext[AHEAD ? n : 1][CPL];
+            if constexpr (AHEAD) load_v(0, vnext);
 #pragma unroll 1
             for (int p = 0; p < np; ++p) {
                 // s_arr is indexed by a runtime p: select without dynamic register indexing
@@ -176,18 +191,20 @@ __global__ __launch_bounds__(64) void k_fused_valu(FusedParams P) {
                 const float pe = __expf(sp - mu);
                 z += pe;
                 const float wgt = pe * s_wgt[p];
-                const int j = s_list[p0 + p] & ((1 << RUN_SHIFT) - 1);
-                const VT* vj = (const VT*)P.v + (size_t)j * n * C + c0;
-                float vin[n][CPL];
+                if constexpr (AHEAD) {
 #pragma unroll
-                for (int x = 0; x < n; ++x)
+                    for (int x = 0; x < n; ++x)
 #pragma unroll
-                    for (int u = 0; u < CPL; ++u) vin[x][u] = e2f::load_as_float(vj + x * C + u);
+                        for (int u = 0; u < CPL; ++u) vin[x][u] = vnext[x][u];
+                    load_v(min(p + 1, np - 1), vnext);
+                } else {
+                    load_v(p, vin);
+                }
                 e2f::eaas_accumulate<L, LF, CPL>(vin, s_D + p * DSP, P.cw, wgt, A);
             }
             __syncthreads();
         }
-        if (rows_done) break;
+        if (base >= total) break;
     }
 
     if (active) {
