@@ -600,14 +600,7 @@ e2f_status e2f_attn_forward_nonlinear(e2f_ctx* ctx, const e2f_cells* cells, cons
     const E2fAttnWs L = e2f_attn_ws_layout(ctx, N, ws, 0);
     void* q1 = static_cast<char*>(ws) + L.bytes;
     if ((rc = e2f_launch_prepare(ctx, cells->view, pos, w, L, st)) != E2F_OK) return rc;
-    // W_Q1 h of every atom: the projection kernel once more, with W_Q1 in the value's place (it rewrites q and k
-    // with the same numbers; the second run below leaves them in place with the values)
-    e2f_weights wq = *w;
-    wq.WV = w->WQ1;
-    E2fAttnWs Lq = L;
-    Lq.v = q1;
-    if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, &wq, Lq, 0, st)) != E2F_OK) return rc;
-    if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, 0, st)) != E2F_OK) return rc;
+    if ((rc = e2f_launch_project_q1(ctx, cells->view, h, w, L, q1, st)) != E2F_OK) return rc;
     return e2f_launch_fused_nonlinear(ctx, cells->view, w, L, q1, out, st);
 }
 

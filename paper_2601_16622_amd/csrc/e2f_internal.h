@@ -178,6 +178,8 @@ e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, c
 bool e2f_factorized_supported(const e2f_ctx* ctx);
 e2f_status e2f_launch_factorized(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, const E2fFactWs& fw,
                                  float* out, hipStream_t st);
+e2f_status e2f_launch_project_q1(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
+                                 const E2fAttnWs& ws, void* q1, hipStream_t st);
 e2f_status e2f_launch_project_simple(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
                                      float* q, float* k, float* v, hipStream_t st);
 e2f_status e2f_launch_fused(const e2f_ctx* ctx, const E2fCellsView& cv, const e2f_weights* w, const E2fAttnWs& ws,
