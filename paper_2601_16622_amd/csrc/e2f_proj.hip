@@ -115,7 +115,7 @@ __device__ __forceinline__ void store_run_bf16(uint16_t* row, int pos0, const fl
 // components in tile order (HI: l=4 rows 0..8, l=3 rows 9..15; LO: l=2 rows 0..4, l=1 rows 5..7, l=0 row 8,
 // rows 9..15 zero), heads of 16 channels.
 template <typename T, int C, int MG, int CT, bool TILED>
-__global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && C <= (sizeof(T) == 2 ? 192 : 128) ? 2 : 1))) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
@@ -137,6 +137,10 @@ __global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* _
         kacc[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     for (int m0 = 0; m0 < nl; m0 += MG) {
+        // (an offset of zero that the compiler cannot see through: the weights are the same for every pass over the
+        // orders, and it would load those of all five maps before the loop and keep them in registers)
+        int fresh = 0;
+        asm volatile("" : "+s"(fresh));
         typename F::type A[MG][NS];
 #pragma unroll
         for (int mm = 0; mm < MG; ++mm) {
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* _
         }
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-            const size_t wr = wrow + (size_t)ct * 16 * C;
+            const size_t wr = wrow + (size_t)ct * 16 * C + fresh;
             const int co = (cg * CT + ct) * 16 + i;
             // q and k: two projections each, multiplied element-wise and summed over m
 #pragma unroll
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* _
 // channel tiles, tiled v rows by two degrees) merge in that XCD's L2 before they reach memory, and the h rows
 // they all read are fetched once.  q1 (or null; plain layout only): W_Q1 h as well, in v's layout.
 template <int C, bool TILED>
-__global__ __launch_bounds__(64) void k_project_ws(E2fCellsView cv, const uint16_t* __restrict__ h,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && !TILED ? 2 : 1))) void k_project_ws(E2fCellsView cv, const uint16_t* __restrict__ h,
                                                    const uint16_t* __restrict__ WQ1, const uint16_t* __restrict__ WQ2,
                                                    const uint16_t* __restrict__ WK1, const uint16_t* __restrict__ WK2,
                                                    const uint16_t* __restrict__ WV, int L, int tpw,
@@ -922,8 +926,10 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
     if constexpr (C % Frag<T>::KSTEP != 0) {
         return false;
     } else {
-        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order)
-        constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 5 : 2));
+        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order), and for one
+        // channel tile so that two waves fit a SIMD (a wave alone waits for every weight tile it loads: fp32, 128 channels,
+        // five orders in 366 registers 60 us at 2 240 atoms, L = 2; three orders in 208 registers take 8 us off the call)
+        constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 3 : 2));
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
         const int waves_ct = (cv.N + 15) / 16 * (ctx->cfg.L_max + 1) * (C / 16 / CT);
