@@ -19,6 +19,30 @@ __global__ void k_cells_init(int32_t* bbox, int S, int32_t* cell_start, int32_t*
     if (i < max_cells) cell_fill[i] = 0;
 }
 
+// Boxes of a wave's segments: v comes as the lane's position twice and leaves, in the first lane of every run of lanes
+// with the same `seg` (-1: no atom), as min x, y, z and max x, y, z of the run.  Returns whether this lane is the first of a run.
+__device__ __forceinline__ bool run_boxes(int seg, int lane, float (&v)[6]) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const bool same = __shfl_down(seg, off) == seg && lane + off < 64;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const float o = __shfl_down(v[k], off);
+            if (same) v[k] = k < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
+        }
+    }
+    const int before = __shfl_up(seg, 1);
+    return seg >= 0 && (lane == 0 || before != seg);
+}
+__device__ __forceinline__ int segment_of(const int32_t* seg_offsets, int S, int a) {   // largest s with seg_offsets[s] <= a
+    int lo = 0, hi = S;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (seg_offsets[mid] <= a) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 // Segment of every atom (binary search in the offsets) and the segment bounding boxes.
 __global__ void k_cells_bbox(const float* __restrict__ pos, const int32_t* __restrict__ seg_offsets, int N, int S,
                              int32_t* __restrict__ atom_seg, int32_t* __restrict__ bbox) {
@@ -27,12 +51,7 @@ __global__ void k_cells_bbox(const float* __restrict__ pos, const int32_t* __res
     int s = 0;
     float x = 0.f, y = 0.f, z = 0.f;
     if (live) {
-        int lo = 0, hi = S;  // largest s with seg_offsets[s] <= a
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (seg_offsets[mid] <= a) lo = mid; else hi = mid;
-        }
-        s = lo;
+        s = segment_of(seg_offsets, S, a);
         atom_seg[a] = s;
         x = pos[3 * a]; y = pos[3 * a + 1]; z = pos[3 * a + 2];
     }
@@ -46,17 +65,7 @@ __global__ void k_cells_bbox(const float* __restrict__ pos, const int32_t* __res
     const int sl = live ? s : -1, s0 = __shfl(sl, 0);
     const bool uniform = __all(live && s == s0);
     float v[6] = {x, y, z, x, y, z};   // min x, y, z; max x, y, z
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const bool same = __shfl_down(sl, off) == sl && lane + off < 64;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const float o = __shfl_down(v[k], off);
-            if (same) v[k] = k < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
-        }
-    }
-    const int before = __shfl_up(sl, 1);
-    const bool first = live && (lane == 0 || before != sl);   // first lane of its segment in this wave
+    const bool first = run_boxes(sl, lane, v);
     if (lane == 0) {
         s_seg[wave] = uniform ? s0 : -1;
 #pragma unroll
@@ -81,9 +90,54 @@ __global__ void k_cells_bbox(const float* __restrict__ pos, const int32_t* __res
     }
 }
 
-// One block: grid of every segment (edge doubled until the segment stays within its cell budget of
-// 27 + 2 * atoms, so the total never exceeds the workspace), then an exclusive scan of the cell counts.
-// A periodic axis (box length > 0) gets floor(length / edge) >= 3 cells that tile the box exactly, origin 0.
+// Grid of a segment of ns atoms with bounding box bb (ordered integers): the edge is doubled until the segment stays
+// within its cell budget of 27 + 2 * atoms, so that the total never exceeds the workspace.  A periodic axis (box: lengths
+// and their reciprocals, or null; length > 0) gets floor(length / edge) >= 3 cells that tile the box exactly, origin 0.
+// Returns the number of cells; the first cell's id is left to the caller.
+__device__ __forceinline__ int segment_grid(int ns, const int32_t* bb, float edge0, const float* __restrict__ box, E2fSegGrid& g) {
+    int cells = 1;  // an empty segment keeps one empty cell
+    const float lx = box ? box[0] : 0.0f, ly = box ? box[1] : 0.0f, lz = box ? box[2] : 0.0f;
+    g.lx = lx; g.ly = ly; g.lz = lz;
+    g.rx = box ? box[3] : 0.0f;
+    g.ry = box ? box[4] : 0.0f;
+    g.rz = box ? box[5] : 0.0f;
+    if (ns > 0) {
+        const float mnx = ordered_to_float(bb[0]), mny = ordered_to_float(bb[1]);
+        const float mnz = ordered_to_float(bb[2]), mxx = ordered_to_float(bb[3]);
+        const float mxy = ordered_to_float(bb[4]), mxz = ordered_to_float(bb[5]);
+        const long long budget = 27ll + 2ll * ns;
+        float edge = edge0;
+        long long nx = 1, ny = 1, nz = 1;
+        bool fits = false;
+        auto cells_along = [&](float len, float extent) -> long long {
+            const long long whole = (long long)floorf((len > 0.0f ? len : extent) / edge);
+            return len > 0.0f ? (whole > 3 ? whole : 3) : whole + 1;   // (27 cells always fit the budget)
+        };
+        for (int it = 0; it < 200 && !fits; ++it) {  // bounded: edge overflows to inf long before
+            nx = cells_along(lx, mxx - mnx);
+            ny = cells_along(ly, mxy - mny);
+            nz = cells_along(lz, mxz - mnz);
+            fits = nx >= 1 && ny >= 1 && nz >= 1 && nx <= budget && ny <= budget && nz <= budget &&
+                   nx * ny * nz <= budget;
+            if (!fits) edge *= 2.0f;
+        }
+        if (!fits) {  // non-finite coordinates: one cell holds the whole segment
+            nx = ny = nz = 1;
+            edge = edge0;
+        }
+        g.ox = lx > 0.0f ? 0.0f : mnx;
+        g.oy = ly > 0.0f ? 0.0f : mny;
+        g.oz = lz > 0.0f ? 0.0f : mnz;
+        g.ix = lx > 0.0f ? (float)nx / lx : 1.0f / edge;
+        g.iy = ly > 0.0f ? (float)ny / ly : 1.0f / edge;
+        g.iz = lz > 0.0f ? (float)nz / lz : 1.0f / edge;
+        g.nx = (int)nx; g.ny = (int)ny; g.nz = (int)nz;
+        cells = (int)(nx * ny * nz);
+    }
+    return cells;
+}
+
+// One block: grid of every segment, and an exclusive scan of the cell counts.
 __global__ void k_cells_grid(const int32_t* __restrict__ bbox, const int32_t* __restrict__ seg_offsets, int S,
                              float edge0, const float* __restrict__ box, E2fSegGrid* __restrict__ grid) {
     __shared__ int s_part[1024];
@@ -96,46 +150,7 @@ __global__ void k_cells_grid(const int32_t* __restrict__ bbox, const int32_t* __
         E2fSegGrid g = {0.f, 0.f, 0.f, 1.f, 1.f, 1.f, 1, 1, 1, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (s < S) {
             const int ns = seg_offsets[s + 1] - seg_offsets[s];
-            cells = 1;  // an empty segment keeps one empty cell
-            // box: [S][6], lengths (0 = open axis) and their reciprocals as the host rounded them
-            const float lx = box ? box[6 * s] : 0.0f, ly = box ? box[6 * s + 1] : 0.0f, lz = box ? box[6 * s + 2] : 0.0f;
-            g.lx = lx; g.ly = ly; g.lz = lz;
-            g.rx = box ? box[6 * s + 3] : 0.0f;
-            g.ry = box ? box[6 * s + 4] : 0.0f;
-            g.rz = box ? box[6 * s + 5] : 0.0f;
-            if (ns > 0) {
-                const float mnx = ordered_to_float(bbox[s * 6 + 0]), mny = ordered_to_float(bbox[s * 6 + 1]);
-                const float mnz = ordered_to_float(bbox[s * 6 + 2]), mxx = ordered_to_float(bbox[s * 6 + 3]);
-                const float mxy = ordered_to_float(bbox[s * 6 + 4]), mxz = ordered_to_float(bbox[s * 6 + 5]);
-                const long long budget = 27ll + 2ll * ns;
-                float edge = edge0;
-                long long nx = 1, ny = 1, nz = 1;
-                bool fits = false;
-                auto cells_along = [&](float len, float extent) -> long long {
-                    const long long whole = (long long)floorf((len > 0.0f ? len : extent) / edge);
-                    return len > 0.0f ? (whole > 3 ? whole : 3) : whole + 1;   // (27 cells always fit the budget)
-                };
-                for (int it = 0; it < 200 && !fits; ++it) {  // bounded: edge overflows to inf long before
-                    nx = cells_along(lx, mxx - mnx);
-                    ny = cells_along(ly, mxy - mny);
-                    nz = cells_along(lz, mxz - mnz);
-                    fits = nx >= 1 && ny >= 1 && nz >= 1 && nx <= budget && ny <= budget && nz <= budget &&
-                           nx * ny * nz <= budget;
-                    if (!fits) edge *= 2.0f;
-                }
-                if (!fits) {  // non-finite coordinates: one cell holds the whole segment
-                    nx = ny = nz = 1;
-                    edge = edge0;
-                }
-                g.ox = lx > 0.0f ? 0.0f : mnx;
-                g.oy = ly > 0.0f ? 0.0f : mny;
-                g.oz = lz > 0.0f ? 0.0f : mnz;
-                g.ix = lx > 0.0f ? (float)nx / lx : 1.0f / edge;
-                g.iy = ly > 0.0f ? (float)ny / ly : 1.0f / edge;
-                g.iz = lz > 0.0f ? (float)nz / lz : 1.0f / edge;
-                g.nx = (int)nx; g.ny = (int)ny; g.nz = (int)nz;
-                cells = (int)(nx * ny * nz);
-            }
+            cells = segment_grid(ns, bbox + 6 * s, edge0, box ? box + 6 * s : nullptr, g);
         }
         // block-wide exclusive scan of `cells`
         s_part[threadIdx.x] = cells;
@@ -159,25 +174,31 @@ __global__ void k_cells_grid(const int32_t* __restrict__ bbox, const int32_t* __
     if (threadIdx.x == 0) grid[S].base = s_carry;   // cells in use: what the scan of the counts has to cover
 }
 
-__global__ void k_cells_assign(const float* __restrict__ pos, const int32_t* __restrict__ atom_seg,
-                               const E2fSegGrid* __restrict__ grid, int N, int32_t* __restrict__ atom_cell,
-                               int32_t* __restrict__ atom_sub, int32_t* __restrict__ cell_count /* = cell_start + 1 */) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= N) return;
-    const E2fSegGrid g = grid[atom_seg[a]];
-    const float fx = (e2f::fold_coord(pos[3 * a], g.lx, g.rx) - g.ox) * g.ix;
-    const float fy = (e2f::fold_coord(pos[3 * a + 1], g.ly, g.ry) - g.oy) * g.iy;
-    const float fz = (e2f::fold_coord(pos[3 * a + 2], g.lz, g.rz) - g.oz) * g.iz;
+// Cell of a position p, and its place in the order inside the cell.
+__device__ __forceinline__ void cell_of(const float* p, const E2fSegGrid& g, int& c, int& sub) {
+    const float fx = (e2f::fold_coord(p[0], g.lx, g.rx) - g.ox) * g.ix;
+    const float fy = (e2f::fold_coord(p[1], g.ly, g.ry) - g.oy) * g.iy;
+    const float fz = (e2f::fold_coord(p[2], g.lz, g.rz) - g.oz) * g.iz;
     int cx = (int)floorf(fx), cy = (int)floorf(fy), cz = (int)floorf(fz);
     cx = min(max(cx, 0), g.nx - 1); cy = min(max(cy, 0), g.ny - 1); cz = min(max(cz, 0), g.nz - 1);
-    const int c = g.base + (cz * g.ny + cy) * g.nx + cx;
-    atom_cell[a] = c;
+    c = g.base + (cz * g.ny + cy) * g.nx + cx;
     // Order inside the cell: Morton index over 4x4x4 sub-cells, so that atoms that are consecutive in the sorted
     // order (the 16-atom target tiles and the 4-slot candidate groups of the attention kernels) are close in space.
     const int sx = min(max((int)((fx - (float)cx) * 4.0f), 0), 3), sy = min(max((int)((fy - (float)cy) * 4.0f), 0), 3);
     const int sz = min(max((int)((fz - (float)cz) * 4.0f), 0), 3);
     auto spread = [](int v) { return (v & 1) | ((v & 2) << 2); };   // bit 0 -> 0, bit 1 -> 3
-    atom_sub[a] = spread(sx) | (spread(sy) << 1) | (spread(sz) << 2);
+    sub = spread(sx) | (spread(sy) << 1) | (spread(sz) << 2);
+}
+
+__global__ void k_cells_assign(const float* __restrict__ pos, const int32_t* __restrict__ atom_seg,
+                               const E2fSegGrid* __restrict__ grid, int N, int32_t* __restrict__ atom_cell,
+                               int32_t* __restrict__ atom_sub, int32_t* __restrict__ cell_count /* = cell_start + 1 */) {
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a >= N) return;
+    int c, sub;
+    cell_of(pos + 3 * a, grid[atom_seg[a]], c, sub);
+    atom_cell[a] = c;
+    atom_sub[a] = sub;
     atomicAdd(&cell_count[c], 1);
 }
 
@@ -214,6 +235,12 @@ __global__ void k_cells_scatter(const int32_t* __restrict__ atom_cell, const int
     tmp_slot[cell_start[c] + atomicAdd(&cell_fill[c], 1)] = a;
 }
 
+__device__ __forceinline__ void store_sinfo(int4* dst, int seg, int c, const E2fSegGrid& g) {
+    const int local = c - g.base;
+    dst[0] = make_int4(seg, local % g.nx, (local / g.nx) % g.ny, local / (g.nx * g.ny));
+    dst[1] = make_int4(g.nx, g.ny, g.nz, g.base);
+}
+
 // The scatter above fills each cell in arrival order; ranking every atom among its cell mates by (sub-cell, atom
 // index) makes the final order independent of that.
 __global__ void k_cells_rank(const int32_t* __restrict__ tmp_slot, const int32_t* __restrict__ atom_cell,
@@ -236,10 +263,125 @@ __global__ void k_cells_rank(const int32_t* __restrict__ tmp_slot, const int32_t
     scell[b + rank] = c;
     sseg[b + rank] = atom_seg[a];
     atom_slot[a] = b + rank;
-    const E2fSegGrid g = grid[atom_seg[a]];
-    const int local = c - g.base;
-    sinfo[2 * (b + rank)] = make_int4(atom_seg[a], local % g.nx, (local / g.nx) % g.ny, local / (g.nx * g.ny));
-    sinfo[2 * (b + rank) + 1] = make_int4(g.nx, g.ny, g.nz, g.base);
+    store_sinfo(sinfo + 2 * (b + rank), atom_seg[a], c, grid[atom_seg[a]]);
+}
+
+// Inclusive scan over the 1024 threads of a workgroup (s: 16 ints, free again after the caller's next barrier).
+__device__ __forceinline__ int block_scan(int v, int* s) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(v, off);
+        if (lane >= off) v += o;
+    }
+    if (lane == 63) s[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += s[w];
+    return v;
+}
+
+// The whole construction for a small call, in one workgroup and one launch: what the kernels above pass on through
+// memory stays in LDS (boxes, grids, cell offsets, sort keys) and registers (an atom's cell).  The same functions in the
+// same order, so the same lists.  The seven launches above are mostly launch: whole calls in us, seven launches / this, at 64
+// atoms 57.5 / 45.9, 160 in 20 molecules 71.6 / 61.8, 2 000 atoms 92.5 / 80.4, 4 000 in 16 molecules 146 / 136 (the last
+// size with all sort keys in registers and LDS: four atoms per thread, 60 KB).
+constexpr int SMALL_N = 4096, SMALL_S = 1024, SMALL_PER = SMALL_N / 1024;
+__global__ __launch_bounds__(1024) void k_cells_small(const float* __restrict__ pos, const int32_t* __restrict__ seg_offsets, int N,
+                                                      int S, int max_cells, float edge0, const float* __restrict__ box,
+                                                      E2fSegGrid* __restrict__ grid, int32_t* __restrict__ cell_start,
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ scell,
+                                                      int32_t* __restrict__ sseg, int32_t* __restrict__ atom_slot,
+                                                      int4* __restrict__ sinfo) {
+    extern __shared__ int s_mem[];
+    int* s_bbox = s_mem;                                            // [S][6]
+    int* s_off = s_bbox + 6 * S;                                    // [S + 1] segment offsets
+    E2fSegGrid* s_grid = reinterpret_cast<E2fSegGrid*>(s_off + S + 1);   // [S]
+    int* s_start = reinterpret_cast<int*>(s_grid + S);              // [max_cells + 1] counts, then offsets
+    unsigned* s_key = reinterpret_cast<unsigned*>(s_start + max_cells + 1);   // [N]
+    __shared__ int s_scan[2][16];
+    __shared__ int s_cells;
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < 6 * S; i += 1024) s_bbox[i] = (i % 6 < 3) ? INT_MAX : INT_MIN;
+    for (int i = tid; i <= S; i += 1024) s_off[i] = seg_offsets[i];
+    for (int i = tid; i <= max_cells; i += 1024) s_start[i] = 0;
+    __syncthreads();
+    int seg[SMALL_PER], cell[SMALL_PER], sub[SMALL_PER], turn[SMALL_PER];
+    float p[SMALL_PER][3];
+#pragma unroll
+    for (int k = 0; k < SMALL_PER; ++k) {
+        const int a = tid + 1024 * k;
+        seg[k] = -1;
+        p[k][0] = p[k][1] = p[k][2] = 0.0f;
+        if (a < N) {
+            p[k][0] = pos[3 * a];
+            p[k][1] = pos[3 * a + 1];
+            p[k][2] = pos[3 * a + 2];
+            seg[k] = segment_of(s_off, S, a);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < SMALL_PER; ++k) {
+        float v[6] = {p[k][0], p[k][1], p[k][2], p[k][0], p[k][1], p[k][2]};
+        if (run_boxes(seg[k], lane, v)) {
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                atomicMin(&s_bbox[6 * seg[k] + x], float_to_ordered(v[x]));
+                atomicMax(&s_bbox[6 * seg[k] + 3 + x], float_to_ordered(v[3 + x]));
+            }
+        }
+    }
+    __syncthreads();
+    {
+        E2fSegGrid g = {0.f, 0.f, 0.f, 1.f, 1.f, 1.f, 1, 1, 1, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        int cells = 0;
+        if (tid < S) cells = segment_grid(s_off[tid + 1] - s_off[tid], s_bbox + 6 * tid, edge0, box ? box + 6 * tid : nullptr, g);
+        const int end = block_scan(cells, s_scan[0]);
+        if (tid < S) {
+            g.base = end - cells;
+            s_grid[tid] = g;
+            grid[tid] = g;
+        }
+        if (tid == 1023) s_cells = end;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER; ++k)
+        if (seg[k] >= 0) {
+            cell_of(p[k], s_grid[seg[k]], cell[k], sub[k]);
+            turn[k] = atomicAdd(&s_start[cell[k] + 1], 1);   // (any order: the ranks below do not depend on it)
+        }
+    __syncthreads();
+    {
+        const int n = s_cells + 1, chunk = (n + 1023) / 1024, b = min(tid * chunk, n), e = min(b + chunk, n);
+        int sum = 0;
+        for (int i = b; i < e; ++i) sum += s_start[i];
+        int run = block_scan(sum, s_scan[1]) - sum;
+        for (int i = b; i < e; ++i) {
+            run += s_start[i];
+            s_start[i] = run;
+            cell_start[i] = run;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER; ++k)
+        if (seg[k] >= 0) s_key[s_start[cell[k]] + turn[k]] = ((unsigned)sub[k] << 16) | (unsigned)(tid + 1024 * k);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER; ++k)
+        if (seg[k] >= 0) {
+            const int a = tid + 1024 * k, b = s_start[cell[k]], e = s_start[cell[k] + 1];
+            const unsigned key = ((unsigned)sub[k] << 16) | (unsigned)a;
+            int slot = b;
+#pragma unroll 4
+            for (int u = b; u < e; ++u) slot += s_key[u] < key ? 1 : 0;
+            perm[slot] = a;
+            scell[slot] = cell[k];
+            sseg[slot] = seg[k];
+            atom_slot[a] = slot;
+            store_sinfo(sinfo + 2 * slot, seg[k], cell[k], s_grid[seg[k]]);
+        }
+    if (tid == 0) grid[S].base = s_cells;
 }
 
 // One wave per target: walk the 27-cell stencil 64 candidates at a time.
@@ -290,9 +432,9 @@ __global__ __launch_bounds__(64) void k_neighbors(E2fCellsView cv, const float* 
 }
 
 // Neighbour cap: one wave per target finds the K-th smallest key (bits of d^2, atom index) among the target's
-// neighbours inside the cutoff by an 8-bit radix select over the 64-bit keys (a 256-bin histogram in LDS per digit;
-// the keys are kept in LDS after one stencil walk, or, beyond 512 neighbours, the stencil is walked once per digit,
-// so there is no limit on their number), then writes the threshold key and / or the
+// neighbours inside the cutoff.  Up to 256 neighbours: by counting.  More: by an 8-bit radix select over the 64-bit keys (a
+// 256-bin histogram in LDS per digit; the keys are kept in LDS after one stencil walk, or, beyond 512 neighbours, the
+// stencil is walked once per digit, so there is no limit on their number).  Then writes the threshold key and / or the
 // table row of the selected atoms (in cell order, -1 padded).  Keys are unique, so exactly min(K, degree) atoms pass.
 template <bool PBC>
 __global__ __launch_bounds__(64) void k_select_neighbors(E2fCellsView cv, const float* __restrict__ pos, float rc2,
@@ -305,27 +447,29 @@ __global__ __launch_bounds__(64) void k_select_neighbors(E2fCellsView cv, const 
     const E2fSegGrid g = cv.grid[cv.sseg[t]];
     float xi, yi, zi;
     atom_position<PBC>(pos, ai, g, xi, yi, zi);
-    e2f::Stencil<PBC> st;
-    st.init(cv, t);
+    __shared__ e2f::RunList s_run;
+    e2f::fill_runs(s_run, cv, t, lane);
+    __syncthreads();
+    const int candidates = s_run.total();
     // walk(f): f(ok, key, atom) for every candidate of this lane, all lanes in step
     auto walk = [&](auto&& f) {
-        for (int r = 0; r < e2f::Stencil<PBC>::NR; ++r)
-            for (int base = st.lo[r]; base < st.hi[r]; base += 64) {
-                const int j = base + lane;
-                bool ok = false;
-                int aj = 0;
-                unsigned long long key = ~0ull;
-                if (j < st.hi[r] && j != t) {
-                    aj = cv.perm[j];
-                    float xj, yj, zj;
-                    atom_position<PBC>(pos, aj, g, xj, yj, zj);
-                    const float d2 = e2f::dist2_exact(xi, yi, zi, xj + st.shift_x(r), yj + st.shift_y(r),
-                                                      zj + st.shift_z(r));
-                    ok = e2f::is_neighbor(d2, rc2);
-                    key = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)aj;
-                }
-                f(ok, key, aj);
+        for (int base = 0; base < candidates; base += 64) {
+            bool ok = false;
+            int aj = 0;
+            unsigned long long key = ~0ull;
+            if (base + lane < candidates) {
+                int run, j;
+                s_run.candidate(base + lane, run, j);
+                const float4 sh = s_run.sh[run];
+                aj = cv.perm[j];
+                float xj, yj, zj;
+                atom_position<PBC>(pos, aj, g, xj, yj, zj);
+                const float d2 = e2f::dist2_exact(xi, yi, zi, xj + sh.x, yj + sh.y, zj + sh.z);
+                ok = j != t && e2f::is_neighbor(d2, rc2);
+                key = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)aj;
             }
+            f(ok, key, aj);
+        }
     };
     // first walk: count the neighbours and keep their keys in LDS while they fit (they do in any physical system)
     constexpr int KEEP = 512;
@@ -351,7 +495,29 @@ __global__ __launch_bounds__(64) void k_select_neighbors(E2fCellsView cv, const 
         }
     };
     unsigned long long thr = ~0ull;   // no cap needed: every neighbour passes
-    if (total > K) {
+    if (total > K && total <= 256) {
+        // the key with K - 1 smaller ones, counted against all of them (keys are unique): a pass over the list costs a
+        // fraction of one digit of the radix select (capped forward at 50 000 atoms 1 308 -> 1 295 us)
+        unsigned long long mine[4];
+        int below[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            mine[u] = lane + 64 * u < total ? s_key[lane + 64 * u] : ~0ull;
+            below[u] = 0;
+        }
+#pragma unroll 4
+        for (int x = 0; x < total; ++x) {
+            const unsigned long long key = s_key[x];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (64 * u < total) below[u] += key < mine[u] ? 1 : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned long long mask = __ballot(lane + 64 * u < total && below[u] == K - 1);
+            if (mask) thr = __shfl(mine[u], __builtin_ctzll(mask));
+        }
+    } else if (total > K) {
         unsigned long long prefix = 0ull;
         int want = K;   // rank (1-based) of the key looked for among the keys that share the prefix
         for (int shift = 56; shift >= 0; shift -= 8) {
@@ -414,13 +580,22 @@ e2f_status e2f_launch_build_cells(const e2f_ctx* ctx, e2f_cells* c, const float*
     if (N == 0) return E2F_OK;
     const int tb = 256;
     int32_t* cell_start = const_cast<int32_t*>(c->view.cell_start);
+    const float edge = e2f_cell_edge(ctx->cfg.cutoff);
+    const size_t small_lds = ((size_t)6 * S + S + 1 + c->max_cells + 1 + N) * 4 + (size_t)S * sizeof(E2fSegGrid);
+    if (N <= SMALL_N && S <= SMALL_S && small_lds <= 60 * 1024) {
+        k_cells_small<<<1, 1024, small_lds, st>>>(pos, seg_offsets, N, S, c->max_cells, edge, c->view.periodic ? c->box : nullptr,
+                                                 const_cast<E2fSegGrid*>(c->view.grid), cell_start, const_cast<int32_t*>(c->view.perm),
+                                                 const_cast<int32_t*>(c->view.scell), const_cast<int32_t*>(c->view.sseg),
+                                                 const_cast<int32_t*>(c->view.atom_slot), const_cast<int4*>(c->view.sinfo));
+        E2F_HIP_CHECK(hipGetLastError());
+        return E2F_OK;
+    }
     const int n_init = c->max_cells + 1 > S * 6 ? c->max_cells + 1 : S * 6;
     k_cells_init<<<(n_init + tb - 1) / tb, tb, 0, st>>>(c->bbox, S, cell_start, c->cell_fill, c->max_cells);
     k_cells_bbox<<<(N + 1023) / 1024, 1024, 0, st>>>(pos, seg_offsets, N, S, c->atom_seg, c->bbox);
     // edge a hair above the cutoff: the binary32 predicate can accept a pair whose exact |dx| exceeds the
     // cutoff by rounding, and cell coordinates carry rounding of their own
-    k_cells_grid<<<1, 1024, 0, st>>>(c->bbox, seg_offsets, S, e2f_cell_edge(ctx->cfg.cutoff),
-                                     c->view.periodic ? c->box : nullptr, const_cast<E2fSegGrid*>(c->view.grid));
+    k_cells_grid<<<1, 1024, 0, st>>>(c->bbox, seg_offsets, S, edge, c->view.periodic ? c->box : nullptr, const_cast<E2fSegGrid*>(c->view.grid));
     k_cells_assign<<<(N + tb - 1) / tb, tb, 0, st>>>(pos, c->atom_seg, c->view.grid, N, c->atom_cell, c->atom_sub, cell_start + 1);
     k_cells_scan<<<1, 1024, 0, st>>>(cell_start, c->view.grid, S);
     k_cells_scatter<<<(N + tb - 1) / tb, tb, 0, st>>>(c->atom_cell, cell_start, N, c->cell_fill, c->tmp_slot);
