@@ -119,10 +119,10 @@ def test_limits_and_empty_input(torch_cuda):
 
 
 @pytest.mark.parametrize("L,C,H,B", [
-    (1, 16, 1, 1),       # one head for a workgroup of four waves; one radial function
-    (2, 48, 3, 5),       # an idle wave; value rows with a single component left over (9 = 8 + 1)
+    (1, 32, 2, 1),       # two waves of four without a head; value rows of one half block (4 components); one radial function
+    (2, 64, 4, 5),       # value rows with a single component left over (9 = 8 + 1)
     (3, 64, 4, 16),      # value rows of whole blocks (16 components), 16 radial functions
-    (4, 192, 12, 8),     # three groups of heads; the projection without a weight-stationary kernel
+    (4, 256, 16, 8),     # four groups of heads
     (4, 128, 8, 8),
 ])
 def test_matrix_core_kernel_at_its_edges(torch_cuda, L, C, H, B):
