@@ -80,7 +80,7 @@ constexpr float LOG2E = 1.44269504088896341f, LN2 = 0.69314718055994531f;
 // ---- relayout: q rows -> grouped layout, q and k -> four slots of a feature per lane (bf16)
 // One workgroup per group of four sorted slots, thread = (head, feature).
 template <int L>
-__global__ __launch_bounds__(256) void k_bwd_relayout_qk(BwdTileParams P) {
+__device__ __forceinline__ void relayout_qk(const BwdTileParams& P) {
     constexpr int DK = (L + 1) * 16, KS = (DK + 31) / 32, DKP = KS * 32;
     const int grp = blockIdx.x, N = P.cv.N, H = P.H;
     for (int it = threadIdx.x; it < H * DKP; it += 256) {
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void k_bwd_relayout_qk(BwdTileParams P) {
 // ---- relayout: value blocks (four slots of a (component, channel) together) -> rows of (component, channel)
 // One workgroup per group of four sorted slots, thread = (head, component, 8 channels): 16-byte stores.
 template <int L>
-__global__ __launch_bounds__(256) void k_bwd_relayout_v(BwdTileParams P) {
+__device__ __forceinline__ void relayout_v(const BwdTileParams& P) {
     constexpr int n = (L + 1) * (L + 1), VK = n * 16, VS = (VK + 31) / 32, VKP = VS * 32;
     __shared__ int s_off[n];
     if ((int)threadIdx.x < n) s_off[threadIdx.x] = e2f::v4_offset(n, threadIdx.x, 0) | (e2f::v4_role(n, threadIdx.x) == 0 ? 0 : 1 << 30);
@@ -139,15 +139,19 @@ __global__ __launch_bounds__(256) void k_bwd_relayout_v(BwdTileParams P) {
     }
 }
 
-// ---- relayout: dL/d out (caller's order, fp32) -> bf16 rows and bf16 value-block layout in sorted order
+// ---- relayout: dL/d out (caller's order, fp32) -> bf16 rows and bf16 value-block layout in sorted order, and
+// D_i = <g_i, out_i> per head (g is here in full lines; the statistics kernel read g and out a second time for it, in
+// pieces of one head: 107 + 108 us with the relayouts at 9 973 atoms, 62 + 139 this way).
 // One workgroup per group of four sorted slots, thread = (component, 8 channels).
 template <int L>
-__global__ __launch_bounds__(256) void k_bwd_relayout_g(BwdTileParams P) {
+__device__ __forceinline__ void relayout_g(const BwdTileParams& P) {
     constexpr int n = (L + 1) * (L + 1), VK = n * 16, VS = (VK + 31) / 32, VKP = VS * 32;
     __shared__ int s_off[n];
     if ((int)threadIdx.x < n) s_off[threadIdx.x] = e2f::v4_offset(n, threadIdx.x, 0) | (e2f::v4_role(n, threadIdx.x) == 0 ? 0 : 1 << 30);
     __syncthreads();
     const int grp = blockIdx.x, H = P.H, C = P.C, N = P.cv.N;
+    __shared__ float s_part[4][256];
+    float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     int atom[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) atom[s] = 4 * grp + s < N ? P.cv.perm[4 * grp + s] : -1;
@@ -163,6 +167,10 @@ __global__ __launch_bounds__(256) void k_bwd_relayout_g(BwdTileParams P) {
                 v[s][j] = atom[s] >= 0 ? lo[j] : 0.0f;
                 v[s][4 + j] = atom[s] >= 0 ? hi[j] : 0.0f;
             }
+            const float* osrc = P.out + ((size_t)max(atom[s], 0) * n + x) * C + c;
+            const f32x4 olo = *reinterpret_cast<const f32x4*>(osrc), ohi = *reinterpret_cast<const f32x4*>(osrc + 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[s] += lo[j] * olo[j] + hi[j] * ohi[j];
         }
         const int o = s_off[x], cs = (o >> 30) ? 8 : 4;
         uint16_t* d4 = P.g4 + ((size_t)grp * H + head) * n * 64 + (o & 0xffffff) + ch * cs;
@@ -175,12 +183,31 @@ __global__ __launch_bounds__(256) void k_bwd_relayout_g(BwdTileParams P) {
             *reinterpret_cast<u32x4*>(P.grow + base + 32 * s) = (u32x4){pack_bf16(v[s][0], v[s][1]), pack_bf16(v[s][2], v[s][3]),
                                                                        pack_bf16(v[s][4], v[s][5]), pack_bf16(v[s][6], v[s][7])};
     }
+    // D: a thread's pieces all have its channels (256 is a multiple of the C / 8 pieces of a row), so a head's sum is that of
+    // its two pieces' threads, in a fixed order
+#pragma unroll
+    for (int s = 0; s < 4; ++s) s_part[s][threadIdx.x] = part[s];
+    __syncthreads();
+    if ((int)threadIdx.x < 4 * H) {
+        const int s = threadIdx.x & 3, head = threadIdx.x >> 2, pieces = C / 8;
+        float d = 0.0f;
+        for (int u = 0; u < 256; u += pieces) d += s_part[s][u + 2 * head] + s_part[s][u + 2 * head + 1];
+        if (4 * grp + s < N) P.stat4[((size_t)grp * H + head) * 4 + s].y = d;
+    }
     if (VK < VKP) {   // the rows' padding must be finite: it meets zeros of the other operand
         for (int it = threadIdx.x; it < H * 4 * (VKP - VK); it += 256) {
             const int head = it / (4 * (VKP - VK)), s = (it / (VKP - VK)) % 4, kk = VK + it % (VKP - VK);
             P.grow[e2f::k16_offset(4 * (size_t)grp + s, H, head, VKP, kk)] = 0;
         }
     }
+}
+
+// The three relayouts in one launch (grid: groups x 3), the one that moves most first.
+template <int L>
+__global__ __launch_bounds__(256) void k_bwd_relayout(BwdTileParams P) {
+    if (blockIdx.y == 0) relayout_g<L>(P);
+    else if (blockIdx.y == 1) relayout_v<L>(P);
+    else relayout_qk<L>(P);
 }
 
 // The tile's candidate list (entries, pair masks, slot positions) into LDS; what lies behind the list reads as groups
@@ -228,31 +255,28 @@ __device__ __forceinline__ void bias_coefficients(const BwdTileParams& P, int la
     for (int b = 0; b < NB; ++b) cb[b] = read_lane(t, b);
 }
 
-// ---- softmax statistics: lse_i (base-2 units, reference included) and D_i = <g_i, out_i>, per head
+// ---- softmax statistics: lse_i (base-2 units, reference included) per head; D_i beside it comes from the relayout of g
 template <int L, int NB>
 __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
-    constexpr int NW = 4, n = (L + 1) * (L + 1);
+    constexpr int NW = 4;
     constexpr int DK = (L + 1) * 16, KS = (DK + 31) / 32, DKP = KS * 32;
     static_assert(16 * (DKP / 8) <= 256, "one request per thread");
     __shared__ int s_ent[LENT];
     __shared__ unsigned long long s_mask[LENT];
     __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_q[16 * DKP];
-    __shared__ float s_m[NW][16], s_zz[NW][16], s_D[16];
+    __shared__ float s_m[NW][16], s_zz[NW][16];
     const int HG = P.H / P.hpw;
     int tile, hg;
     if (!tile_xcd_remap(blockIdx.x, P.n_tiles, P.blk, HG, tile, hg)) return;   // whole workgroup
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, tn = lane & 15, g = lane >> 4;
-    const int N = P.cv.N, H = P.H, C = P.C;
+    const int N = P.cv.N, H = P.H;
     const int t0 = tile * 16, tslot = min(t0 + tn, N - 1);
     const float4 tp = P.spos[tslot];
     const int cnt = load_list(P, tile, tid, tp, s_ent, s_mask, s_pos);
     if (cnt < 0) return;   // (whole workgroup) a crowded tile: done by the per-atom kernels
     const int nch = (cnt + 7) >> 3;
     const float c_u = 2.0f * P.rbf_gamma * P.rbf_step * LOG2E, c_g = -P.rbf_gamma * LOG2E;
-    // the atom whose D this thread helps to form: thread = (tile atom, channel of the head)
-    const int dt = tid >> 4, dch = tid & 15;
-    const int datom = t0 + dt < N ? P.cv.perm[t0 + dt] : -1;
     for (int hh = 0; hh < P.hpw; ++hh) {
         const int head = hg * P.hpw + hh;
         if (tid < 16 * (DKP / 8)) {
@@ -262,14 +286,6 @@ __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
         }
         float cb[NB];
         bias_coefficients(P, lane, lane < P.B ? P.WbT[lane * H + head] : 0.0f, cb);
-        // <g, out> of this thread's (atom, channel): requested here, summed after the streaming loop
-        float dg[n], dout[n];
-#pragma unroll
-        for (int x = 0; x < n; ++x) {
-            const size_t o = ((size_t)max(datom, 0) * n + x) * C + head * 16 + dch;
-            dg[x] = P.gout[o];
-            dout[x] = P.out[o];
-        }
         f16x8 kf[2][KS];
         auto load_K = [&](int c) {
 #pragma unroll
@@ -327,14 +343,6 @@ __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
             s_m[wave][lane] = m;
             s_zz[wave][lane] = z;
         }
-        {
-            float dsum = 0.0f;
-#pragma unroll
-            for (int x = 0; x < n; ++x) dsum += dg[x] * dout[x];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) dsum += __shfl_xor(dsum, off);
-            if (dch == 0) s_D[dt] = datom >= 0 ? dsum : 0.0f;
-        }
         __syncthreads();
         if (tid < 16 && t0 + tid < N) {
             float mm = s_m[0][tid], zz = s_zz[0][tid];
@@ -345,9 +353,9 @@ __global__ __launch_bounds__(256) void k_bwd_tile_stats(BwdTileParams P) {
                 mm = mn;
             }
             const int slot = t0 + tid;
-            P.stat4[((size_t)(slot >> 2) * H + head) * 4 + (slot & 3)] = make_float2(zz > 0.0f ? mm + __log2f(zz) : 0.0f, s_D[tid]);
+            P.stat4[((size_t)(slot >> 2) * H + head) * 4 + (slot & 3)].x = zz > 0.0f ? mm + __log2f(zz) : 0.0f;
         }
-        __syncthreads();   // the next head reuses s_q, s_D and the partials
+        __syncthreads();   // the next head reuses s_q and the partials
     }
 }
 
@@ -1011,9 +1019,7 @@ void launch_L(const BwdTileParams& P, bool wgrad, hipStream_t st) {
     BwdTileParams Ps = P;
     Ps.blk = P.blk < TILE_BLK_MANY ? P.blk : TILE_BLK_MANY;
     const int grid_s = tile_grid(P.n_tiles, Ps.blk, HG);
-    k_bwd_relayout_qk<L><<<groups, 256, 0, st>>>(P);
-    k_bwd_relayout_v<L><<<groups, 256, 0, st>>>(P);
-    k_bwd_relayout_g<L><<<groups, 256, 0, st>>>(P);
+    k_bwd_relayout<L><<<dim3(groups, 3), 256, 0, st>>>(P);
     if (P.B > 8) {   // (the radial bias polynomial has its coefficients in registers: instances for B <= 8 and B <= 16)
         k_bwd_tile_stats<L, 16><<<grid_s, 256, 0, st>>>(Ps);
         k_bwd_tile_pairs<L, false, 16, false><<<grid, 256, 0, st>>>(P);
