@@ -312,22 +312,6 @@ __host__ __device__ __forceinline__ int v4_role(int n, int x) {
     return 1 + ((local - odd) & 1);
 }
 
-// Value rows of the non-linear logit's matrix-core kernel: per (slot, head) n * 16 bf16 in blocks of eight components,
-// [16 channels][8], then the n % 8 components left over as [16 channels][n % 8].  Element i of a slot's row holds
-// component x of channel ch of a head.
-__host__ __device__ __forceinline__ void nl_element(int n, int i, int& head, int& x, int& ch) {
-    head = i / (n * 16);
-    const int in = i - head * (n * 16), o = in >> 7, full = n >> 3;
-    if (o < full) {
-        x = o * 8 + (in & 7);
-        ch = (in & 127) >> 3;
-    } else {
-        const int rem = n & 7, tail = in - full * 128;
-        x = full * 8 + tail % rem;
-        ch = tail / rem;
-    }
-}
-
 // Sums of K values over groups of `lanes` neighbouring lanes (a power of two, at most 64; the same in every lane of the
 // wave), in every lane of the group.  Inside a row of 16 lanes the partners are reached by cross-lane operands of the
 // additions instead of shuffles through the LDS unit: exchanges at distance 1 and 2, then the mirrored half row and the

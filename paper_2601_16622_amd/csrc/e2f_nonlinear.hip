@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Neither loses bits: the 32-bit operand (harmonics, weights) is cut into three 8-bit significands that lie side by side
 // along the product's unused rows (3 axes x 3 parts of 16) or its unused depth (3 x (2l+1) <= 27 of 32); the other
 // operand is bf16 in memory.  A wave takes 16 pairs at a time, lane = (channel, 4 pairs).
-// Value rows: e2f::nl_element, so that a lane fetches 8 components of its channel with one 16-byte load.
+// Value rows as k_nonlinear_rows leaves them, so that a lane fetches 8 components of its channel with one 16-byte load.
 // Measured at 4 000 atoms, L = 4, 128 channels, 60 neighbours: whole call 1 250 us with the kernel above (1 084 in it), 571
 // with this one; 256 registers, two waves per SIMD, the value rows of one group of 16 pairs in flight.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -481,29 +481,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// Value rows from the plain layout [component][channel] into e2f::nl_element's, in place: a workgroup reads its slot's
-// row whole before it writes it.
-__global__ __launch_bounds__(256) void k_nonlinear_rows(uint16_t* v, int n, int C) {
-    extern __shared__ uint16_t s_row[];
+// Value rows from the plain layout [component][channel] into the one that k_nonlinear_heads reads, in place: per head n * 16
+// bf16 in blocks of eight components, [16 channels][8], then the n % 8 components left over as [16 channels][n % 8].  A
+// workgroup reads its slot's row whole before it writes it.
+template <int L>
+__global__ __launch_bounds__(256) void k_nonlinear_rows(uint16_t* v, int C) {
+    constexpr int n = (L + 1) * (L + 1), OCT = n / 8, REM = n % 8;
+    extern __shared__ __attribute__((aligned(16))) uint16_t s_row[];
     uint16_t* row = v + (size_t)blockIdx.x * n * C;
     for (int i = threadIdx.x; i < n * C / 8; i += 256)
         reinterpret_cast<u32x4*>(s_row)[i] = reinterpret_cast<const u32x4*>(row)[i];
     __syncthreads();
-    for (int i = threadIdx.x; i < n * C / 2; i += 256) {
-        uint32_t two[2];
+    if constexpr (OCT > 0)
+        for (int i = threadIdx.x; i < C * OCT; i += 256) {   // (head, block, channel)
+            const int ch = i & 15, head = (i >> 4) / OCT, o = (i >> 4) % OCT;
+            const uint16_t* src = s_row + 8 * o * C + head * 16 + ch;
+            u32x4 w;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            int head, x, ch;
-            e2f::nl_element(n, 2 * i + u, head, x, ch);
-            two[u] = s_row[x * C + head * 16 + ch];
+            for (int u = 0; u < 4; ++u) w[u] = src[2 * u * C] | ((uint32_t)src[(2 * u + 1) * C] << 16);
+            *reinterpret_cast<u32x4*>(row + head * (n * 16) + o * 128 + ch * 8) = w;
         }
-        reinterpret_cast<uint32_t*>(row)[i] = two[0] | (two[1] << 16);
-    }
+    if constexpr (REM > 0)
+        for (int i = threadIdx.x; i < C; i += 256)
+#pragma unroll
+            for (int u = 0; u < REM; ++u)
+                row[(i >> 4) * (n * 16) + OCT * 128 + (i & 15) * REM + u] = s_row[(8 * OCT + u) * C + i];
 }
 
 template <int L>
 void launch_heads(const e2f_ctx* ctx, const NlParams& P, const float* w_path, hipStream_t st) {
-    k_nonlinear_rows<<<P.cv.N, 256, (size_t)ctx->n * P.C * 2, st>>>((uint16_t*)P.v, ctx->n, P.C);
+    k_nonlinear_rows<L><<<P.cv.N, 256, (size_t)ctx->n * P.C * 2, st>>>((uint16_t*)P.v, P.C);
     k_nonlinear_heads<L><<<tile_grid(P.cv.N, e2f::XCD_CHUNK, (P.H + 3) / 4), 256, 0, st>>>(P, w_path, axis_table(ctx));
 }
 

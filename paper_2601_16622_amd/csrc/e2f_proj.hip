@@ -927,8 +927,8 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
         return false;
     } else {
         // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order), and for one
-        // channel tile so that two waves fit a SIMD (a wave alone waits for every weight tile it loads: fp32, 128 channels,
-        // five orders in 366 registers 60 us at 2 240 atoms, L = 2; three orders in 208 registers take 8 us off the call)
+        // channel tile so that two waves fit a SIMD (fp32, 128 channels: five orders take 366 registers, three 208; the same
+        // 60 us at 2 240 atoms, L = 2, where the matrix instructions alone are 21, without the spills of the four-tile form)
         constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 3 : 2));
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
