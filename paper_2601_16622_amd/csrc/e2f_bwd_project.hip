@@ -27,6 +27,33 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to 
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
 }
 
+// Four 32-bit factors as bf16 operands.  PARTS = 1: rounded.  PARTS = 3: cut into three parts of 8 significant bits, which
+// together are the factor (infinities and NaN sit in the first part alone, so that the sum over the parts keeps them).
+template <int PARTS>
+__device__ __forceinline__ void split_bf16(f32x4 t, u32x2 (&part)[PARTS]) {
+    if constexpr (PARTS == 1) {
+        part[0] = (u32x2){pack_bf16(t[0], t[1]), pack_bf16(t[2], t[3])};
+    } else {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            const u32x4 b = __builtin_bit_cast(u32x4, t);
+            part[p] = (u32x2){__builtin_amdgcn_perm(b[1], b[0], 0x07060302u), __builtin_amdgcn_perm(b[3], b[2], 0x07060302u)};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float r = t[x] - __uint_as_float(b[x] & 0xffff0000u);
+                t[x] = r == r ? r : 0.0f;
+            }
+        }
+    }
+}
+// Parts of a row factor as an operand.  fp32 features: one, the factor itself.  bf16 features: at 256 channels three, the
+// whole 32 bits; up to 128 channels one for dL/dh (the counterpart of the forward pass rounding the projected values
+// to bf16: 1.6e-3 of the norm of dL/dh, where three leave the rounding of the sums) and two for the weights' gradients.
+template <typename T, int CP>
+constexpr int H_PARTS = sizeof(T) == 2 && CP > 128 ? 3 : 1;
+template <typename T, int CP>
+constexpr int W_PARTS = sizeof(T) == 4 ? 1 : CP > 128 ? 3 : 2;
+
 // The matrix operands of a feature type.  A fragment is 16 bytes of one row per lane: EPF elements of the contraction
 // index.  Which index an element stands for is free as long as both operands agree; a half-wave (32-row tiles) or a
 // quarter-wave (16-row tiles) takes the next EPF elements of the row, so that a lane's load is contiguous.
@@ -84,8 +111,7 @@ struct DegreeMap {
 };
 
 // ---- dL/dh.  A workgroup owns 32 RT rows of one degree and all channels: the rows x stay in LDS, and for each of the
-// five maps the factors t_k = (dq or dk) (W x) go through LDS as one more operand of the same shape (bf16 features: rounded to
-// bf16, the counterpart of the forward pass rounding the projected values).  Wave w owns 32 output channels of the first
+// five maps the factors t_k = (dq or dk) (W x) go through LDS as H_PARTS more operands of the same shape.  Wave w owns 32 output channels of the first
 // product, written with the channels as rows, so that a lane holds four consecutive channels of its row (16-byte loads of
 // dq and dk, 8- or 16-byte stores to LDS), and the same 32 input channels of the second one, written with the data rows as
 // rows, so that a store of the result covers whole 128-byte lines.  The weights are read once per workgroup, by
@@ -94,21 +120,21 @@ struct DegreeMap {
 // Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
 // the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
 // kernels before (one thread per channel on the vector ALUs; at 128 bf16 channels weights held in registers, one
-// degree's slabs per workgroup) in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4 x 256: 189 us
-// (2 818), x 128 with weight gradients: 66 us (150).
+// degree's slabs per workgroup) in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4 x 128 with
+// weight gradients: 66 us (150), x 256: 349 us (2 818; one bf16 a factor would take 189 us, at the loss stated at H_PARTS).
 // CP: channels padded up to a multiple of 32 (PAD: C < CP; the missing ones read as zero).
 template <typename T, int CP, int RT, bool PAD>
 __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_rows(
     const T* __restrict__ h, MapWeights<T> mw, const T* __restrict__ WT, const float* __restrict__ gq,
     const float* __restrict__ gk, const float* __restrict__ gv, float* __restrict__ gh, int L, int C_, int N,
     DegreeMap map) {
-    constexpr int EPF = Mat<T>::EPF, ROWS = 32 * RT, THREADS = 2 * CP;
+    constexpr int EPF = Mat<T>::EPF, ROWS = 32 * RT, THREADS = 2 * CP, PARTS = H_PARTS<T, CP>;
     constexpr int ROW = CP + EPF;              // LDS row pitch: 16 bytes of padding against bank conflicts
     constexpr int NF = CP / (2 * EPF);         // fragments of a whole contraction
     constexpr int CF = NF < 8 ? NF : 8;        // fragments per chunk
     constexpr int CPS = NF / CF;               // chunks per product
     static_assert(NF % CF == 0, "whole chunks");
-    __shared__ __attribute__((aligned(16))) T s_X[ROWS * ROW], s_T[ROWS * ROW];
+    __shared__ __attribute__((aligned(16))) T s_X[ROWS * ROW], s_T[PARTS * ROWS * ROW];
     __shared__ __attribute__((aligned(16))) int s_row[ROWS];   // row -> atom * n + component
     __shared__ int s_inv[ROWS];                                // row -> atom * (L + 1) + degree
     const int C = PAD ? C_ : CP;
@@ -138,6 +164,16 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
             dst[f] = (!PAD || (row < C && col < C)) ? *reinterpret_cast<const u32x4*>(base + (size_t)row * C + col) : (u32x4){0u, 0u, 0u, 0u};
         }
     };
+    auto store_factor = [&](int at, f32x4 t) {   // four channels of a row
+        if constexpr (EPF == 8) {
+            u32x2 part[PARTS];
+            split_bf16<PARTS>(t, part);
+#pragma unroll
+            for (int p = 0; p < PARTS; ++p) *reinterpret_cast<u32x2*>(s_T + p * ROWS * ROW + at) = part[p];
+        } else {
+            *reinterpret_cast<f32x4*>(s_T + at) = t;
+        }
+    };
     load_chunk(0, buf[0]);
     {   // x and dv of the unit's rows
         constexpr int PX = ROWS * CP / EPF / THREADS;   // 16-byte pieces of x per thread
@@ -152,8 +188,7 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
         for (int j = 0; j < PV; ++j) {
             const int e = tid + THREADS * j, rr = e / (CP / 4), c = 4 * (e % (CP / 4));
             const f32x4 v = (!PAD || c < C) ? *reinterpret_cast<const f32x4*>(gv + (size_t)s_row[rr] * C + c) : (f32x4){0.f, 0.f, 0.f, 0.f};
-            if constexpr (EPF == 8) *reinterpret_cast<u32x2*>(s_T + rr * ROW + c) = (u32x2){pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-            else *reinterpret_cast<f32x4*>(s_T + rr * ROW + c) = v;
+            store_factor(rr * ROW + c, v);
         }
     }
     f32x16 dx[RT];
@@ -173,7 +208,10 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
                 for (int f = 0; f < CF; ++f)
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) dx[rt] = Mat<T>::mma32(frag(s_T, rt, c * CF + f), buf[q & 1][f], dx[rt]);
+                    for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+                            dx[rt] = Mat<T>::mma32(frag(s_T + p * ROWS * ROW, rt, c * CF + f), buf[q & 1][f], dx[rt]);
             }
         } else {   // p[channel][row] of the map, then t
             f32x16 p[RT];
@@ -193,13 +231,12 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 const float* grow = g + (size_t)s_inv[32 * rt + i] * C + 32 * w + 4 * hf;
-                T* trow = s_T + (32 * rt + i) * ROW + 32 * w + 4 * hf;
+                const int at = (32 * rt + i) * ROW + 32 * w + 4 * hf;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {   // channels 32 w + 8 j + 4 hf + 0 .. 3
                     const f32x4 gg = (!PAD || 32 * w + 8 * j < C) ? *reinterpret_cast<const f32x4*>(grow + 8 * j) : (f32x4){0.f, 0.f, 0.f, 0.f};
                     const f32x4 t = {gg[0] * p[rt][4 * j], gg[1] * p[rt][4 * j + 1], gg[2] * p[rt][4 * j + 2], gg[3] * p[rt][4 * j + 3]};
-                    if constexpr (EPF == 8) *reinterpret_cast<u32x2*>(trow + 8 * j) = (u32x2){pack_bf16(t[0], t[1]), pack_bf16(t[2], t[3])};
-                    else *reinterpret_cast<f32x4*>(trow + 8 * j) = t;
+                    store_factor(at + 8 * j, t);
                 }
             }
             __syncthreads();
@@ -224,8 +261,7 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 // eight waves), with all input channels; it walks its rows 64 at a time.  The rows x of a step are shared by the waves
 // through LDS; a wave forms the products p of its own channels with the weights in registers, written with the data rows as
 // rows, which leaves the factors t in the register layout that the second product wants as its A operand (contraction
-// over the data rows), so they never leave the wave.  bf16 features: the factors as two bf16 (leading part and
-// remainder, 16 significant bits), and a second copy of x turned in LDS, with the eight rows that a lane takes of one
+// over the data rows), so they never leave the wave.  bf16 features: the factors as W_PARTS bf16, and a second copy of x turned in LDS, with the eight rows that a lane takes of one
 // channel side by side.  fp32 features: the rows of x as they are (a lane takes one row of 16 channels per step of the
 // fp32 instruction).  One map per workgroup: two (sharing dq or dk and the rows of x) take 200 registers, which
 // leaves one workgroup per CU and a half-empty second round of them (bf16 98 us, fp32 154 us).
@@ -237,7 +273,7 @@ template <typename T, int CP, int NW, bool PAD>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CP <= 128 ? 4 : 2))) void k_bwd_wgrad(
     const T* __restrict__ h, MapWeights<T> mw, const float* __restrict__ gq, const float* __restrict__ gk,
     const float* __restrict__ gv, int L, int C_, int N, int split, float* __restrict__ part) {
-    constexpr int EPF = Mat<T>::EPF, THREADS = 64 * NW;
+    constexpr int EPF = Mat<T>::EPF, THREADS = 64 * NW, PARTS = W_PARTS<T, CP>;
     constexpr bool BF = EPF == 8;
     constexpr int ROW = CP + EPF, TROW = WSTEP + 8;
     constexpr int NF = CP / (4 * EPF);      // fragments of a contraction over the channels
@@ -347,21 +383,32 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CP <= 1
         if constexpr (BF) {
 #pragma unroll
             for (int P = 0; P < WSTEP / 32; ++P) {
-                u32x4 hi, lo;
+                u32x4 part[PARTS];
 #pragma unroll
                 for (int S = 0; S < 2; ++S) {
                     const f32x4 t = factors(2 * P + S);
+                    if constexpr (PARTS == 3) {
+                        u32x2 p[3];
+                        split_bf16<3>(t, p);
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) {
-                        const uint32_t v = pack_bf16(t[2 * x], t[2 * x + 1]);
-                        hi[2 * S + x] = v;
-                        lo[2 * S + x] = pack_bf16(t[2 * x] - __uint_as_float(v << 16), t[2 * x + 1] - __uint_as_float(v & 0xffff0000u));
+                        for (int u = 0; u < 3; ++u) {
+                            part[u][2 * S] = p[u][0];
+                            part[u][2 * S + 1] = p[u][1];
+                        }
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) {
+                            const uint32_t v = pack_bf16(t[2 * x], t[2 * x + 1]);
+                            part[0][2 * S + x] = v;
+                            part[1][2 * S + x] = pack_bf16(t[2 * x] - __uint_as_float(v << 16), t[2 * x + 1] - __uint_as_float(v & 0xffff0000u));
+                        }
                     }
                 }
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     const u32x4 X = *reinterpret_cast<const u32x4*>(s_Xt + (16 * ct + i) * TROW + 8 * ((4 * P + g) ^ ((4 * ct + (i >> 2)) & 7)));
-                    acc[ct] = Mat<T>::mma16(lo, X, Mat<T>::mma16(hi, X, acc[ct]));
+#pragma unroll
+                    for (int u = 0; u < PARTS; ++u) acc[ct] = Mat<T>::mma16(part[u], X, acc[ct]);
                 }
             }
         } else {
@@ -414,8 +461,9 @@ void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const
     if (gh) {
         const int t16 = C / 16;
         k_transpose_weights<T><<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
-        // Rows per workgroup: 128 (bf16) or 64 (fp32) while that leaves two workgroups per CU, else half of it
-        constexpr int RT = sizeof(T) == 2 ? 4 : 2;
+        // Rows per workgroup: 128 (one bf16 a factor) or 64 (32 bits) while that leaves two workgroups per CU, else half of it
+        // (256 channels, 4 000 atoms: 64 rows 349 us, 32 rows 473 us; the weights pass through every workgroup)
+        constexpr int RT = sizeof(T) == 2 && H_PARTS<T, CP> == 1 ? 4 : 2;
         const bool wide = (long long)N * (L + 1) * (L + 1) >= 512ll * 32 * RT;
         if (wide) launch_rows<T, CP, RT, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
         else launch_rows<T, CP, RT / 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);

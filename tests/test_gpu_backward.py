@@ -241,6 +241,50 @@ def test_backward_through_the_maps(torch_cuda, dtype, L, C, H, N):
         P.close()
 
 
+def chain_rule(P, gq, gk, gv):
+    """(dL/dh, gradients of the five projection matrices) from dL/dq, dL/dk, dL/dv, in float64."""
+    import torch
+    L, C, N = P.cfg["L"], P.cfg["C"], P.N
+    h = P.h.double()
+    Wd = [P.weights[k].double() for k in ("WQ1", "WQ2", "WK1", "WK2", "WV")]
+    gh, gW = torch.zeros_like(h), torch.zeros((5, L + 1, C, C), dtype=torch.float64, device=h.device)
+    for l in range(L + 1):
+        x = h[:, l * l:(l + 1) ** 2].reshape(-1, C)
+        p = [x @ w[l].T for w in Wd[:4]]
+        dq, dk = (t[:, l:l + 1].double().expand(N, 2 * l + 1, C).reshape(-1, C) for t in (gq, gk))
+        t = [dq * p[1], dq * p[0], dk * p[3], dk * p[2], gv[:, l * l:(l + 1) ** 2].double().reshape(-1, C)]
+        gh[:, l * l:(l + 1) ** 2] = sum(a @ w[l] for a, w in zip(t, Wd)).reshape(N, 2 * l + 1, C)
+        for k in range(5):
+            gW[k, l] = t[k].T @ x
+    return gh, gW
+
+
+@pytest.mark.parametrize("L,H,N", [(1, 16, 3), (3, 16, 100), (2, 4, 75), (4, 16, 1400)])
+def test_backward_through_the_maps_at_256_channels_keeps_32_bits(torch_cuda, L, H, N):
+    """bf16 features at 256 channels: the row factors keep all their 32 bits, so what is left is the rounding of fp32 sums
+    (dL/dh: 5 x 256 products in two levels, 2^-24 sqrt(1280 / 2) = 1.5e-6 if every addition rounded on its own; the
+    weights: rows of a slice 32 at a time, below 2^-24 sqrt(64)).  One bf16 per factor would show 1.6e-3, two 2.4e-6.
+    Both unit sizes (64 rows from 512 units on)."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    rng = np.random.default_rng(N)
+    cfg = dict(L=L, C=256, H=H, B=4, lf=1, cutoff=2.5, dtype="bf16")
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        _, gq, gk, gv, gh, _, _, gW = P.backward(g, with_weights=True)
+        torch.cuda.synchronize()
+        for got, ref, tol in zip((gh, gW), chain_rule(P, gq, gk, gv), (1.5e-6, 5e-7)):
+            err = float((got.double() - ref).norm() / ref.norm().clamp(min=1e-30))
+            assert err <= tol, (err, tol)
+    finally:
+        P.close()
+
+
 def test_backward_rejects_what_it_does_not_cover(torch_cuda):
     from paper_2601_16622_amd import binding as B
     wl = custom(30, (60,), 2, 32, 2, 4, "f32", 3.5, 7.0)
