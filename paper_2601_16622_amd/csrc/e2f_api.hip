@@ -1,5 +1,4 @@
 // C ABI of libe2f.so: argument checks, workspace layout, and the sequence of launches per entry point.
-#include <algorithm>
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -615,19 +614,15 @@ static E2fBwdWs bwd_ws_layout(const e2f_ctx* ctx, int32_t N, void* ws, size_t at
     Bw.lse = (float*)take((size_t)N * ctx->cfg.H * 4);
     Bw.Dn = (float*)take((size_t)N * ctx->cfg.H * 4);
     Bw.G = (float*)take((size_t)3 * E2F_MAX_N * E2F_MAX_N * 4);
-    take((size_t)E2F_MAX_N * E2F_NP * 4);   // (unused: the documented size stays)
     Bw.Gu = (float*)take((size_t)3 * E2F_MAX_N * E2F_MAX_N * 4);
     Bw.pWb = (float*)take((size_t)N * ctx->cfg.H * ctx->cfg.B * 4);
     Bw.pwp = (float*)take((size_t)N * 32 * 4);
     const size_t C = ctx->cfg.C, L1 = ctx->cfg.L_max + 1;
-    Bw.wT = take((size_t)5 * L1 * C * C * (ctx->cfg.feat_dtype == E2F_BF16 ? 2 : 4));
+    Bw.wT = ctx->cfg.feat_dtype == E2F_BF16 ? (uint16_t*)take((size_t)5 * L1 * C * C * 2) : nullptr;
     Bw.wpart = nullptr;
-    if (with_W) {
-        // the partial sums need e2f_wgrad_split(L_max) (L_max+1)^2 slices; the call's documented size (five row arrays and
-        // 8 (L_max+1)^2 slices, which an older form of the sums filled) stays what it was
-        take((size_t)5 * N * ctx->n * C * 4);
-        Bw.wpart = (float*)take((size_t)std::max(8, e2f_wgrad_split(ctx->cfg.L_max)) * L1 * L1 * 5 * C * C * 4);
-    }
+    // The size that include/e2f.h states, five [N][n][C] arrays and 8 (L_max+1)^2 slices, so that a buffer of that size
+    // stays large enough; the partial sums take what they need of it (e2f_wgrad_split), the rest is not touched.
+    if (with_W) Bw.wpart = (float*)take(e2f_align_up((size_t)5 * N * ctx->n * C * 4) + (size_t)8 * L1 * L1 * 5 * C * C * 4);
     Bw.bytes = off;
     return Bw;
 }
@@ -638,7 +633,6 @@ static bool backward_in_tile_form(const e2f_ctx* ctx, bool wgrad) {
     return ctx->use_tile_attn && (!wgrad || e2f_backward_tile_weight_gradients_supported(ctx));
 }
 
-// Never less than the forward pass wants, so that a training step can run both in the one workspace.
 static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_W) {
     size_t bytes = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 0).bytes, with_W).bytes;
     if (backward_in_tile_form(ctx, false)) {   // either form may run, depending on the gradients asked for
@@ -646,8 +640,7 @@ static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_
         const size_t b3 = e2f_bwd_tile_ws_layout(ctx, N, nullptr, b2).bytes;
         if (b3 > bytes) bytes = b3;
     }
-    const size_t fwd = e2f_attn_workspace_bytes(ctx, N);
-    return bytes > fwd ? bytes : fwd;
+    return bytes;
 }
 
 size_t e2f_attn_backward_workspace_bytes(const e2f_ctx* ctx, int32_t N) {

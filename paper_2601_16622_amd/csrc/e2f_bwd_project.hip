@@ -91,14 +91,13 @@ struct MapWeights {
     const T* W[5];   // WQ1, WQ2, WK1, WK2, WV: [L+1][C out][C in]
 };
 
-// WT[k][l][ci][co] = W_k[l][co][ci], so that the transposed products read their weights by rows too; one workgroup
-// per (k, l, 16 x 16 tile).
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_weights(MapWeights<T> mw, int L1, int C, T* __restrict__ WT) {
-    __shared__ T s[16][17];
+// WT[k][l][ci][co] = W_k[l][co][ci], so that the transposed products of bf16 features read their weights by rows too (a
+// fragment is eight of them); one workgroup per (k, l, 16 x 16 tile).
+__global__ __launch_bounds__(256) void k_transpose_weights(MapWeights<uint16_t> mw, int L1, int C, uint16_t* __restrict__ WT) {
+    __shared__ uint16_t s[16][17];
     const int tiles = C / 16, t = blockIdx.x % (tiles * tiles), kl = blockIdx.x / (tiles * tiles);
     const int k = kl / L1, l = kl % L1, tr = t / tiles, tc = t % tiles;
-    const T* W = k == 0 ? mw.W[0] : k == 1 ? mw.W[1] : k == 2 ? mw.W[2] : k == 3 ? mw.W[3] : mw.W[4];
+    const uint16_t* W = k == 0 ? mw.W[0] : k == 1 ? mw.W[1] : k == 2 ? mw.W[2] : k == 3 ? mw.W[3] : mw.W[4];
     const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     s[r][c] = W[((size_t)l * C + 16 * tr + r) * C + 16 * tc + c];
     __syncthreads();
@@ -116,7 +115,7 @@ struct DegreeMap {
 // dq and dk, 8- or 16-byte stores to LDS), and the same 32 input channels of the second one, written with the data rows as
 // rows, so that a store of the result covers whole 128-byte lines.  The weights are read once per workgroup, by
 // fragments straight into registers, eight of them (one chunk) ahead of the products: they stay in the L2s (five 128-channel
-// degrees are 1.5 MB with their transposes), and no channel count is too wide for the registers.
+// degrees are 0.8 MB, 1.5 with the transposes that bf16 features read), and no channel count is too wide for the registers.
 // Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
 // the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
 // kernels before (one thread per channel on the vector ALUs; at 128 bf16 channels weights held in registers, one
@@ -155,12 +154,19 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
     u32x4 buf[2][CF];
     auto load_chunk = [&](int q, u32x4 (&dst)[CF]) {   // q: chunk of the whole sequence
         const int st = q / CPS, c = q % CPS;
-        // stage 0: WT[4]; stage 1 + 2k: the map whose product enters t_k (1, 0, 3, 2); stage 2 + 2k: WT[k]
-        const T* base = st == 0 ? WT + 4 * kstride + wl : (st & 1) ? mw.W[((st - 1) / 2) ^ 1] + wl : WT + ((st - 2) / 2) * kstride + wl;
-        const int row = 32 * w + i;
+        // stage 0: map 4 transposed; stage 1 + 2k: the map whose product enters t_k (1, 0, 3, 2); stage 2 + 2k: map k transposed
+        const int kt = st == 0 ? 4 : (st - 2) / 2, row = 32 * w + i;
+        const bool transposed = !(st & 1);
+        const T* base = !transposed ? mw.W[((st - 1) / 2) ^ 1] + wl : EPF == 8 ? WT + kt * kstride + wl : mw.W[kt] + wl;
 #pragma unroll
         for (int f = 0; f < CF; ++f) {
             const int col = (c * CF + f) * 2 * EPF + EPF * hf;
+            if (EPF == 4 && transposed) {   // fp32: the four elements one by one, 32 lanes side by side, no copy needed
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    dst[f][x] = (!PAD || (row < C && col < C)) ? __float_as_uint((float)base[(size_t)(col + x) * C + row]) : 0u;
+                continue;
+            }
             dst[f] = (!PAD || (row < C && col < C)) ? *reinterpret_cast<const u32x4*>(base + (size_t)row * C + col) : (u32x4){0u, 0u, 0u, 0u};
         }
     };
@@ -459,8 +465,10 @@ template <typename T, int CP, bool PAD>
 void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const float* gk, const float* gv, float* gh,
               float* grad_W, float* part, int L, int C, int N, hipStream_t st) {
     if (gh) {
-        const int t16 = C / 16;
-        k_transpose_weights<T><<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
+        if constexpr (sizeof(T) == 2) {
+            const int t16 = C / 16;
+            k_transpose_weights<<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
+        }
         // Rows per workgroup: 128 (one bf16 a factor) or 64 (32 bits) while that leaves two workgroups per CU, else half of it
         // (256 channels, 4 000 atoms: 64 rows 349 us, 32 rows 473 us; the weights pass through every workgroup)
         constexpr int RT = sizeof(T) == 2 && H_PARTS<T, CP> == 1 ? 4 : 2;
@@ -470,7 +478,7 @@ void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const
     }
     if (grad_W) {
         constexpr int NW = CP / 16 < 8 ? CP / 16 : 8;
-        const int split = e2f_wgrad_split(L);
+        const int split = e2f_wgrad_split(L, C, N);
         const dim3 grid(split * (L + 1) * (L + 1), 5 * (CP / 16 / NW));
         k_bwd_wgrad<T, CP, NW, PAD><<<grid, 64 * NW, 0, st>>>(h, mw, gq, gk, gv, L, C, N, split, part);
         const size_t M = (size_t)5 * (L + 1) * C * C;

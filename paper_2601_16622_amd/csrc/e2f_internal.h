@@ -120,9 +120,9 @@ struct E2fBwdWs {
     float* Gu;       // [3][25][25]
     float* pWb;      // [N][H][B]
     float* pwp;      // [N][32]
-    void* wT;        // [5][L+1][C in][C out] the projection matrices transposed, feature type
+    uint16_t* wT;    // [5][L+1][C in][C out] the projection matrices transposed (bf16 features; null for fp32)
     // for the gradients of the projection matrices (only in the larger workspace of that form of the call)
-    float* wpart;    // [e2f_wgrad_split(L) (L+1)^2 slices][5][C][C] partial sums
+    float* wpart;    // [e2f_wgrad_split(L, C, N) (L+1)^2 slices][5][C][C] partial sums
     size_t bytes;
 };
 
@@ -150,8 +150,12 @@ struct E2fFactWs {
 };
 
 // Slices of rows per component in the sums of the projection matrices' gradients: about 100 slices in all, five maps
-// each, which is one round of two workgroups per CU.
-static inline int e2f_wgrad_split(int L) { return (100 + (L + 1) * (L + 1) / 2) / ((L + 1) * (L + 1)); }
+// each, which is one round of two workgroups per CU; no more than the room in the workspace, which is that of 8
+// slices and of five [N][(L+1)^2][C] arrays: split (L+1)^2 C^2 <= 8 (L+1)^2 C^2 + N (L+1)^2 C.
+static inline int e2f_wgrad_split(int L, int C, int N) {
+    const int want = (100 + (L + 1) * (L + 1) / 2) / ((L + 1) * (L + 1)), room = 8 + N / C;
+    return want < room ? want : room;
+}
 
 static inline size_t e2f_align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 // Cell edge: a hair above the cutoff, since the binary32 predicate can accept a pair whose exact |dx| exceeds the

@@ -226,6 +226,22 @@ def test_backward_entry_point_sizes_and_limits(lib):
             B.e2f_destroy(ctx)
 
 
+@pytest.mark.parametrize("L,C,H,dtype,N,plain,weights", [
+    (1, 16, 2, "f32", 1, 18688, 183808), (1, 256, 16, "f32", 17, 170240, 42461440),
+    (2, 128, 8, "f32", 2240, 18259200, 93461760), (1, 32, 2, "bf16", 100, 355328, 1266688),
+    (4, 128, 8, "bf16", 10000, 355903488, 1061439488),
+])
+def test_backward_workspaces_do_not_grow(lib, L, C, H, dtype, N, plain, weights):
+    """Sizes that programs may have stored or allocated once: a buffer of them stays large enough (few atoms at a low
+    degree, where the slices of partial sums outweigh the arrays, and fp32 features among them)."""
+    ctx = B.e2f_create(L, C, H, 8, 1, 5.0, dtype)
+    try:
+        assert B.e2f_attn_backward_workspace_bytes(ctx, N) <= plain
+        assert B.e2f_attn_backward_weights_workspace_bytes(ctx, N) <= weights
+    finally:
+        B.e2f_destroy(ctx)
+
+
 def test_cap_and_table_entry_points_reject_bad_arguments(lib):
     ctx = B.e2f_create(1, 16, 2, 8, 1, 5.0, "f32")
     try:

@@ -285,6 +285,39 @@ def test_backward_through_the_maps_at_256_channels_keeps_32_bits(torch_cuda, L, 
         P.close()
 
 
+@pytest.mark.parametrize("dtype,L,C,H,N", [
+    ("f32", 1, 16, 2, 1), ("f32", 1, 256, 16, 3), ("f32", 2, 128, 8, 40), ("bf16", 1, 32, 2, 2), ("bf16", 1, 32, 2, 500),
+    ("f32", 1, 16, 2, 300), ("bf16", 2, 256, 16, 20), ("bf16", 4, 64, 4, 33),
+])
+def test_backward_stays_inside_its_workspace(torch_cuda, dtype, L, C, H, N):
+    """A workspace of exactly the size asked for, inside a larger buffer: the bytes around it are untouched, and the gradients
+    of the projection matrices (whose partial sums lie last, in slices whose number depends on the room) agree with
+    the chain rule in float64 to the bounds of the test above."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    rng = np.random.default_rng(N + L)
+    cfg = dict(L=L, C=C, H=H, B=4, lf=1, cutoff=2.5, dtype=dtype)
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        for with_weights in (False, True):
+            need = (B.e2f_attn_backward_weights_workspace_bytes if with_weights else B.e2f_attn_backward_workspace_bytes)(P.ctx, N)
+            around = torch.full((4096 + need + 4096,), 0xA5, dtype=torch.uint8, device=P.device)
+            P.bwd_ws = around[4096:4096 + need]
+            got = P.backward(g, with_weights=with_weights)
+            torch.cuda.synchronize()
+            assert bool((around[:4096] == 0xA5).all()) and bool((around[4096 + need:] == 0xA5).all())
+        ref_h, ref_W = chain_rule(P, *got[1:4])
+        for x, ref, tol in ((got[4], ref_h, 1e-5 if dtype == "f32" else 4e-3), (got[7], ref_W, 1e-5 if dtype == "f32" else 5e-5)):
+            assert float((x.double() - ref).norm()) <= tol * max(float(ref.norm()), 1e-30)
+    finally:
+        P.close()
+
+
 def test_backward_rejects_what_it_does_not_cover(torch_cuda):
     from paper_2601_16622_amd import binding as B
     wl = custom(30, (60,), 2, 32, 2, 4, "f32", 3.5, 7.0)
