@@ -294,6 +294,7 @@ e2f_status e2f_attn_forward_factorized(e2f_ctx *ctx, const e2f_cells *cells, con
  *             (larger by five [N][(L_max+1)^2][C] float arrays and 8 (L_max+1)^2 [5][C][C] ones, room for partial sums of
  *             the result)
  *   ws        device, at least e2f_attn_backward_workspace_bytes(ctx, N) bytes, 256-byte aligned
+ * grad_out and the gradients may start at any float (a view into a larger buffer); out, like h, is 16-byte aligned.
  * Cell lists from e2f_build_cells and e2f_build_cells_periodic are accepted.  E2F_ERR_UNSUPPORTED: lf != 1, or a
  * head width C/H that is not a power of two <= 64.  Where the forward pass runs on the bf16 TILE kernel the pair work of
  * this call runs in the same form on the matrix cores (with grad_Wb / grad_w_path only for B <= 8; beyond that, and for

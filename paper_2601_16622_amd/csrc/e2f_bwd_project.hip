@@ -193,7 +193,7 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
         for (int j = 0; j < PV; ++j) {
             const int e = tid + THREADS * j, rr = e / (CP / 4), c = 4 * (e % (CP / 4));
-            const f32x4 v = (!PAD || c < C) ? *reinterpret_cast<const f32x4*>(gv + (size_t)s_row[rr] * C + c) : (f32x4){0.f, 0.f, 0.f, 0.f};
+            const f32x4 v = (!PAD || c < C) ? *reinterpret_cast<const e2f::f32x4_unaligned*>(gv + (size_t)s_row[rr] * C + c) : (f32x4){0.f, 0.f, 0.f, 0.f};
             store_factor(rr * ROW + c, v);
         }
     }
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
                 const int at = (32 * rt + i) * ROW + 32 * w + 4 * hf;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {   // channels 32 w + 8 j + 4 hf + 0 .. 3
-                    const f32x4 gg = (!PAD || 32 * w + 8 * j < C) ? *reinterpret_cast<const f32x4*>(grow + 8 * j) : (f32x4){0.f, 0.f, 0.f, 0.f};
+                    const f32x4 gg = (!PAD || 32 * w + 8 * j < C) ? *reinterpret_cast<const e2f::f32x4_unaligned*>(grow + 8 * j) : (f32x4){0.f, 0.f, 0.f, 0.f};
                     const f32x4 t = {gg[0] * p[rt][4 * j], gg[1] * p[rt][4 * j + 1], gg[2] * p[rt][4 * j + 2], gg[3] * p[rt][4 * j + 3]};
                     store_factor(at + 8 * j, t);
                 }
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(64) void k_sum_slices(const float* __restrict__ par
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
     for (int c = 0; c < m; ++c) s += *reinterpret_cast<const f32x4*>(p + (size_t)c * 5 * CC);
-    *reinterpret_cast<f32x4*>(out + e4) = s;
+    *reinterpret_cast<e2f::f32x4_unaligned*>(out + e4) = s;
 }
 
 template <typename T, int CP, int RT, bool PAD>

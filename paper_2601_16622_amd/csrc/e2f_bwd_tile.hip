@@ -161,7 +161,7 @@ __device__ __forceinline__ void relayout_g(const BwdTileParams& P) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const float* src = P.gout + ((size_t)max(atom[s], 0) * n + x) * C + c;
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(src), hi = *reinterpret_cast<const f32x4*>(src + 4);
+            const f32x4 lo = *reinterpret_cast<const e2f::f32x4_unaligned*>(src), hi = *reinterpret_cast<const e2f::f32x4_unaligned*>(src + 4);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 v[s][j] = atom[s] >= 0 ? lo[j] : 0.0f;

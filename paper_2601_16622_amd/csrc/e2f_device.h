@@ -342,6 +342,10 @@ __device__ __forceinline__ void group_sums(float (&x)[K], int lanes) {
         for (int i = 0; i < K; ++i) x[i] += __shfl_xor(x[i], 32);
 }
 
+// Four floats of a buffer whose caller promises no more than a float's alignment (the gradients of the backward pass):
+// still one 16-byte access, which global memory allows at every multiple of 4 bytes.
+typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {  // round to nearest even
     uint32_t u = __float_as_uint(f);

@@ -318,6 +318,37 @@ def test_backward_stays_inside_its_workspace(torch_cuda, dtype, L, C, H, N):
         P.close()
 
 
+@pytest.mark.parametrize("dtype,C,H", [("f32", 32, 2), ("f32", 48, 3), ("bf16", 64, 4), ("bf16", 64, 1), ("bf16", 256, 16)])
+def test_backward_with_gradient_buffers_at_any_float(torch_cuda, dtype, C, H):
+    """dL/d out and all gradients as views 4, 8 or 12 bytes into larger buffers: the same bits, and nothing written beside
+    the views."""
+    from paper_2601_16622_amd import binding as B
+    torch = torch_cuda
+    L, N = 2, 67
+    P = B.Problem(custom(31, (N,), L, C, H, 4, dtype, 3.5, 9.0))
+    try:
+        P.build_cells()
+        P.forward()
+        shapes = [(N, 9, C), (N, 3), (N, L + 1, C), (N, L + 1, C), (N, 9, C), (N, 9, C), (H, 4), (L + 1, L + 1), (5, L + 1, C, C)]
+        g = torch.randn(shapes[0], generator=torch.Generator().manual_seed(1)).to(P.device)
+        want = P.backward(g, with_weights=True)
+        bufs, views = [], []
+        for i, shape in enumerate(shapes):
+            size, at = int(np.prod(shape)), 64 + 1 + i % 3
+            bufs.append(torch.full((size + 128,), 7.0, device=P.device))
+            views.append(bufs[-1][at:at + size].view(shape))
+        views[0].copy_(g)
+        B.e2f_attn_backward(P.ctx, P.cells, P.pos, P.h, P.seg, P.weights, P.out, views[0], *views[1:6], P.bwd_ws, *views[6:])
+        torch.cuda.synchronize()
+        for x, y in zip(want, views[1:]):
+            assert y.data_ptr() % 16 and torch.equal(x, y)
+        for b, v in zip(bufs, views):
+            v.fill_(7.0)
+            assert bool((b == 7.0).all())
+    finally:
+        P.close()
+
+
 def test_backward_rejects_what_it_does_not_cover(torch_cuda):
     from paper_2601_16622_amd import binding as B
     wl = custom(30, (60,), 2, 32, 2, 4, "f32", 3.5, 7.0)
