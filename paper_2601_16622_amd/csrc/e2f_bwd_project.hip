@@ -118,9 +118,9 @@ struct DegreeMap {
 // degrees are 0.8 MB, 1.5 with the transposes that bf16 features read), and no channel count is too wide for the registers.
 // Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
 // the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
-// kernels before (one thread per channel on the vector ALUs; at 128 bf16 channels weights held in registers, one
-// degree's slabs per workgroup) in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4 x 128 with
-// weight gradients: 66 us (150), x 256: 349 us (2 818; one bf16 a factor would take 189 us, at the loss stated at H_PARTS).
+// one-thread-per-channel kernel on the vector ALUs in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4
+// x 256: 349 us (2 818; one bf16 a factor would take 189 us, at the loss stated at H_PARTS).  Up to 128 bf16 channels it
+// has the smaller calls, see k_bwd_rows_stationary.
 // CP: channels padded up to a multiple of 32 (PAD: C < CP; the missing ones read as zero).
 template <typename T, int CP, int RT, bool PAD>
 __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_rows(
@@ -261,6 +261,192 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
             for (int r = 0; r < 4; ++r)
                 if (r0 + rr + r < rows) gh[(size_t)ats[r] * C + ci] = dx[rt][4 * j + r];
         }
+}
+
+// ---- dL/dh for many rows, bf16 features and up to 128 channels: the weights stay.  A workgroup owns one degree and
+// a few consecutive tiles of 16 atoms and walks their (tile, order) slabs with one load of its weights, in registers;
+// wave ct owns output channels 16 ct .. 16 ct + 15 of the forward products and the same input channels of the transposed
+// ones.  Both products are written with the channels as rows and the atoms as columns, (W x)^T = W X^T and
+// dX^T = sum_k W_k^T T_k^T, so that the weights are the A operand, a lane ends up with four consecutive channels
+// of one atom (16-byte loads of dq, dk, dv and 16-byte stores of the result) and the row factors t_k cross the waves
+// through LDS as [atom][channel] rows, rounded to bf16 as in k_bwd_rows.  The feature rows of a slab are fetched once per
+// workgroup and shared through LDS as well.
+// It takes a call from STATIONARY_WORK row elements on: a load of the weights is shared by more rows the more rows there are, and
+// below that its workgroups do not fill the chip.  Measured, us, this kernel / k_bwd_rows with 64 rows a workgroup: 128
+// channels, L = 4: 1 000 atoms 38 / 31, 1 500 39 / 42, 2 000 40 / 59, 3 000 43 / 83 (62 with 128 rows), 4 000 79 / 106 (80),
+// 6 000 86 / 152 (101), 9 000 130 / 219 (139); 64 channels, L = 3: 2 000 atoms 20 / 13, 4 000 21 / 21, 6 000 25 / 28, 9 000 30 / 45
+// (43); 32 channels, L = 1: 9 000 atoms 12 / 8, 20 000 14 / 12, 40 000 18 / 19.
+constexpr long long STATIONARY_WORK = 1ll << 22;
+constexpr int ROWS_SLABS = 18;   // slabs a workgroup walks with one load of its weights
+// Workgroups [first[d], first[d + 1]) own degree L - d (the highest degree, with the most slabs per tile, first) and
+// tiles[d] consecutive tiles of 16 atoms each, so that every workgroup walks about the same number of slabs.
+struct SlabMap {
+    int first[E2F_MAX_L + 2];
+    int tiles[E2F_MAX_L + 1];
+};
+
+template <int C>
+__global__ __launch_bounds__(64 * (C / 16)) void k_bwd_rows_stationary(
+    const uint16_t* __restrict__ h, MapWeights<uint16_t> mw, const uint16_t* __restrict__ WT, const float* __restrict__ gq,
+    const float* __restrict__ gk, const float* __restrict__ gv, float* __restrict__ gh, int L, int N, SlabMap map) {
+    constexpr int NS = C / 32, ROW = C + 8;   // LDS rows of 16 atoms, 16 bytes of padding against bank conflicts
+    constexpr int PD = 3;                     // slabs in flight from memory
+    // Two buffers each, used in turn.  In one pass of the loop a wave runs the second stage of slab s (reads s_T[s & 1]),
+    // the first stage of slab s + 1 (reads s_X[(s + 1) & 1], writes s_T[(s + 1) & 1]) and stores the feature rows of
+    // slab s + 2 (s_X[s & 1]): the two stages of consecutive slabs overlap inside a wave and one barrier per slab is enough.
+    __shared__ __attribute__((aligned(16))) uint16_t s_T[2][5][16][ROW];
+    __shared__ __attribute__((aligned(16))) uint16_t s_X[2][16][ROW];
+    // (the wave's index through readfirstlane, so that the compiler knows it to be the same in all lanes)
+    const int tid = threadIdx.x, ct = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i = lane & 15, g = lane >> 4;
+    const int n_tiles = (N + 15) / 16, n = (L + 1) * (L + 1);
+    int d = 0;
+    while (d < L && (int)blockIdx.x >= map.first[d + 1]) ++d;
+    const int l = L - d, nl = 2 * l + 1;
+    const int tile0 = ((int)blockIdx.x - map.first[d]) * map.tiles[d];
+    const int n_slabs = (min(n_tiles, tile0 + map.tiles[d]) - tile0) * nl;   // slab s: tile tile0 + s / nl, order s % nl
+    if (n_slabs <= 0) return;
+    const int ch0 = 16 * ct + 4 * g;   // the four channels this lane holds of its atom
+    auto frag = [](const uint16_t* p) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p)); };
+    bf16x8 W1[4][NS], W2[5][NS];
+    {
+        const size_t row = ((size_t)l * C + 16 * ct + i) * C + 8 * g;
+        const size_t lstride = (size_t)(L + 1) * C * C;
+#pragma unroll
+        for (int S = 0; S < NS; ++S) {
+            W1[0][S] = frag(mw.W[0] + row + 32 * S);
+            W1[1][S] = frag(mw.W[1] + row + 32 * S);
+            W1[2][S] = frag(mw.W[2] + row + 32 * S);
+            W1[3][S] = frag(mw.W[3] + row + 32 * S);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) W2[k][S] = frag(WT + k * lstride + row + 32 * S);
+        }
+    }
+    // What is read of a slab.  The feature rows of its 16 atoms, shared by the waves: thread tid fetches four channels
+    // (xa, xc) of one row, which reach the waves through s_X.  dv for the lane's own atom and channels.  Both are
+    // requested PD slabs before their use, in rings of registers indexed at compile time; dq and dk of a tile (lane's
+    // atom and channels again) are requested when the tile before it starts.
+    const int xa = tid / (C / 4), xc = 4 * (tid % (C / 4));
+    // the four places where the sequence of slabs is walked (requests of x and of dv, first stage, second stage)
+    // each keep (first atom of the tile, order); a cursor stays on the last slab once it gets there
+    struct Cursor {
+        int a0, m;
+    };
+    const int a_last = (tile0 + n_slabs / nl - 1) * 16;
+    auto advance = [&](Cursor& c) {
+        if (c.m + 1 < nl) {
+            ++c.m;
+        } else if (c.a0 < a_last) {
+            c.m = 0;
+            c.a0 += 16;
+        }
+    };
+    Cursor cx = {tile0 * 16, 0}, cv = cx, cf = cx, co = cx;
+    auto fetch_x = [&]() {
+        const u32x2 v = *reinterpret_cast<const u32x2*>(h + ((size_t)min(cx.a0 + xa, N - 1) * n + l * l + cx.m) * C + xc);
+        advance(cx);
+        return v;
+    };
+    auto fetch_dv = [&]() {
+        const f32x4 v = *reinterpret_cast<const e2f::f32x4_unaligned*>(gv + ((size_t)min(cv.a0 + i, N - 1) * n + l * l + cv.m) * C + ch0);
+        advance(cv);
+        return v;
+    };
+    auto fetch_dqk = [&](int a0, f32x4& dq, f32x4& dk) {
+        const size_t at = ((size_t)min(a0 + i, N - 1) * (L + 1) + l) * C + ch0;
+        dq = *reinterpret_cast<const e2f::f32x4_unaligned*>(gq + at);
+        dk = *reinterpret_cast<const e2f::f32x4_unaligned*>(gk + at);
+    };
+    auto store_x = [&](int s, u32x2 v) { *reinterpret_cast<u32x2*>(&s_X[s & 1][xa][xc]) = v; };
+    f32x4 dq, dk, dq_next, dk_next;
+    // first stage of slab s: the four forward products of the slab's rows, then the five row factors
+    // t = (dq (WQ2 x), dq (WQ1 x), dk (WK2 x), dk (WK1 x), dv), to LDS as bf16 (an absent atom's row is not stored at the end)
+    auto factors = [&](int s, f32x4 dv) {
+        if (cf.m == 0) {   // (uniform) a new tile
+            dq = dq_next;
+            dk = dk_next;
+            fetch_dqk(cf.a0 + 16, dq_next, dk_next);
+        }
+        advance(cf);
+        f32x4 p[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int S = 0; S < NS; ++S) {
+            const bf16x8 X = frag(&s_X[s & 1][i][32 * S + 8 * g]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1[k][S], X, p[k], 0, 0, 0);
+        }
+        // p[k][r] = (W_k x)[channel 16 ct + 4 g + r] of atom i
+        f32x4 t[5];
+        t[0] = dq * p[1];
+        t[1] = dq * p[0];
+        t[2] = dk * p[3];
+        t[3] = dk * p[2];
+        t[4] = dv;
+        const int buf = s & 1;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            *reinterpret_cast<u32x2*>(&s_T[buf][k][i][ch0]) = (u32x2){pack_bf16(t[k][0], t[k][1]), pack_bf16(t[k][2], t[k][3])};
+        }
+    };
+    // ring slot of slab s: s % PD.  Before pass s of the loop the rings hold x of slabs s + 2 .. s + 4 and dv of
+    // slabs s + 1 .. s + 3; s_X holds x of slabs s and s + 1 and s_T the factors of slab s.
+    u32x2 xr[PD];
+    f32x4 dvr[PD];
+    fetch_dqk(tile0 * 16, dq_next, dk_next);
+    store_x(0, fetch_x());
+    store_x(1, fetch_x());
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+        xr[(u + 2) % PD] = fetch_x();
+        dvr[u] = fetch_dv();
+    }
+    __syncthreads();
+    factors(0, dvr[0]);
+    dvr[0] = fetch_dv();
+    __syncthreads();
+    // One pass of the loop, for slab s = s0 + u with ring slots known at compile time.  (LAST: a pass of the last,
+    // partial group, which checks whether its slab and the next exist.  The passes of the full groups have no such
+    // branches: the compiler places its waits on the loads by the least number of memory instructions on any path
+    // from a request to its use, and a path that skips passes would make it wait for requests one pass old.)
+    auto pass = [&](int s, int u, bool LAST) __attribute__((always_inline)) {
+        // The first stage of the next slab and the second stage of this one are independent.
+        auto first_stage = [&]() {
+            // the feature rows of slab s + 2 have arrived: into the buffer that slab s used
+            store_x(s + 2, xr[(u + 2) % PD]);
+            xr[(u + 2) % PD] = fetch_x();
+            if (!LAST || s + 1 < n_slabs) factors(s + 1, dvr[(u + 1) % PD]);
+            dvr[(u + 1) % PD] = fetch_dv();
+        };
+        auto second_stage = [&]() {
+            const int buf = s & 1;
+            // (two partial sums: one accumulator would chain all the matrix instructions one after the other)
+            f32x4 dp[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int k = 0; k < 5; ++k)
+#pragma unroll
+                for (int S = 0; S < NS; ++S) {
+                    const int j = (k * NS + S) & 1;
+                    dp[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[k][S], frag(&s_T[buf][k][i][32 * S + 8 * g]), dp[j], 0, 0, 0);
+                }
+            const f32x4 dx = dp[0] + dp[1];
+            // dx[r] = dL/dh[atom i][component][channel 16 ct + 4 g + r]
+            const int atom = co.a0 + i;
+            if (atom < N) *reinterpret_cast<e2f::f32x4_unaligned*>(gh + ((size_t)atom * n + l * l + co.m) * C + ch0) = dx;
+            advance(co);
+        };
+        first_stage();
+        second_stage();
+        __syncthreads();
+    };
+    int s0 = 0;
+    for (; s0 + PD < n_slabs; s0 += PD) {
+#pragma unroll
+        for (int u = 0; u < PD; ++u) pass(s0 + u, u, false);
+    }
+#pragma unroll
+    for (int u = 0; u < PD; ++u)
+        if (s0 + u < n_slabs) pass(s0 + u, u, true);   // (uniform)
 }
 
 // ---- dL/dW.  A workgroup owns a slice of a degree's rows, one of the five maps and 16 output channels per wave (up to
@@ -461,6 +647,20 @@ void launch_rows(const MapWeights<T>& mw, const T* WT, const T* h, const float* 
     k_bwd_rows<T, CP, RT, PAD><<<map.first[L + 1], 2 * CP, 0, st>>>(h, mw, WT, gq, gk, gv, gh, L, C, N, map);
 }
 
+template <int C>
+void launch_rows_stationary(const MapWeights<uint16_t>& mw, const uint16_t* WT, const uint16_t* h, const float* gq, const float* gk,
+                            const float* gv, float* gh, int L, int N, hipStream_t st) {
+    const int tiles = (N + 15) / 16;
+    SlabMap map;
+    map.first[0] = 0;
+    for (int d = 0; d <= L; ++d) {
+        const int nl = 2 * (L - d) + 1;
+        map.tiles[d] = (ROWS_SLABS + nl - 1) / nl;
+        map.first[d + 1] = map.first[d] + (tiles + map.tiles[d] - 1) / map.tiles[d];
+    }
+    k_bwd_rows_stationary<C><<<map.first[L + 1], 64 * (C / 16), 0, st>>>(h, mw, WT, gq, gk, gv, gh, L, N, map);
+}
+
 template <typename T, int CP, bool PAD>
 void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const float* gk, const float* gv, float* gh,
               float* grad_W, float* part, int L, int C, int N, hipStream_t st) {
@@ -469,12 +669,16 @@ void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const
             const int t16 = C / 16;
             k_transpose_weights<<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
         }
-        // Rows per workgroup: 128 (one bf16 a factor) or 64 (32 bits) while that leaves two workgroups per CU, else half of it
-        // (256 channels, 4 000 atoms: 64 rows 349 us, 32 rows 473 us; the weights pass through every workgroup)
-        constexpr int RT = sizeof(T) == 2 && H_PARTS<T, CP> == 1 ? 4 : 2;
-        const bool wide = (long long)N * (L + 1) * (L + 1) >= 512ll * 32 * RT;
-        if (wide) launch_rows<T, CP, RT, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
-        else launch_rows<T, CP, RT / 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+        const long long rows = (long long)N * (L + 1) * (L + 1);
+        if constexpr (sizeof(T) == 2 && CP <= 128) {
+            if (rows * C >= STATIONARY_WORK) launch_rows_stationary<CP>(mw, WT, h, gq, gk, gv, gh, L, N, st);
+            else launch_rows<T, CP, 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+        } else {
+            // 64 rows a workgroup while that leaves two workgroups per CU, else 32 (256 bf16 channels, 4 000 atoms: 64 rows
+            // 349 us, 32 rows 473 us; the weights pass through every workgroup)
+            if (rows >= 512 * 64) launch_rows<T, CP, 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+            else launch_rows<T, CP, 1, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
+        }
     }
     if (grad_W) {
         constexpr int NW = CP / 16 < 8 ? CP / 16 : 8;

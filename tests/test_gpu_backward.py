@@ -259,6 +259,36 @@ def chain_rule(P, gq, gk, gv):
     return gh, gW
 
 
+@pytest.mark.parametrize("L,C,N", [(4, 128, 1310), (4, 128, 1311), (4, 128, 3001), (2, 64, 7281), (2, 64, 7282), (3, 64, 4096),
+                                   (1, 32, 32767), (1, 32, 32769)])
+def test_backward_through_the_maps_beside_the_change_of_kernel(torch_cuda, L, C, N):
+    """dL/dh up to 128 bf16 channels on both sides of 2^22 row elements, N (L + 1)^2 C, where the kernel with the weights in
+    registers takes over, and with a last tile of one atom: every row factor rounded to one bf16 by either (rms 1.1e-3 to
+    1.65e-3 of the result), row by row, and the same with and without the weights' gradients."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    rng = np.random.default_rng(N)
+    cfg = dict(L=L, C=C, H=C // 16, B=4, lf=1, cutoff=2.0, dtype="bf16")
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        plain = P.backward(g)
+        got = P.backward(g, with_weights=True)
+        torch.cuda.synchronize()
+        ref, _ = chain_rule(P, *plain[1:4])
+        rows, scale = (plain[4].double() - ref).flatten(0, 1).norm(dim=1), ref.flatten(0, 1).norm(dim=1)
+        assert float(rows.norm()) <= 2.5e-3 * float(scale.norm())
+        assert float(rows.max()) <= 2.5e-2 * float(scale.max())
+        other, _ = chain_rule(P, *got[1:4])
+        assert float((got[4].double() - other).norm()) <= 2.5e-3 * float(other.norm())
+    finally:
+        P.close()
+
+
 @pytest.mark.parametrize("L,H,N", [(1, 16, 3), (3, 16, 100), (2, 4, 75), (4, 16, 1400)])
 def test_backward_through_the_maps_at_256_channels_keeps_32_bits(torch_cuda, L, H, N):
     """bf16 features at 256 channels: the row factors keep all their 32 bits, so what is left is the rounding of fp32 sums
