@@ -115,15 +115,14 @@ __device__ __forceinline__ void store_run_bf16(uint16_t* row, int pos0, const fl
 // components in tile order (HI: l=4 rows 0..8, l=3 rows 9..15; LO: l=2 rows 0..4, l=1 rows 5..7, l=0 row 8,
 // rows 9..15 zero), heads of 16 channels.
 template <typename T, int C, int MG, int CT, bool TILED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && C <= (sizeof(T) == 2 ? 192 : 128) ? 2 : 1))) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
+__global__ __launch_bounds__(64) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
-                                                     float* __restrict__ k, T* __restrict__ v) {
+                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first) {
     typedef Frag<T> F;
     constexpr int NS = C / F::KSTEP;
-    // (the degrees with the most orders start first, so that the launch does not end on its longest waves)
-    const int tile = blockIdx.x, cg = blockIdx.y, l = L - (int)blockIdx.z;
+    const int tile = blockIdx.x, cg = longest_first ? blockIdx.y : blockIdx.z, l = longest_first ? L - (int)blockIdx.z : blockIdx.y;
     const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
     const int N = cv.N, n = (L + 1) * (L + 1), nl = 2 * l + 1;
     const int slot_i = min(tile * 16 + i, N - 1);            // clamped rows are computed and not stored
@@ -137,10 +136,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && C
         kacc[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     for (int m0 = 0; m0 < nl; m0 += MG) {
-        // (an offset of zero that the compiler cannot see through: the weights are the same for every pass over the
-        // orders, and it would load those of all five maps before the loop and keep them in registers)
+        // Several channel tiles: an offset of zero that the compiler cannot see through.  The weights are the same for every
+        // pass over the orders, and it would load those of all maps and tiles before the loop, into scratch memory (fp32, L = 2,
+        // 9 000 atoms, 192 channels 1 314 us with them, 388 without).  Those of one tile fit the registers and stay there
+        // (4 000 atoms, 190 us; loaded again in every pass 254).
         int fresh = 0;
-        asm volatile("" : "+s"(fresh));
+        if constexpr (CT > 1) asm volatile("" : "+s"(fresh));
         typename F::type A[MG][NS];
 #pragma unroll
         for (int mm = 0; mm < MG; ++mm) {
@@ -926,24 +927,31 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
     if constexpr (C % Frag<T>::KSTEP != 0) {
         return false;
     } else {
-        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order), and for one
-        // channel tile so that two waves fit a SIMD (fp32, 128 channels: five orders take 366 registers, three 208; the same
-        // 60 us at 2 240 atoms, L = 2, where the matrix instructions alone are 21, without the spills of the four-tile form)
-        constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 3 : 2));
+        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order).  (Three orders at
+        // 128 fp32 channels, so that two waves fit a SIMD, are no faster at 2 000 atoms, L = 2, and 240 instead of 207 us at
+        // 4 000, L = 4.)
+        constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 5 : 2));
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
         const int waves_ct = (cv.N + 15) / 16 * (ctx->cfg.L_max + 1) * (C / 16 / CT);
         auto go = [&](auto ct_tag) {
             constexpr int ct = decltype(ct_tag)::value;
-            const dim3 grid((cv.N + 15) / 16, C / 16 / ct, ctx->cfg.L_max + 1);
+            // The degrees with the most orders start first, so that the launch does not end on its longest waves (fp32, 1 000
+            // atoms: 128 channels, L = 2, 30 us against 37; 192, L = 4, 118 against 134).  From 128 channels on a SIMD holds one
+            // wave, and beyond five rounds of them the degrees are better mixed, since the short waves of the low degrees, mostly
+            // waiting for weights, would have the chip to themselves at the end (128 channels, L = 2, 9 000 atoms 203 us
+            // against 183; the four-tile form gains by the first order at every size it has).
+            const int tiles = (cv.N + 15) / 16, L1 = ctx->cfg.L_max + 1;
+            const bool longest_first = ct > 1 || C < 128 || (long long)tiles * L1 * (C / 16) <= 5 * 1024;
+            const dim3 grid = longest_first ? dim3(tiles, C / 16 / ct, L1) : dim3(tiles, L1, C / 16 / ct);
             if (tiled)
                 k_project_mfma<T, C, MG, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v);
+                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
             else
                 k_project_mfma<T, C, MG, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v);
+                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
         };
         if (CT > 1 && waves_ct < 4096)
             go(std::integral_constant<int, 1>{});
