@@ -459,12 +459,17 @@ __global__ __launch_bounds__(64) void k_select_neighbors(E2fCellsView cv, const 
             unsigned long long key = ~0ull;
             if (base + lane < candidates) {
                 int run, j;
-                s_run.candidate(base + lane, run, j);
-                const float4 sh = s_run.sh[run];
+                s_run.candidate<e2f::Stencil<PBC>::NR>(base + lane, run, j);
                 aj = cv.perm[j];
                 float xj, yj, zj;
                 atom_position<PBC>(pos, aj, g, xj, yj, zj);
-                const float d2 = e2f::dist2_exact(xi, yi, zi, xj + sh.x, yj + sh.y, zj + sh.z);
+                if constexpr (PBC) {
+                    const float4 sh = s_run.sh[run];
+                    xj += sh.x;
+                    yj += sh.y;
+                    zj += sh.z;
+                }
+                const float d2 = e2f::dist2_exact(xi, yi, zi, xj, yj, zj);
                 ok = j != t && e2f::is_neighbor(d2, rc2);
                 key = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)aj;
             }
@@ -498,25 +503,30 @@ __global__ __launch_bounds__(64) void k_select_neighbors(E2fCellsView cv, const 
     if (total > K && total <= 256) {
         // the key with K - 1 smaller ones, counted against all of them (keys are unique): a pass over the list costs a
         // fraction of one digit of the radix select (capped forward at 50 000 atoms 1 308 -> 1 295 us)
-        unsigned long long mine[4];
-        int below[4];
+        auto count_below = [&](auto parts) {   // 64 keys to a register
+            constexpr int U = decltype(parts)::value;
+            unsigned long long mine[U];
+            int below[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            mine[u] = lane + 64 * u < total ? s_key[lane + 64 * u] : ~0ull;
-            below[u] = 0;
-        }
+            for (int u = 0; u < U; ++u) {
+                mine[u] = lane + 64 * u < total ? s_key[lane + 64 * u] : ~0ull;
+                below[u] = 0;
+            }
 #pragma unroll 4
-        for (int x = 0; x < total; ++x) {
-            const unsigned long long key = s_key[x];
+            for (int x = 0; x < total; ++x) {
+                const unsigned long long key = s_key[x];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (64 * u < total) below[u] += key < mine[u] ? 1 : 0;
-        }
+                for (int u = 0; u < U; ++u) below[u] += key < mine[u] ? 1 : 0;
+            }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const unsigned long long mask = __ballot(lane + 64 * u < total && below[u] == K - 1);
-            if (mask) thr = __shfl(mine[u], __builtin_ctzll(mask));
-        }
+            for (int u = 0; u < U; ++u) {
+                const unsigned long long mask = __ballot(lane + 64 * u < total && below[u] == K - 1);
+                if (mask) thr = __shfl(mine[u], __builtin_ctzll(mask));
+            }
+        };
+        if (total <= 64) count_below(std::integral_constant<int, 1>{});
+        else if (total <= 128) count_below(std::integral_constant<int, 2>{});
+        else count_below(std::integral_constant<int, 4>{});
     } else if (total > K) {
         unsigned long long prefix = 0ull;
         int want = K;   // rank (1-based) of the key looked for among the keys that share the prefix

@@ -136,10 +136,11 @@ struct RunList {
     int lo[18], pre[19];   // first slot of a run; candidates before it
     float4 sh[18];         // lattice translation
     __device__ __forceinline__ int total() const { return pre[18]; }
+    template <int NR = 18>   // 9 under open boundaries, whose other runs are empty and come last
     __device__ __forceinline__ void candidate(int c, int& run, int& slot) const {   // c < total()
         run = 0;
 #pragma unroll
-        for (int r = 1; r < 18; ++r) run += c >= pre[r] ? 1 : 0;
+        for (int r = 1; r < NR; ++r) run += c >= pre[r] ? 1 : 0;
         slot = lo[run] + c - pre[run];
     }
 };
