@@ -95,10 +95,12 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
     // keys (the cap's test needs the candidate's atom index, which the lists in memory do not carry; the cutoff is tested
     // where the distance is needed: done here for every slot it took 7 us more per launch and gave the heads nothing).
     __shared__ unsigned long long s_mask[CAPG + PADE];
-    // the pass's targets: position and squared reach (0: not in this pass); with a cap the position as it is (at
-    // infinity: not in this pass) and the threshold keys beside it
-    __shared__ float4 s_tgt[16];
+    __shared__ float4 s_tgt[16];   // the pass's targets: where they are and how far they reach (not at all: not in this pass)
+    // with a cap, for the pair masks: the positions as they are (at infinity: not in this pass), the threshold keys, and the
+    // atom index of every listed slot
+    __shared__ float4 s_tpos[CAP ? 16 : 1];
     __shared__ int2 s_tcap[CAP ? 16 : 1];
+    __shared__ float s_atom[CAP ? CAPG * 4 : 1];
     // periodic boundaries: the pass's candidate runs (first and last slot, slot groups before the run, translation)
     constexpr int NRUN = PBC ? 27 : 9;
     __shared__ int s_rlo[32], s_rhi[32], s_rpre[32];
@@ -195,15 +197,16 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
             __syncthreads();   // every wave has finished with the previous pass's table
             if (threadIdx.x < 16) {
                 if constexpr (CAP) {
-                    s_tgt[threadIdx.x] = make_float4(t_active ? tp.x : INFINITY, tp.y, tp.z, 0.0f);
+                    s_tpos[threadIdx.x] = make_float4(t_active ? tp.x : INFINITY, tp.y, tp.z, 0.0f);
                     s_tcap[threadIdx.x] = make_int2((int)capd, capi);
-                } else {
-                    // |p - t|^2 < rc^2 as |q|^2 + q.(-2u) + (|u|^2 - rc^2) < 0 with q = p - o, u = t - o around the
-                    // tile's first target o (small numbers, so the expanded square keeps its accuracy)
-                    const float ux = tp.x - origin.x, uy = tp.y - origin.y, uz = tp.z - origin.z;
-                    s_tgt[threadIdx.x] = make_float4(-2.0f * ux, -2.0f * uy, -2.0f * uz,
-                                                     t_active ? ux * ux + uy * uy + uz * uz - P.rc2 * 1.001f : INFINITY);
                 }
+                // |p - t|^2 < reach^2 as |q|^2 + q.(-2u) + (|u|^2 - reach^2) < 0 with q = p - o, u = t - o around the
+                // tile's first target o (small numbers, so the expanded square keeps its accuracy); with a neighbour cap a
+                // target reaches no further than its threshold distance
+                const float reach2 = CAP && capd != 0xffffffffu ? fminf(P.rc2, __uint_as_float(capd)) : P.rc2;
+                const float ux = tp.x - origin.x, uy = tp.y - origin.y, uz = tp.z - origin.z;
+                s_tgt[threadIdx.x] = make_float4(-2.0f * ux, -2.0f * uy, -2.0f * uz,
+                                                 t_active ? ux * ux + uy * uy + uz * uz - reach2 * 1.001f : INFINITY);
             }
             // shape of the pass's grid from the first target's record; box lengths (periodic only) from the grid
             struct { int nx, ny, nz, base; float lx, ly, lz; } G;
@@ -270,7 +273,7 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
             int cnt = 0;
             {
             int grp[LU];
-            unsigned valid4[LU], mlo[CAP ? LU : 1], mhi[CAP ? LU : 1];   // with a cap: the pairs of targets 0..7 and 8..15
+            unsigned valid4[LU];
             bool keep[LU];
             unsigned long long leaders[LU];
             float4 pj[LU];
@@ -307,49 +310,26 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                 int mine = 0;
 #pragma unroll
                 for (int u = 0; u < LU; ++u) valid4[u] = (unsigned)(__ballot(valid[u]) >> (lane & ~3)) & 0xFu;
-                if constexpr (CAP) {
-                    // (the target itself is at distance zero, an image of it at a box length: neither passes)
+                bool nearby[LU];
+                float qx[LU], qy[LU], qz[LU], qq[LU];
 #pragma unroll
-                    for (int u = 0; u < LU; ++u) mlo[u] = mhi[u] = 0u;
+                for (int u = 0; u < LU; ++u) {
+                    nearby[u] = false;
+                    qx[u] = pj[u].x - origin.x;
+                    qy[u] = pj[u].y - origin.y;
+                    qz[u] = pj[u].z - origin.z;
+                    qq[u] = qx[u] * qx[u] + qy[u] * qy[u] + qz[u] * qz[u];
+                }
 #pragma unroll
-                    for (int tt = 0; tt < 16; ++tt) {
-                        const float4 tg = s_tgt[tt];
-                        const int2 tc = s_tcap[tt];
-#pragma unroll
-                        for (int u = 0; u < LU; ++u) {
-                            const float d2 = e2f::dist2_exact(tg.x, tg.y, tg.z, pj[u].x, pj[u].y, pj[u].z);
-                            const bool ok = (d2 < P.rc2) & (d2 > 0.0f) & e2f::under_cap(d2, pj[u].w, (uint32_t)tc.x, tc.y);
-                            (tt < 8 ? mlo[u] : mhi[u]) |= ok ? 1u << (4 * (tt & 7)) : 0u;
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < LU; ++u) {
-                        mlo[u] = quad_or(valid[u] ? mlo[u] << (lane & 3) : 0u);
-                        mhi[u] = quad_or(valid[u] ? mhi[u] << (lane & 3) : 0u);
-                        keep[u] = (mlo[u] | mhi[u]) != 0u;
-                    }
-                } else {
-                    bool nearby[LU];
-                    float qx[LU], qy[LU], qz[LU], qq[LU];
-#pragma unroll
-                    for (int u = 0; u < LU; ++u) {
-                        nearby[u] = false;
-                        qx[u] = pj[u].x - origin.x;
-                        qy[u] = pj[u].y - origin.y;
-                        qz[u] = pj[u].z - origin.z;
-                        qq[u] = qx[u] * qx[u] + qy[u] * qy[u] + qz[u] * qz[u];
-                    }
-#pragma unroll
-                    for (int tt = 0; tt < 16; ++tt) {
-                        const float4 tg = s_tgt[tt];
-#pragma unroll
-                        for (int u = 0; u < LU; ++u)
-                            nearby[u] |= qx[u] * tg.x + (qy[u] * tg.y + (qz[u] * tg.z + (qq[u] + tg.w))) < 0.0f;
-                    }
+                for (int tt = 0; tt < 16; ++tt) {
+                    const float4 tg = s_tgt[tt];
 #pragma unroll
                     for (int u = 0; u < LU; ++u)
-                        keep[u] = ((__ballot(valid[u] && nearby[u]) >> (lane & ~3)) & 0xFull) != 0ull;
+                        nearby[u] |= qx[u] * tg.x + (qy[u] * tg.y + (qz[u] * tg.z + (qq[u] + tg.w))) < 0.0f;
                 }
+#pragma unroll
+                for (int u = 0; u < LU; ++u)
+                    keep[u] = ((__ballot(valid[u] && nearby[u]) >> (lane & ~3)) & 0xFull) != 0ull;
 #pragma unroll
                 for (int u = 0; u < LU; ++u) {
                     leaders[u] = __ballot(keep[u] && (lane & 3) == 0);
@@ -372,16 +352,40 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                 if (keep[u]) {
                     if ((lane & 3) == 0) {
                         s_ent[e] = (int)(((unsigned)grp[u] << 8) | ((MODE == 1 ? (unsigned)pidx : 0u) << 4) | valid4[u]);
-                        if constexpr (CAP) s_mask[e] = ((unsigned long long)mhi[u] << 32) | mlo[u];
-                        else s_mask[e] = P.table ? 0ull : (unsigned long long)valid4[u] * pass_nibbles;
+                        if (!CAP) s_mask[e] = P.table ? 0ull : (unsigned long long)valid4[u] * pass_nibbles;
                     }
                     float* sp = s_posf + e * 12 + (lane & 3);
                     sp[0] = pj[u].x;
                     sp[4] = pj[u].y;
                     sp[8] = pj[u].z;
+                    if constexpr (CAP) s_atom[4 * e + (lane & 3)] = pj[u].w;
                 }
                 e0 += __popcll(leaders[u]);
             }
+            }
+            if constexpr (CAP) {
+                // ---- neighbour cap: which pairs of a listed slot and a target count, one slot per thread.  (For every candidate
+                // slot in the place of the test above, before the list is packed, it took the list kernel from 13 to 21 us in a
+                // batch of 500 atoms: three quarters of the candidates are not kept.)  The target itself is at distance
+                // zero, an image of it at a box length: neither passes.
+                __syncthreads();
+                for (int x = threadIdx.x; x < 4 * cnt; x += 64 * NW) {
+                    const int e = x >> 2, s = x & 3;
+                    const float px = s_posf[e * 12 + s], py = s_posf[e * 12 + 4 + s], pz = s_posf[e * 12 + 8 + s], atom = s_atom[x];
+                    unsigned mlo = 0u, mhi = 0u;   // targets 0 .. 7 and 8 .. 15
+#pragma unroll
+                    for (int tt = 0; tt < 16; ++tt) {
+                        const float4 tg = s_tpos[tt];
+                        const int2 tc = s_tcap[tt];
+                        const float d2 = e2f::dist2_exact(tg.x, tg.y, tg.z, px, py, pz);
+                        const bool ok = (d2 < P.rc2) & (d2 > 0.0f) & e2f::under_cap(d2, atom, (uint32_t)tc.x, tc.y);
+                        (tt < 8 ? mlo : mhi) |= ok ? 1u << (4 * (tt & 7)) : 0u;
+                    }
+                    const bool valid = (s_ent[e] >> s) & 1;
+                    mlo = quad_or(valid ? mlo << s : 0u);
+                    mhi = quad_or(valid ? mhi << s : 0u);
+                    if (s == 0) s_mask[e] = ((unsigned long long)mhi << 32) | mlo;
+                }
             }
             if (!CAP && P.table) {   // (a call has a cap or a table)
                 // ---- neighbour table: the listed atoms of the pass's targets, looked up in the batch (an atom outside

@@ -530,3 +530,34 @@ def test_fused_activation_memory_is_linear_and_below_the_baseline(torch_cuda):
     E, peak = P.forward_materialized(torch_cuda.empty_like(P.out))
     assert peak > 5 * P.activation_bytes()
     P.close()
+
+
+@pytest.mark.parametrize("n,Ks", [(2, (1,)), (17, (3, 16)), (22, (5, 21, 40)), (67, (20, 65)), (961, (16, 300, 959, 1000))])
+def test_cap_and_table_on_the_tile_lists(torch_cuda, n, Ks):
+    """A ball of atoms that all see each other, capped and by table: list lengths that are no multiple of four, all atoms or
+    few of them within reach of a target (the list holds those within reach, the pair masks those under the cap), and a
+    cap so wide that the tiles' lists do not fit (961 atoms make 241 entries; 300 of 960 do).  Against the oracle, and
+    capped against the table that names the same atoms."""
+    import oracle as O
+    from paper_2601_16622_amd import binding as B, workloads as W
+    rng = np.random.default_rng(n)
+    cfg = dict(L=2, C=32, H=2, B=8, lf=1, cutoff=6.0, dtype="bf16")
+    pos = rng.uniform(-1.7, 1.7, size=(n, 3)).astype(np.float32)
+    wl = W._pack(cfg, [pos, pos[:5] + np.float32(30.0)], rng, elements=False)
+    off, idx = O.neighbor_list(wl["pos"], wl["seg"], np.float32(6.0))
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        for K in Ks:
+            ref = O.attn_forward({k: cfg[k] for k in ("L", "C", "H", "B", "lf", "cutoff")}, wl["pos"], wl["h"], wl["seg"], wl["weights"],
+                                 nbr=O.cap_neighbors(wl["pos"], off, idx, K))
+            capped = P.forward_capped(K).clone()
+            table, _ = P.neighbor_table(K)
+            by_table = P.forward_table(table)
+            torch_cuda.cuda.synchronize()
+            for got in (capped, by_table):
+                got = got.cpu().numpy().astype(np.float64)
+                assert np.linalg.norm(got - ref) <= 1e-2 * np.linalg.norm(ref), K
+            assert float((capped - by_table).norm()) <= 5e-3 * float(by_table.norm())
+    finally:
+        P.close()
