@@ -398,11 +398,16 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                     const int nb = P.table[(size_t)ai * K + x % K];
                     if (nb >= 0 && nb < N && nb != ai) {
                         const int sj = P.cv.atom_slot[nb];
-                        for (int e = 0; e < cnt; ++e)   // (a group on the border of two runs has an entry in each)
-                            if ((int)((unsigned)s_ent[e] >> 8) == (sj >> 2) && ((s_ent[e] >> (sj & 3)) & 1)) {
-                                atomicOr(&s_mask[e], 1ull << (4 * i + (sj & 3)));
-                                break;
-                            }
+                        // four entries at a time (a group on the border of two runs has an entry in each, with other slots of it)
+                        const unsigned group = (unsigned)sj >> 2, bit = 1u << (sj & 3);
+                        for (int e0 = 0, at = -1; e0 < cnt && at < 0; e0 += 4) {
+                            const int4 ent = *reinterpret_cast<const int4*>(s_ent + e0);
+                            const unsigned ents[4] = {(unsigned)ent.x, (unsigned)ent.y, (unsigned)ent.z, (unsigned)ent.w};
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                if (ents[u] >> 8 == group && (ents[u] & bit) && e0 + u < cnt) at = e0 + u;
+                            if (at >= 0) atomicOr(&s_mask[at], 1ull << (4 * i + (sj & 3)));
+                        }
                     }
                 }
             }
