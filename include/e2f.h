@@ -212,8 +212,8 @@ e2f_status e2f_attn_forward_materialized(e2f_ctx *ctx, const e2f_cells *cells, c
 /*
  * Neighbour cap (the max_neighbors setting of the paper's model table): the same operator as e2f_attn_forward with
  * N(i) restricted to the max_neighbors nearest atoms inside the cutoff (distance compared through the binary32 d^2 of
- * the cutoff predicate, ties to the lower atom index).  The thresholds are found by a radix select on the GPU inside
- * the call and kept in two more int32 [N] arrays at the end of the workspace; all three attention kernels apply them.
+ * the cutoff predicate, ties to the lower atom index).  The thresholds are found on the GPU inside the
+ * call (by counting, or by a radix select beyond 256 neighbours) and kept in two more int32 [N] arrays at the end of the workspace; all three attention kernels apply them.
  * max_neighbors <= 0: E2F_ERR_INVALID_ARG.  Otherwise as e2f_attn_forward.
  */
 size_t e2f_attn_capped_workspace_bytes(const e2f_ctx *ctx, int32_t N);

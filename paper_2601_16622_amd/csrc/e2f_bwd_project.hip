@@ -697,10 +697,13 @@ e2f_status launch_T(const e2f_ctx* ctx, int N, const e2f_weights* w, const void*
     const int L = ctx->cfg.L_max, C = ctx->cfg.C;
     T* WT = reinterpret_cast<T*>(bw.wT);
 #define E2F_C(CP, PAD) launch_C<T, CP, PAD>(mw, WT, (const T*)h, gq, gk, gv, gh, grad_W, bw.wpart, L, C, N, st)
+    if constexpr (sizeof(T) == 4) {   // (bf16 features come in whole 32 channels)
+        if (C == 16) E2F_C(32, true);
+        if (C == 48) E2F_C(64, true);
+    }
     switch (C) {
-        case 16: E2F_C(32, true); break;
+        case 16: case 48: break;
         case 32: E2F_C(32, false); break;
-        case 48: E2F_C(64, true); break;
         case 64: E2F_C(64, false); break;
         case 128: E2F_C(128, false); break;
         case 256: E2F_C(256, false); break;

@@ -282,9 +282,10 @@ __device__ __forceinline__ int block_scan(int v, int* s) {
 
 // The whole construction for a small call, in one workgroup and one launch: what the kernels above pass on through
 // memory stays in LDS (boxes, grids, cell offsets, sort keys) and registers (an atom's cell).  The same functions in the
-// same order, so the same lists.  The seven launches above are mostly launch: whole calls in us, seven launches / this, at 64
-// atoms 57.5 / 45.9, 160 in 20 molecules 71.6 / 61.8, 2 000 atoms 92.5 / 80.4, 4 000 in 16 molecules 146 / 136 (the last
-// size with all sort keys in registers and LDS: four atoms per thread, 60 KB).
+// same order, so the same lists.  The seven launches above are mostly launch: the call in us, seven launches / this, at 64
+// atoms 25 / 13, 1 000 33 / 15, 2 240 in 64 molecules 28 / 17, 4 000 in 16 31 / 22, 4 096 38 / 23, 3 900 in 200 35 / 35, 1 500 in
+// 700 26 / 27; everything in one cell, where the ranks cost most, 1 000 atoms 191 / 35, 4 096 702 / 379.  It ends where its
+// room does, four atoms per thread in registers and 60 KB of LDS (51 at 4 000 atoms in 16 molecules), still ahead there.
 constexpr int SMALL_N = 4096, SMALL_S = 1024, SMALL_PER = SMALL_N / 1024;
 __global__ __launch_bounds__(1024) void k_cells_small(const float* __restrict__ pos, const int32_t* __restrict__ seg_offsets, int N,
                                                       int S, int max_cells, float edge0, const float* __restrict__ box,

@@ -116,7 +116,7 @@ struct E2fBwdWs {
     float* lse;  // [N][H] log of the softmax normaliser per sorted slot and head
     float* Dn;   // [N][H] <dL/d out_i, out_i> per head
     float* G;    // [3][25][25] axis operators of the degree-1 filter
-    // for the gradients of Wb and w_path: unit-weight path coefficients and axis operators, per-atom partial sums
+    // for the gradients of Wb and w_path: axis operators with unit path weights, per-atom partial sums
     float* Gu;       // [3][25][25]
     float* pWb;      // [N][H][B]
     float* pwp;      // [N][32]
@@ -243,7 +243,6 @@ e2f_status e2f_launch_backward(const e2f_ctx* ctx, const E2fCellsView& cv, const
 e2f_status e2f_launch_backward_maps(const e2f_ctx* ctx, int N, const e2f_weights* w, const void* h, const float* grad_q,
                                     const float* grad_k, const float* grad_v, float* grad_h, float* grad_W,
                                     const E2fBwdWs& bw, hipStream_t st);
-// cw[comp][t] = P coefficient with every path weight one.
 // table: the caller's padded neighbour table [N][table_K], or null (every atom within the cutoff is a neighbour)
 e2f_status e2f_launch_tile(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, const int32_t* table,
                            int table_K, float* out, hipStream_t st);

@@ -1189,8 +1189,7 @@ e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, c
 
 // The plain layouts and W_Q1 h (q1, v's plain layout).  Where the weight-stationary kernel runs it stores the product that
 // it forms for q anyway; elsewhere the projection runs a second time with W_Q1 in the value's place (it rewrites q and k
-// with the same numbers).  One pass: call of 4 000 atoms, L = 4, 128
-// channels 552 -> 484 us.
+// with the same numbers).  One pass: call of 4 000 atoms, L = 4, 128 channels 552 -> 484 us.
 e2f_status e2f_launch_project_q1(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
                                  const E2fAttnWs& ws, void* q1, hipStream_t st) {
     if (cv.N == 0) return E2F_OK;

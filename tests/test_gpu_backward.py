@@ -140,7 +140,7 @@ def test_backward_tile_form_periodic(torch_cuda):
 
 def test_backward_tile_form_with_crowded_tiles(torch_cuda):
     """1500 atoms in a 6 A cube inside a sparse shell, and a sparse cluster apart: the dense tiles keep more slot groups
-    than a tile's candidate list holds (192 entries; the same recipe as the forward pass's test of long lists) and
+    than a tile's candidate list holds (240 entries; the same recipe as the forward pass's test of long lists) and
     are left to the per-atom kernels, which read the tile layouts and exchange the softmax statistics with the tile
     kernels of the sparse tiles around them."""
     from paper_2601_16622_amd import workloads as W

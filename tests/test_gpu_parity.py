@@ -392,7 +392,7 @@ def test_isolated_atoms_and_crowded_cells(torch_cuda):
 
 def test_tile_kernel_with_lists_longer_than_the_shared_list_area(torch_cuda):
     """1500 atoms in a 6 A box (bf16, heads of 16: the tile kernel): central atoms have over 1000 neighbours, so their
-    tiles keep more slot groups than a tile's shared candidate list holds (192 entries) and more than one batch of
+    tiles keep more slot groups than a tile's shared candidate list holds (240 entries) and more than one batch of
     the list in LDS (256): those tiles build their lists per head, in several batches; a sparse cluster beside them
     uses the shared lists."""
     from paper_2601_16622_amd import workloads as W
