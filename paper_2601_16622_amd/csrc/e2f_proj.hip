@@ -115,9 +115,12 @@ __device__ __forceinline__ void store_run_bf16(uint16_t* row, int pos0, const fl
 // components in tile order (HI: l=4 rows 0..8, l=3 rows 9..15; LO: l=2 rows 0..4, l=1 rows 5..7, l=0 row 8,
 // rows 9..15 zero), heads of 16 channels.
 // Two waves to a SIMD where a wave's rows and weights leave the registers for it (fp32 up to 64 channels, L = 4, 2 000 atoms
-// 36 -> 33 us; bf16 192 channels, L = 4, 1 000 atoms 38 us against 48 with the weights loaded again in every pass).
+// 36 -> 33 us; bf16 192 channels, L = 4, 1 000 atoms 38 us against 48 with the weights loaded again in every pass), and for
+// fp32 128 channels in the instance of three orders.
+template <typename T, int C, int MG>
+constexpr bool THREE_ORDERS = sizeof(T) == 4 && C == 128 && MG == 3;
 template <typename T, int C, int MG, int CT, bool TILED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && C <= (sizeof(T) == 2 ? 192 : 64) ? 2 : 1))) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (C <= (sizeof(T) == 2 ? 192 : 64) || THREE_ORDERS<T, C, MG>) ? 2 : 1))) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
@@ -141,9 +144,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && C
         // Several channel tiles: an offset of zero that the compiler cannot see through.  The weights are the same for every
         // pass over the orders, and it would load those of all maps and tiles before the loop, into scratch memory (fp32, L = 2,
         // 9 000 atoms, 192 channels 1 314 us with them, 388 without).  Those of one tile fit the registers and stay there
-        // (4 000 atoms, 190 us; loaded again in every pass 254).
+        // (4 000 atoms, 190 us; loaded again in every pass 254), but not beside a second wave (THREE_ORDERS: 60 us without, 55 with).
         int fresh = 0;
-        if constexpr (CT > 1) asm volatile("" : "+s"(fresh));
+        if constexpr (CT > 1 || THREE_ORDERS<T, C, MG>) asm volatile("" : "+s"(fresh));
         typename F::type A[MG][NS];
 #pragma unroll
         for (int mm = 0; mm < MG; ++mm) {
@@ -929,36 +932,39 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
     if constexpr (C % Frag<T>::KSTEP != 0) {
         return false;
     } else {
-        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order).  (Three orders at
-        // 128 fp32 channels, so that two waves fit a SIMD, are no faster at 2 000 atoms, L = 2, and 240 instead of 207 us at
-        // 4 000, L = 4.)
+        // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order)
         constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 5 : 2));
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
-        const int waves_ct = (cv.N + 15) / 16 * (ctx->cfg.L_max + 1) * (C / 16 / CT);
-        auto go = [&](auto ct_tag) {
-            constexpr int ct = decltype(ct_tag)::value;
+        const int tiles = (cv.N + 15) / 16, L1 = ctx->cfg.L_max + 1, waves_ct = tiles * L1 * (C / 16 / CT);
+        const bool few = (long long)tiles * L1 * (C / 16) <= 5 * 1024;   // one-tile waves in up to five rounds of one wave per SIMD
+        auto go = [&](auto ct_tag, auto mg_tag) {
+            constexpr int ct = decltype(ct_tag)::value, mg = decltype(mg_tag)::value;
             // The degrees with the most orders start first, so that the launch does not end on its longest waves (fp32, 1 000
             // atoms: 128 channels, L = 2, 30 us against 37; 192, L = 4, 118 against 134).  From 128 channels on a SIMD holds one
             // wave, and beyond five rounds of them the degrees are better mixed, since the short waves of the low degrees, mostly
             // waiting for weights, would have the chip to themselves at the end (128 channels, L = 2, 9 000 atoms 203 us
             // against 183; the four-tile form gains by the first order at every size it has).
-            const int tiles = (cv.N + 15) / 16, L1 = ctx->cfg.L_max + 1;
-            const bool longest_first = ct > 1 || C < 128 || (long long)tiles * L1 * (C / 16) <= 5 * 1024;
+            const bool longest_first = ct > 1 || C < 128 || few;
             const dim3 grid = longest_first ? dim3(tiles, C / 16 / ct, L1) : dim3(tiles, L1, C / 16 / ct);
             if (tiled)
-                k_project_mfma<T, C, MG, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
+                k_project_mfma<T, C, mg, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
             else
-                k_project_mfma<T, C, MG, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
+                k_project_mfma<T, C, mg, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
                                                                         ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
         };
-        if (CT > 1 && waves_ct < 4096)
-            go(std::integral_constant<int, 1>{});
+        // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2: 500 atoms 21 us
+        // against 22.4, 2 286 atoms 61.7 / 63.5, but 9 000 atoms 199 / 185 and L = 4, 4 000 atoms 240 / 206)
+        constexpr bool CAN_THREE = sizeof(T) == 4 && C == 128;
+        if (CAN_THREE && few && L1 <= 3)
+            go(std::integral_constant<int, 1>{}, std::integral_constant<int, CAN_THREE ? 3 : MG>{});
+        else if (CT > 1 && waves_ct < 4096)
+            go(std::integral_constant<int, 1>{}, std::integral_constant<int, MG>{});
         else
-            go(std::integral_constant<int, CT>{});
+            go(std::integral_constant<int, CT>{}, std::integral_constant<int, MG>{});
         return true;
     }
 }
