@@ -272,12 +272,12 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 // through LDS as [atom][channel] rows, rounded to bf16 as in k_bwd_rows.  The feature rows of a slab are fetched once per
 // workgroup and shared through LDS as well.
 // It takes a call from STATIONARY_WORK row elements on: a load of the weights is shared by more rows the more rows there are, and
-// below that its workgroups do not fill the chip.  Measured, us, this kernel / k_bwd_rows with 64 rows a workgroup: 128
-// channels, L = 4: 1 000 atoms 38 / 31, 1 500 39 / 42, 2 000 40 / 59, 3 000 43 / 83 (62 with 128 rows), 4 000 79 / 106 (80),
-// 6 000 86 / 152 (101), 9 000 130 / 219 (139); 64 channels, L = 3: 2 000 atoms 20 / 13, 4 000 21 / 21, 6 000 25 / 28, 9 000 30 / 45
-// (43); 32 channels, L = 1: 9 000 atoms 12 / 8, 20 000 14 / 12, 40 000 18 / 19.
+// below that its workgroups do not fill the chip.  Measured, us, this kernel / k_bwd_rows with 64 rows a workgroup (with 128):
+// 128 channels, L = 4: 1 000 atoms 38 / 31, 1 500 39 / 42, 2 000 40 / 59, 3 000 43 / 83 (62), 4 000 55 / 106 (80), 6 000 76 / 152
+// (101), 9 000 115 / 219 (139); 64 channels, L = 3: 2 000 atoms 20 / 13, 4 000 21 / 21, 6 000 26 / 28, 9 000 30 / 45 (43); 32 channels,
+// L = 1: 9 000 atoms 12 / 8, 20 000 14 / 12, 40 000 18 / 19.
 constexpr long long STATIONARY_WORK = 1ll << 22;
-constexpr int ROWS_SLABS = 18;   // slabs a workgroup walks with one load of its weights
+constexpr int SLABS_MIN = 18, SLABS_MAX = 36;   // slabs a workgroup walks with one load of its weights
 // Workgroups [first[d], first[d + 1]) own degree L - d (the highest degree, with the most slabs per tile, first) and
 // tiles[d] consecutive tiles of 16 atoms each, so that every workgroup walks about the same number of slabs.
 struct SlabMap {
@@ -651,12 +651,31 @@ template <int C>
 void launch_rows_stationary(const MapWeights<uint16_t>& mw, const uint16_t* WT, const uint16_t* h, const float* gq, const float* gk,
                             const float* gv, float* gh, int L, int N, hipStream_t st) {
     const int tiles = (N + 15) / 16;
+    auto make = [&](int slabs, int& longest) {   // every workgroup about `slabs`, whatever its degree
+        SlabMap map;
+        map.first[0] = longest = 0;
+        for (int d = 0; d <= L; ++d) {
+            const int nl = 2 * (L - d) + 1;
+            map.tiles[d] = (slabs + nl - 1) / nl;
+            map.first[d + 1] = map.first[d] + (tiles + map.tiles[d] - 1) / map.tiles[d];
+            if (map.tiles[d] * nl > longest) longest = map.tiles[d] * nl;
+        }
+        return map;
+    };
+    // Workgroups of about equal length run in whole rounds of what the chip holds (one, three or eight to a CU, by registers),
+    // and a load of the weights costs about six slabs: the slabs per workgroup with the shortest sum of rounds.  (128 channels,
+    // L = 4, always 18 / so: 3 840 atoms 75 / 53 us, 6 000 86 / 76, 9 973 157 / 127.)
+    const int at_once = 256 * (C == 128 ? 1 : C == 64 ? 3 : 8);
     SlabMap map;
-    map.first[0] = 0;
-    for (int d = 0; d <= L; ++d) {
-        const int nl = 2 * (L - d) + 1;
-        map.tiles[d] = (ROWS_SLABS + nl - 1) / nl;
-        map.first[d + 1] = map.first[d] + (tiles + map.tiles[d] - 1) / map.tiles[d];
+    long long best = -1;
+    for (int slabs = SLABS_MIN; slabs <= SLABS_MAX; ++slabs) {
+        int longest;
+        const SlabMap m = make(slabs, longest);
+        const long long cost = (long long)((m.first[L + 1] + at_once - 1) / at_once) * (longest + 6);
+        if (best < 0 || cost < best) {
+            best = cost;
+            map = m;
+        }
     }
     k_bwd_rows_stationary<C><<<map.first[L + 1], 64 * (C / 16), 0, st>>>(h, mw, WT, gq, gk, gv, gh, L, N, map);
 }
