@@ -180,8 +180,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // ---- degree-1 filter, bf16 features, heads of 16 channels: one wave per (target, head) on the matrix cores.
 //
-// Bound by the vector ALUs: a pair costs every channel 2 (L + 1) sigma's, each an exponential and a reciprocal at a
-// quarter of the rate, and the products around them.  What the kernel above spends beside that goes to the matrix cores:
+// Vector work and waits: a pair costs every channel 2 (L + 1) sigma's, each an exponential and a reciprocal at a quarter of the
+// rate, and the products around them (vector ALUs active 51 % of the SIMD cycles), and a wave waits 44 % of its cycles, mostly
+// for the rows of the pairs it is about to use.  What the kernel above spends beside that goes to the matrix cores:
 //   a       the target's feature is a product over its own rows, [pairs] x (2l+1) times (2l+1) x [channels] per degree
 //   message linear in the pair vector, so T_mu += w_ij (r_ij)_mu v_j, three rows against the value rows, and the axis
 //           operators G_mu = D(R_mu)^T P D(R_mu) once per target in place of two rotations per pair
