@@ -1010,8 +1010,10 @@ bool launch_ws_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, co
 bool dispatch_ws_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
                      hipStream_t st) {
     // While the features fit the caches the per-tile kernel, which fetches its weights per wave, is a little faster
-    // (0.29 against 0.33 ms at 6000 atoms, 128 channels, L = 4: 77 MB of features); beyond, it falls off (0.93
-    // against 0.42 ms at 8000 atoms, 1.16 against 0.47 at 10 000).
+    // (0.29 against 0.33 ms at 6000 atoms, 128 channels, L = 4: 77 MB of features).  The line was drawn where its four-tile
+    // form fell off (0.93 against 0.42 ms at 8000 atoms), for the scratch memory it used then; without that it takes 0.34
+    // against 0.39 at 8000 and 0.80 against 0.87 at 20 000, so there is no longer a size here where this one is ahead at 128
+    // channels; at 64 it is from 20 000 atoms on (0.250 / 0.257).
     if ((long long)cv.N * ctx->n * ctx->cfg.C * 4 < (80ll << 20)) return false;
     switch (ctx->cfg.C) {
         case 64: return launch_ws_f32<64>(ctx, cv, h, w, ws, st);
