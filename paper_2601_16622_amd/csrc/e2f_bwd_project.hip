@@ -701,7 +701,7 @@ void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const
     }
     if (grad_W) {
         constexpr int NW = CP / 16 < 8 ? CP / 16 : 8;
-        const int split = e2f_wgrad_split(L, C, N);
+        const int split = e2f_wgrad_split(L, C, N, sizeof(T) == 4);
         const dim3 grid(split * (L + 1) * (L + 1), 5 * (CP / 16 / NW));
         k_bwd_wgrad<T, CP, NW, PAD><<<grid, 64 * NW, 0, st>>>(h, mw, gq, gk, gv, L, C, N, split, part);
         const size_t M = (size_t)5 * (L + 1) * C * C;

@@ -122,7 +122,7 @@ struct E2fBwdWs {
     float* pwp;      // [N][32]
     uint16_t* wT;    // [5][L+1][C in][C out] the projection matrices transposed (bf16 features; null for fp32)
     // for the gradients of the projection matrices (only in the larger workspace of that form of the call)
-    float* wpart;    // [e2f_wgrad_split(L, C, N) (L+1)^2 slices][5][C][C] partial sums
+    float* wpart;    // [e2f_wgrad_split(L, C, N, ..) (L+1)^2 slices][5][C][C] partial sums
     size_t bytes;
 };
 
@@ -150,10 +150,13 @@ struct E2fFactWs {
 };
 
 // Slices of rows per component in the sums of the projection matrices' gradients: about 100 slices in all, five maps
-// each, which is one round of two workgroups per CU; no more than the room in the workspace, which is that of 8
-// slices and of five [N][(L+1)^2][C] arrays: split (L+1)^2 C^2 <= 8 (L+1)^2 C^2 + N (L+1)^2 C.
-static inline int e2f_wgrad_split(int L, int C, int N) {
-    const int want = (100 + (L + 1) * (L + 1) / 2) / ((L + 1) * (L + 1)), room = 8 + N / C;
+// each, which is one round of two workgroups per CU, but for fp32 features, whose sums round once per row, at least 8 from
+// 512 atoms on (6 000 atoms, L = 4, 128 channels: 7.3e-7 of the norm from 64 bits with 4, 5.5e-7 with 8; fewer atoms differ
+// by nothing but the time of the last sum, 246 / 265 us a call of 60 atoms); no more than the room in the workspace, which is that of 8 slices and of five [N][(L+1)^2][C] arrays: split (L+1)^2 C^2 <= 8 (L+1)^2 C^2 + N (L+1)^2 C.
+static inline int e2f_wgrad_split(int L, int C, int N, bool fp32) {
+    int want = (100 + (L + 1) * (L + 1) / 2) / ((L + 1) * (L + 1));
+    if (fp32 && N >= 512 && want < 8) want = 8;
+    const int room = 8 + N / C;
     return want < room ? want : room;
 }
 

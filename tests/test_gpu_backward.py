@@ -259,6 +259,32 @@ def chain_rule(P, gq, gk, gv):
     return gh, gW
 
 
+@pytest.mark.parametrize("L,C,H", [(3, 64, 4), (4, 128, 8)])
+def test_fp32_weight_gradients_round_as_few_sums_as_eight_slices(torch_cuda, L, C, H):
+    """fp32 features, 6 000 atoms, degrees 3 and 4: sums over slices of N / 8 rows, one rounding per row.  A chain of n additions of
+    random terms is off by about 2^-24 sqrt(n / 2) / sqrt(3) of its sum, 6.7e-7 for n = 750 and 9.4e-7 for 1 500 (four slices); the
+    matrix instruction's own order leaves 5.5e-7 and 7.3e-7 of it."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    N = 6000
+    rng = np.random.default_rng(L)
+    cfg = dict(L=L, C=C, H=H, B=4, lf=1, cutoff=2.5, dtype="f32")
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        _, gq, gk, gv, _, _, _, gW = P.backward(g, with_weights=True)
+        torch.cuda.synchronize()
+        ref = chain_rule(P, gq, gk, gv)[1]
+        err = float((gW.double() - ref).norm() / ref.norm())
+        assert err <= (5.7e-7 if L == 3 else 6.3e-7), err
+    finally:
+        P.close()
+
+
 @pytest.mark.parametrize("L,C,N", [(4, 128, 1310), (4, 128, 1311), (4, 128, 3001), (2, 64, 7281), (2, 64, 7282), (3, 64, 4096),
                                    (1, 32, 32767), (1, 32, 32769)])
 def test_backward_through_the_maps_beside_the_change_of_kernel(torch_cuda, L, C, N):
