@@ -212,8 +212,9 @@ e2f_status e2f_attn_forward_materialized(e2f_ctx *ctx, const e2f_cells *cells, c
 /*
  * Neighbour cap (the max_neighbors setting of the paper's model table): the same operator as e2f_attn_forward with
  * N(i) restricted to the max_neighbors nearest atoms inside the cutoff (distance compared through the binary32 d^2 of
- * the cutoff predicate, ties to the lower atom index).  The thresholds are found on the GPU inside the
- * call (by counting, or by a radix select beyond 256 neighbours) and kept in two more int32 [N] arrays at the end of the workspace; all three attention kernels apply them.
+ * the cutoff predicate, ties to the lower atom index).  The thresholds are found on the GPU inside the call
+ * (by counting, or by a radix select beyond 256 neighbours) and kept in two more int32 [N] arrays at the end of the
+ * workspace; all three attention kernels apply them.
  * max_neighbors <= 0: E2F_ERR_INVALID_ARG.  Otherwise as e2f_attn_forward.
  */
 size_t e2f_attn_capped_workspace_bytes(const e2f_ctx *ctx, int32_t N);
@@ -293,7 +294,9 @@ e2f_status e2f_attn_forward_factorized(e2f_ctx *ctx, const e2f_cells *cells, con
  *             channel), fully overwritten; needs the larger workspace e2f_attn_backward_weights_workspace_bytes(ctx, N)
  *             (larger by five [N][(L_max+1)^2][C] float arrays and 8 (L_max+1)^2 [5][C][C] ones, room for partial sums of
  *             the result)
- *   ws        device, at least e2f_attn_backward_workspace_bytes(ctx, N) bytes, 256-byte aligned
+ *   ws        device, at least e2f_attn_backward_workspace_bytes(ctx, N) bytes, 256-byte aligned.  (Both queries answer no
+ *             less than e2f_attn_workspace_bytes, so that one buffer serves a forward and a backward pass; where that is
+ *             more than the backward pass needs by itself, fp32 features for one, the smaller buffer is accepted.)
  * grad_out and the gradients may start at any float (a view into a larger buffer); out, like h, is 16-byte aligned.
  * Cell lists from e2f_build_cells and e2f_build_cells_periodic are accepted.  E2F_ERR_UNSUPPORTED: lf != 1, or a
  * head width C/H that is not a power of two <= 64.  Where the forward pass runs on the bf16 TILE kernel the pair work of

@@ -633,7 +633,8 @@ static bool backward_in_tile_form(const e2f_ctx* ctx, bool wgrad) {
     return ctx->use_tile_attn && (!wgrad || e2f_backward_tile_weight_gradients_supported(ctx));
 }
 
-static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_W) {
+// What the call needs of its workspace.
+static size_t backward_needs(const e2f_ctx* ctx, int32_t N, bool with_W) {
     size_t bytes = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 0).bytes, with_W).bytes;
     if (backward_in_tile_form(ctx, false)) {   // either form may run, depending on the gradients asked for
         const size_t b2 = bwd_ws_layout(ctx, N, nullptr, e2f_attn_ws_layout(ctx, N, nullptr, 2).bytes, with_W).bytes;
@@ -641,6 +642,12 @@ static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_
         if (b3 > bytes) bytes = b3;
     }
     return bytes;
+}
+
+// What it asks for: never less than the forward pass wants, so that a training step can run both in the one workspace.
+static size_t backward_workspace_bytes(const e2f_ctx* ctx, int32_t N, bool with_W) {
+    const size_t bytes = backward_needs(ctx, N, with_W), fwd = e2f_attn_workspace_bytes(ctx, N);
+    return bytes > fwd ? bytes : fwd;
 }
 
 size_t e2f_attn_backward_workspace_bytes(const e2f_ctx* ctx, int32_t N) {
@@ -663,8 +670,7 @@ static e2f_status backward_impl(e2f_ctx* ctx, const e2f_cells* cells, const floa
     e2f_status rc = check_forward_args(ctx, cells, pos, h, seg_offsets, N, S, w, const_cast<float*>(out), ws, (size_t)-1);
     if (rc != E2F_OK || N == 0) return rc;
     if (!grad_out || !grad_pos || !grad_q || !grad_k || !grad_v) return E2F_ERR_INVALID_ARG;
-    if (ws_bytes < (grad_W ? e2f_attn_backward_weights_workspace_bytes(ctx, N) : e2f_attn_backward_workspace_bytes(ctx, N)))
-        return E2F_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < backward_needs(ctx, N, grad_W != nullptr)) return E2F_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const bool tile = backward_in_tile_form(ctx, grad_Wb || grad_w_path);
     const int v_layout = tile ? 2 : 0;

@@ -233,11 +233,13 @@ def test_backward_entry_point_sizes_and_limits(lib):
 ])
 def test_backward_workspaces_do_not_grow(lib, L, C, H, dtype, N, plain, weights):
     """Sizes that programs may have stored or allocated once: a buffer of them stays large enough (few atoms at a low
-    degree, where the slices of partial sums outweigh the arrays, and fp32 features among them)."""
+    degree, where the slices of partial sums outweigh the arrays, and fp32 features among them).  The queries ask for more
+    only where the forward pass, which may share the buffer, wants more."""
     ctx = B.e2f_create(L, C, H, 8, 1, 5.0, dtype)
     try:
-        assert B.e2f_attn_backward_workspace_bytes(ctx, N) <= plain
-        assert B.e2f_attn_backward_weights_workspace_bytes(ctx, N) <= weights
+        forward = B.e2f_attn_workspace_bytes(ctx, N)
+        assert forward <= B.e2f_attn_backward_workspace_bytes(ctx, N) <= max(plain, forward)
+        assert forward <= B.e2f_attn_backward_weights_workspace_bytes(ctx, N) <= max(weights, forward)
     finally:
         B.e2f_destroy(ctx)
 

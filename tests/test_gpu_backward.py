@@ -374,6 +374,37 @@ def test_backward_stays_inside_its_workspace(torch_cuda, dtype, L, C, H, N):
         P.close()
 
 
+@pytest.mark.parametrize("L,C,H,N,size", [(1, 256, 16, 17, 170240), (2, 128, 8, 2240, 18259200)])
+def test_backward_accepts_less_than_the_forward_pass_wants(torch_cuda, L, C, H, N, size):
+    """fp32 features: the backward pass needs less by itself than the forward pass, whose size the query answers.  A
+    buffer of the smaller size (one that programs may have kept) is accepted and enough, with bytes around it that
+    stay as they are; half of it is refused."""
+    from paper_2601_16622_amd import binding as B
+    from paper_2601_16622_amd import workloads as W
+    torch = torch_cuda
+    rng = np.random.default_rng(N)
+    cfg = dict(L=L, C=C, H=H, B=8, lf=1, cutoff=2.5, dtype="f32")
+    wl = W._pack(cfg, [rng.uniform(0.0, (N / 0.1) ** (1.0 / 3.0), size=(N, 3)).astype(np.float32)], rng, elements=False)
+    P = B.Problem(wl)
+    try:
+        P.build_cells()
+        P.forward()
+        assert B.e2f_attn_backward_workspace_bytes(P.ctx, N) > size
+        g = torch.randn(P.out.shape, generator=torch.Generator().manual_seed(1)).to(P.device)
+        want = [x.clone() for x in P.backward(g)]
+        around = torch.full((4096 + size + 4096,), 0xA5, dtype=torch.uint8, device=P.device)
+        got = [torch.empty_like(x) for x in want]
+        B.e2f_attn_backward(P.ctx, P.cells, P.pos, P.h, P.seg, P.weights, P.out, g, *got, around[4096:4096 + size])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want, got))
+        assert bool((around[:4096] == 0xA5).all()) and bool((around[4096 + size:] == 0xA5).all())
+        with pytest.raises(B.E2fError) as e:
+            B.e2f_attn_backward(P.ctx, P.cells, P.pos, P.h, P.seg, P.weights, P.out, g, *got, around[4096:4096 + size // 2])
+        assert e.value.code == 3
+    finally:
+        P.close()
+
+
 @pytest.mark.parametrize("dtype,C,H", [("f32", 32, 2), ("f32", 48, 3), ("bf16", 64, 4), ("bf16", 64, 1), ("bf16", 256, 16)])
 def test_backward_with_gradient_buffers_at_any_float(torch_cuda, dtype, C, H):
     """dL/d out and all gradients as views 4, 8 or 12 bytes into larger buffers: the same bits, and nothing written beside
