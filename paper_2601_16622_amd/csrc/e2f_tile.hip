@@ -694,7 +694,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int DK = (L + 1) * 16, KS = (DK + 31) / 32, DKP = KS * 32;
     constexpr int LENT = LCAP + 8 * NW;   // the list, padded to whole groups of four chunks
     constexpr int W_BYTES = NW * 3 * 64 * 16, PO_BYTES = n * 64 * 16;
-    __shared__ int s_ent[LENT];
+    __shared__ unsigned s_ent[LENT];   // slot groups
     __shared__ unsigned long long s_mask[LENT];
     __shared__ float4 s_pos[LENT * 3];
     __shared__ __attribute__((aligned(16))) uint16_t s_q[16 * DKP];
@@ -712,14 +712,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int tile, hg;
     if (!tile_xcd_remap(blockIdx.x, P.n_tiles, P.blk, HG, tile, hg)) return;   // whole workgroup
     const int head0 = hg * P.hpw;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, tn = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, tn = lane & 15, g = lane >> 4;
     // (components, accumulator slots and value rows of a wave as in tile_item)
     constexpr int NP = NX / 2, NS = 1 + 2 * NP;
     constexpr bool HAS_ODD = (NX & 1) || (n % NW != 0 && ((NX - 1) & 1));
     const int nxw = n / NW + (wave < n % NW ? 1 : 0);
     const int x0 = wave * (n / NW) + min(wave, n % NW);
     static_assert((n / NW) / 2 == NP, "every wave has NP pairs of components (a wave with one component more has it unpaired)");
-    constexpr int npair = NP;
     const bool single = (nxw & 1) != 0;
     const int N = P.cv.N, H = P.H;
     const int t0 = tile * 16, nt = min(16, N - t0);
@@ -752,7 +751,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (cnt < 0) return;   // (whole workgroup) a crowded tile: the list kernel has done it, with lists per head
     // ---- into LDS; what lies behind the list reads as groups without a valid slot, at a finite position
     if (tid < LCAP) {
-        s_ent[tid] = tid < cnt ? ent_mine : 0;
+        s_ent[tid] = tid < cnt ? (unsigned)ent_mine >> 8 : 0u;
         s_mask[tid] = tid < cnt ? mask_mine : 0ull;
     }
     if (tid < LENT - LCAP) {
@@ -781,21 +780,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     f16x8 kf[2][KS];
     VRows<NP> vr;
+    // (row addresses: a per-lane base plus the entry's slot group times a stride, one multiply-add each)
+    const uint32_t k_group = (uint32_t)(H * KS * 256), v_group = (uint32_t)(H * n * 128);   // bytes of a slot group's rows
     auto load_K = [&](int c, int head) {
+        const unsigned char* kb = reinterpret_cast<const unsigned char*>(P.k16) + (size_t)head * (KS * 256) + ((tn & 3) * 64 + g * 16);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-            const int e = s_ent[8 * c + 4 * mt + (tn >> 2)];
-            const size_t off = e2f::k16_offset(4 * (size_t)((unsigned)e >> 8) + (tn & 3), H, head, DKP, 8 * g);
+            const unsigned char* kr = kb + (uint64_t)s_ent[8 * c + 4 * mt + (tn >> 2)] * k_group;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kf[mt][ks] = *reinterpret_cast<const f16x8*>(P.k16 + off + 128 * ks);
+            for (int ks = 0; ks < KS; ++ks) kf[mt][ks] = *reinterpret_cast<const f16x8*>(kr + 256 * ks);
         }
     };
     // v rows of this wave's components for the lane's two entries (k = 8g..8g+3 from entry g of the chunk, 8g+4..8g+7
     // from entry 4+g): the wave's single component, then its pairs (see e2f::v4_offset)
     auto v_base = [&](int c, int head, const uint16_t*& ba, const uint16_t*& bb) {
-        const unsigned ea = (unsigned)s_ent[8 * c + g] >> 8, eb = (unsigned)s_ent[8 * c + 4 + g] >> 8;
-        ba = P.v4 + (((size_t)ea * H + head) * n + x0) * 64 + (single ? 64 : 0) + tn * 8;
-        bb = P.v4 + (((size_t)eb * H + head) * n + x0) * 64 + (single ? 64 : 0) + tn * 8;
+        const unsigned char* vb = reinterpret_cast<const unsigned char*>(P.v4 + ((size_t)head * n + x0) * 64 + (single ? 64 : 0)) + tn * 16;
+        ba = reinterpret_cast<const uint16_t*>(vb + (uint64_t)s_ent[8 * c + g] * v_group);
+        bb = reinterpret_cast<const uint16_t*>(vb + (uint64_t)s_ent[8 * c + 4 + g] * v_group);
     };
     auto first_rows = [&](int head) {   // the rows the streaming loop starts with
         if (nch > 0) {
@@ -804,7 +805,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             v_base(0, head, ba, bb);
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                if (p < npair) vr.load_pair(p, ba, bb);
+                vr.load_pair(p, ba, bb);
             if (HAS_ODD && single) vr.load_single(ba - 64 - tn * 4, bb - 64 - tn * 4);   // (in the order of their use)
         }
     };
@@ -881,20 +882,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const float f = move ? __builtin_amdgcn_exp2f(m_ref - gmax) : 1.0f;
                 m_ref = move ? gmax : m_ref;
                 z *= f;
-                // Rows of the accumulators are targets: T <- diag(f) T on the matrix cores in fp32.  Slice r pairs
-                // A_r[i][g] = f_i [i == 4g + r] with B_r[g][j] = T[4g + r][j], register r of lane (j, g).
-                float ar[4];
+                // Rows of the accumulators are targets: register r of lane (j, g) is row 4g + r.  (A quarter of the items move a
+                // reference; as a product with diag(f) on the fp32 matrix instruction a move took 336 instructions of 32 cycles.)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) ar[r] = tn == 4 * g + r ? f : 0.0f;
+                for (int r = 0; r < 4; ++r) {
+                    const float fr = __shfl(f, 4 * g + r);
 #pragma unroll
-                for (int mu = 0; mu < 3; ++mu)
+                    for (int mu = 0; mu < 3; ++mu)
 #pragma unroll
-                    for (int x = 0; x < NS; ++x) {
-                        f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) d = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[r], acc[mu][x][r], d, 0, 0, 0);
-                        acc[mu][x] = d;
-                    }
+                        for (int x = 0; x < NS; ++x) acc[mu][x][r] *= fr;
+                }
             }
             // ---- weights of this wave's chunk -> LDS
             {
@@ -922,36 +919,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
             __syncthreads();
             // ---- aggregate the chunks of the group into this wave's components
+            auto chunk = [&](int cc, auto more_tag) {
+                constexpr bool MORE = decltype(more_tag)::value;
+                bf16x8 W[3];
 #pragma unroll
-            for (int cc = 0; cc < NW; ++cc) {
-                const int c = NW * G + cc;
-                if (c < nch) {
-                    bf16x8 W[3];
+                for (int mu = 0; mu < 3; ++mu) W[mu] = __builtin_bit_cast(bf16x8, s_W[(cc * 3 + mu) * 64 + lane]);
+                const uint16_t *ba = nullptr, *bb = nullptr;   // the next chunk's rows replace each operand once it has been used
+                if (MORE) v_base(NW * G + cc + 1, head, ba, bb);
 #pragma unroll
-                    for (int mu = 0; mu < 3; ++mu) W[mu] = __builtin_bit_cast(bf16x8, s_W[(cc * 3 + mu) * 64 + lane]);
-                    const uint16_t *ba, *bb;   // the next chunk's rows replace each operand once it has been used
-                    v_base(min(c + 1, nch - 1), head, ba, bb);
+                for (int p = 0; p < NP; ++p) {
+                    vr.swap(p);
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        if (p < npair) {   // (wave-uniform)
-                            const bf16x8 b0 = vr.first(p), b1 = vr.second(p);
+                    for (int mu = 0; mu < 3; ++mu) acc[mu][1 + 2 * p] = mfma(W[mu], vr.swapped_first(p), acc[mu][1 + 2 * p]);
 #pragma unroll
-                            for (int mu = 0; mu < 3; ++mu) acc[mu][1 + 2 * p] = mfma(W[mu], b0, acc[mu][1 + 2 * p]);
-#pragma unroll
-                            for (int mu = 0; mu < 3; ++mu) acc[mu][2 + 2 * p] = mfma(W[mu], b1, acc[mu][2 + 2 * p]);
-                            vr.load_pair(p, ba, bb);
-                        }
-                    // The wave with an odd component takes it last.  The waits on the pairs' rows are the same
-                    // instructions for all waves, counted for the waves without the extra rows; with those rows
-                    // requested first, the wave that has them waited at every chunk for rows it had just asked for.
-                    if (HAS_ODD && single) {   // (wave-uniform)
-                        const bf16x8 bv = vr.single();
-#pragma unroll
-                        for (int mu = 0; mu < 3; ++mu) acc[mu][0] = mfma(W[mu], bv, acc[mu][0]);
-                        vr.load_single(ba - 64 - tn * 4, bb - 64 - tn * 4);
-                    }
+                    for (int mu = 0; mu < 3; ++mu) acc[mu][2 + 2 * p] = mfma(W[mu], vr.swapped_second(p), acc[mu][2 + 2 * p]);
+                    if (MORE) vr.load_pair(p, ba, bb);
                 }
-            }
+                // The wave with an odd component takes it last.  The waits on the pairs' rows are the same
+                // instructions for all waves, counted for the waves without the extra rows; with those rows
+                // requested first, the wave that has them waited at every chunk for rows it had just asked for.
+                if (HAS_ODD && single) {   // (wave-uniform)
+                    const bf16x8 bv = vr.single();
+#pragma unroll
+                    for (int mu = 0; mu < 3; ++mu) acc[mu][0] = mfma(W[mu], bv, acc[mu][0]);
+                    if (MORE) vr.load_single(ba - 64 - tn * 4, bb - 64 - tn * 4);
+                }
+            };
+            const int here = min(NW, nch - NW * G), full = min(here, nch - 1 - NW * G);   // (the list's last chunk requests no rows)
+            for (int cc = 0; cc < full; ++cc) chunk(cc, std::true_type{});
+            if (full < here) chunk(full, std::false_type{});
         }
 
         // ---- the next head's queries, radial weights and first rows are on their way during this head's epilogue
@@ -969,7 +965,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (lane < 16) s_z[wave][lane] = z;
         auto finish = [&](auto wv_tag) {
             constexpr int WV = decltype(wv_tag)::value;
-            constexpr int RO = (n - WV + NW - 1) / NW;                      // components WV, WV + NW, ...
+            constexpr uint32_t XO = E2F_AXIS_WAVES[L - 1][WV];               // this wave's output components
+            constexpr int RO = __builtin_popcount(XO);
             constexpr int X0 = WV * (n / NW) + (WV < n % NW ? WV : n % NW);  // this wave's accumulator components
             constexpr int NXW = n / NW + (WV < n % NW ? 1 : 0);
             f32x4 pr[RO];
@@ -982,11 +979,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int x = 0; x < NXW; ++x) s_po[(X0 + x) * 64 + lane] = acc[mu][x + ((NXW & 1) ? 0 : 1)];
                 __syncthreads();
 #pragma unroll
-                for (int i = 0; i < RO; ++i) {
+                for (int xi = 0; xi < n; ++xi) {
+                    uint32_t users = 0;
 #pragma unroll
-                    for (int xi = 0; xi < n; ++xi)
-                        if ((E2F_AXIS_NZ[mu][WV + NW * i] >> xi) & 1u)
-                            pr[i] += s_G[AXIS_INDEX.v[mu][WV + NW * i][xi]] * s_po[xi * 64 + lane];
+                    for (int xo = 0; xo < n; ++xo)
+                        if (((XO >> xo) & 1u) && ((E2F_AXIS_NZ[mu][xo] >> xi) & 1u)) users |= 1u << xo;
+                    if (users) {
+                        const f32x4 t = s_po[xi * 64 + lane];
+#pragma unroll
+                        for (int xo = 0; xo < n; ++xo)
+                            if ((users >> xo) & 1u) pr[__builtin_popcount(XO & ((1u << xo) - 1u))] += s_G[AXIS_INDEX.v[mu][xo][xi]] * t;
+                    }
                 }
             }
             f32x4 inv;
@@ -1009,15 +1012,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const size_t cstride = (size_t)P.C;
             if (nt == 16) {   // (uniform) every row exists: no per-row test
 #pragma unroll
-                for (int i = 0; i < RO; ++i)
+                for (int xo = 0; xo < n; ++xo)
+                    if ((XO >> xo) & 1u)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) orp[r][(WV + NW * i) * cstride] = pr[i][r] * inv[r];
+                        for (int r = 0; r < 4; ++r) orp[r][xo * cstride] = pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r];
             } else {
 #pragma unroll
-                for (int i = 0; i < RO; ++i)
+                for (int xo = 0; xo < n; ++xo)
+                    if ((XO >> xo) & 1u)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (orow[r] >= 0) orp[r][(WV + NW * i) * cstride] = pr[i][r] * inv[r];
+                        for (int r = 0; r < 4; ++r)
+                            if (orow[r] >= 0) orp[r][xo * cstride] = pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r];
             }
         };
         const int wave_u = __builtin_amdgcn_readfirstlane(wave);

@@ -68,8 +68,29 @@ struct VRows {
     __device__ __forceinline__ bf16x8 second(int p) const {
         return __builtin_bit_cast(bf16x8, (u32x4){pa[p][2], pa[p][3], pb[p][2], pb[p][3]});
     }
+    // The same operands in place: entry a's second component and entry b's first change places (two exchanges where the
+    // operands put together above take eight moves).
+    __device__ __forceinline__ void swap(int p) {
+        unsigned a2 = pa[p][2], a3 = pa[p][3], b0 = pb[p][0], b1 = pb[p][1];
+        // (the two idle cycles are what a matrix instruction needs behind a vector instruction that wrote its operand; the
+        // compiler does not see into the statement and would not leave them)
+        asm("v_swap_b32 %0, %2\n\tv_swap_b32 %1, %3\n\ts_nop 1" : "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1));
+        pa[p] = (u32x4){pa[p][0], pa[p][1], a2, a3};
+        pb[p] = (u32x4){b0, b1, pb[p][2], pb[p][3]};
+    }
+    __device__ __forceinline__ bf16x8 swapped_first(int p) const { return __builtin_bit_cast(bf16x8, pa[p]); }
+    __device__ __forceinline__ bf16x8 swapped_second(int p) const { return __builtin_bit_cast(bf16x8, pb[p]); }
 };
 
+// A value the optimizer knows nothing about: what is computed from it is not moved out of a loop.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ int opaque_uniform(int x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
 __device__ __forceinline__ float read_lane(float x, int src_lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src_lane));
 }
