@@ -545,17 +545,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             // follow they stay in LDS instead of being held, and spilled, across the loop)
             int gx_lane = lane;
             asm volatile("" : "+v"(gx_lane));
-            auto u_phase = [&](int first, int count) {
+            // The operands of a step are read from LDS while the step before is multiplied, and a step's rows are replaced by
+            // those that its registers hold next as soon as it has been (left to itself the compiler reads an operand, waits for
+            // it and multiplies, 39 times a chunk: half of a wave's time).
+            bf16x8 gxb[2][3];
+            auto operands = [&](int step) {
 #pragma unroll
-                for (int s = 0; s < VP; ++s)
+                for (int mu = 0; mu < 3; ++mu) gxb[step & 1][mu] = __builtin_bit_cast(bf16x8, s_GX[(mu * VS + step) * 64 + gx_lane]);
+            };
+            auto u_phase = [&](int first, int count, int next_chunk, int next_first, int next_count) {
+                size_t off[2];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+                    off[mt] = e2f::k16_offset(4 * (size_t)((unsigned)s_ent[8 * next_chunk + 4 * mt + (tn >> 2)] >> 8) + (tn & 3), H, head, VKP, 8 * g);
+#pragma unroll
+                for (int s = 0; s < VP; ++s) {
                     if (s < count) {
+                        if (first + s + 1 < VS) operands(first + s + 1);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int mu = 0; mu < 3; ++mu) {
-                            const bf16x8 b = __builtin_bit_cast(bf16x8, s_GX[(mu * VS + first + s) * 64 + gx_lane]);
-                            U[mu][0] = mfma(X[0][s], b, U[mu][0]);
-                            U[mu][1] = mfma(X[1][s], b, U[mu][1]);
+                            U[mu][0] = mfma(X[0][s], gxb[(first + s) & 1][mu], U[mu][0]);
+                            U[mu][1] = mfma(X[1][s], gxb[(first + s) & 1][mu], U[mu][1]);
                         }
                     }
+                    if (s < next_count)
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) X[mt][s] = *reinterpret_cast<const bf16x8*>(rowsV + off[mt] + 128 * (next_first + s));
+                }
+                __builtin_amdgcn_sched_barrier(0);
             };
             // what depends on the pair's distance and logit alone: P_ij, the gate and the bias's derivative
             float p[8], phi[8], db[8];
@@ -578,13 +596,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     phi[u] = 0.5f + 0.5f * __builtin_amdgcn_cosf(d * rev);
                 }
             };
-            u_phase(0, VP);
-            load_X(c, VP, min(VP, VS - VP));
+            operands(0);
+            u_phase(0, VP, c, VP, min(VP, VS - VP));
             scalars(0);
-            u_phase(VP, min(VP, VS - VP));
-            load_X(c, 2 * VP, VS - 2 * VP);
+            u_phase(VP, min(VP, VS - VP), c, 2 * VP, VS - 2 * VP);
             scalars(1);
-            u_phase(2 * VP, VS - 2 * VP);
             // the candidates' k (q) rows, four slots of a group per lane, for the dq (dk) product; requested before the
             // next chunk's rows, so that waiting for them (loads complete in order) does not wait for those
             VRows<KS> y4;
@@ -595,7 +611,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int pp = 0; pp < KS; ++pp) y4.load_pair(pp, ba, bb);
             }
-            load_X(cn, 0, VP);
+            u_phase(2 * VP, VS - 2 * VP, cn, 0, VP);
             load_K(cn);
             // ---- ds and the position gradient
             float ds[8];
