@@ -460,7 +460,7 @@ static e2f_status forward_impl(e2f_ctx* ctx, const e2f_cells* cells, const float
     if (ev) E2F_HIP_CHECK(hipEventRecord(ev[0], st));
     if ((rc = e2f_launch_prepare(ctx, cells->view, pos, w, L, st)) != E2F_OK) return rc;
     if (ev) E2F_HIP_CHECK(hipEventRecord(ev[1], st));
-    if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, v_layout == 3 ? 0 : v_layout, st)) != E2F_OK) return rc;
+    if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, v_layout, st)) != E2F_OK) return rc;
     if (ev) E2F_HIP_CHECK(hipEventRecord(ev[2], st));
     if (tile_f32) {
         // candidate lists, the fp32 tile kernel for the tiles whose list fits, the ALU kernel for the atoms of the others

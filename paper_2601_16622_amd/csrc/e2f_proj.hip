@@ -385,110 +385,112 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && 
         if (s0 + u < n_steps) step(s0 + u, u);
 }
 
-// Weight-stationary projection for fp32 features (v_mfma_f32_16x16x4_f32), plain fp32 q, k, v.  The five fp32 weight
-// tiles of one 16-channel output tile are 160 registers at 128 channels, so the work of an (atom tiles, degree) item
-// is split between two kinds of waves: a QK wave keeps the four weight tiles of q and k for one output tile, a V wave
-// the value weights of VT output tiles; both do 4 C / 16 chains of C / 4 matrix instructions per slab.  Each streams
-// the slabs of h itself (PD in flight); the waves of one group of atom tiles go to one XCD, whose L2 serves the rows
-// they share.  Block -> (XCD, group of atom tiles, degree, wave of the item) as in k_project_ws.
+// fp32 features, 64 and 128 channels: a workgroup of C / 16 waves owns some atom tiles of one degree l; wave ct keeps the five
+// 16 x C weight tiles of its output channels in registers (160 of them at 128 channels) and the slabs of h (16 atoms x one
+// order m) go by, one 16-byte load per thread, requested two slabs ahead and shared through LDS.  Bound: the fp32 matrix
+// instruction, 160 of 32 cycles per slab and wave.  The per-tile kernel (k_project_mfma) has a wave fetch its weights for
+// every tile and wait for them with one or two waves to a SIMD: 62 us at 2 240 atoms, L = 2, 128 channels, where the
+// products are 21.  q and k come out with channels as rows (a lane holds four channels of an atom), v, with the operands
+// exchanged, with atoms as rows: the four slots of a group for one channel, which is how the tile kernel wants it.
+// qf, kf, vf: the fp32 tile kernel's layouts as well (or null), rows of absent slots of the last group as zeros.
+struct RowsF32Plan {
+    int first[E2F_MAX_L + 2];   // first workgroup of degree L - p, p = 0, 1, .. (the longest first), and the end
+    int tpw[E2F_MAX_L + 1];     // atom tiles per workgroup of that degree
+};
+constexpr int ROWS_TPW = 32;
 template <int C>
-__global__ __launch_bounds__(64) void k_project_ws_f32(E2fCellsView cv, const float* __restrict__ h,
-                                                       const float* __restrict__ WQ1, const float* __restrict__ WQ2,
-                                                       const float* __restrict__ WK1, const float* __restrict__ WK2,
-                                                       const float* __restrict__ WV, int L, int tpw,
-                                                       float* __restrict__ q, float* __restrict__ k, float* __restrict__ v) {
-    typedef Frag<float> F;
-    constexpr int NS = C / F::KSTEP, NCT = C / 16, VT = 4, NVW = NCT / VT;   // V waves per item
-    static_assert(NCT % VT == 0, "value waves take four output tiles each");
-    const int N = cv.N, n = (L + 1) * (L + 1), n_tiles = (N + 15) / 16;
-    const int per_group = (L + 1) * (NCT + NVW);
-    const int xcd = blockIdx.x & 7, rest = blockIdx.x >> 3;
-    const int group = (rest / per_group) * 8 + xcd, lw = rest % per_group;
-    const int l = lw / (NCT + NVW), wv = lw % (NCT + NVW), nl = 2 * l + 1;
-    const bool value_wave = wv >= NCT;                 // (uniform)
-    const int ct0 = value_wave ? (wv - NCT) * VT : wv;   // first output tile of this wave
-    const int lane = threadIdx.x, j = lane & 15, g = lane >> 4;
-    const int tile0 = group * tpw, tile1 = min(tile0 + tpw, n_tiles);
-    if (tile0 >= tile1) return;
-    // four stationary weight tiles: (WQ1, WQ2, WK1, WK2) of output tile ct0, or WV of output tiles ct0 .. ct0 + 3
-    F::type Wf[4][NS];
+__global__ __launch_bounds__(4 * C) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_rows_f32(
+    E2fCellsView cv, const float* __restrict__ h, const float* __restrict__ WQ1, const float* __restrict__ WQ2, const float* __restrict__ WK1,
+    const float* __restrict__ WK2, const float* __restrict__ WV, int L, RowsF32Plan plan, float* __restrict__ q, float* __restrict__ k,
+    float* __restrict__ v, float* __restrict__ qf, float* __restrict__ kf, float* __restrict__ vf, float qscale) {
+    constexpr int NS = C / 16, ROW = C + 4;   // (rows four floats apart from each other's banks)
+    __shared__ __attribute__((aligned(16))) float s_x[2][16 * ROW];
+    __shared__ int s_atom[16 * ROWS_TPW];
+    int p = 0;
+    while (p < L && (int)blockIdx.x >= plan.first[p + 1]) ++p;
+    const int l = L - p, nl = 2 * l + 1, n = (L + 1) * (L + 1), N = cv.N, H = C / 16;
+    const int n_tiles = (N + 15) / 16;
+    const int tile0 = ((int)blockIdx.x - plan.first[p]) * plan.tpw[p], tiles = min(plan.tpw[p], n_tiles - tile0);
+    const int tid = threadIdx.x, ct = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i = lane & 15, g = lane >> 4;
+    for (int t = tid; t < 16 * tiles; t += 4 * C) s_atom[t] = cv.perm[min(tile0 * 16 + t, N - 1)];   // (clamped rows are computed and not stored)
+    f32x4 W[5][NS];
+    {
+        const size_t wr = ((size_t)l * C + ct * 16 + i) * C + 4 * g;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const float* W = value_wave ? WV : (t == 0 ? WQ1 : t == 1 ? WQ2 : t == 2 ? WK1 : WK2);
-        const size_t wrow = ((size_t)l * C + ((ct0 + (value_wave ? t : 0)) * 16 + j)) * C;
-#pragma unroll
-        for (int S = 0; S < NS; ++S) Wf[t][S] = F::load(W + wrow, S, g);
+        for (int S = 0; S < NS; ++S) {   // (in the order of their use)
+            W[0][S] = *reinterpret_cast<const f32x4*>(WQ1 + wr + 16 * S);
+            W[1][S] = *reinterpret_cast<const f32x4*>(WQ2 + wr + 16 * S);
+            W[2][S] = *reinterpret_cast<const f32x4*>(WK1 + wr + 16 * S);
+            W[3][S] = *reinterpret_cast<const f32x4*>(WK2 + wr + 16 * S);
+            W[4][S] = *reinterpret_cast<const f32x4*>(WV + wr + 16 * S);
+        }
     }
-    auto load_x = [&](int tile, int m, F::type (&X)[NS]) {
-        const int slot = min(tile * 16 + j, N - 1);  // clamped atoms are computed and not stored
-        const float* row = h + ((size_t)cv.perm[slot] * n + l * l + m) * C;
-#pragma unroll
-        for (int S = 0; S < NS; ++S) X[S] = F::load(row, S, g);
+    __syncthreads();
+    const int slabs = tiles * nl, row = tid / (C / 4), c4 = tid % (C / 4);
+    int ft = 0, fm = 0;   // tile and order of the slab to fetch next
+    auto fetch = [&]() -> f32x4 {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(h + ((size_t)s_atom[ft * 16 + row] * n + l * l + fm) * C + 4 * c4);
+        if (++fm == nl) {
+            fm = 0;
+            if (ft + 1 < tiles) ++ft;   // (past the last slab: its own tile again, not used)
+        }
+        return x;
     };
-    {   // the weights have arrived before the stream starts: inside it only the ring's own loads are in flight
-        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int S = 0; S < NS; ++S) asm volatile("" ::"v"(__builtin_bit_cast(u32x4, Wf[t][S])));
-    }
-    constexpr int PD = 2;
-    const int n_steps = (tile1 - tile0) * nl;
-    F::type X[PD][NS];
-#pragma unroll
-    for (int u = 0; u < PD; ++u) {
-        const int su = min(u, n_steps - 1);
-        load_x(tile0 + su / nl, su % nl, X[u]);
-    }
+    auto put = [&](int buf, const f32x4& x) { *reinterpret_cast<f32x4*>(&s_x[buf][row * ROW + 4 * c4]) = x; };
     f32x4 qacc = {0.f, 0.f, 0.f, 0.f}, kacc = {0.f, 0.f, 0.f, 0.f};
-    // (full groups of PD steps without a check per step: the compiler sets its waits on the ring's loads by the fewest
-    // memory instructions on any path from a request to its use, and a path that skips steps would make that one)
-    auto step = [&](int st, int u) __attribute__((always_inline)) {
-        const int tile = tile0 + st / nl, m = st % nl;
-        const int slot = tile * 16 + j;
-        // four independent chains, interleaved so that no matrix instruction waits for its predecessor
-        f32x4 p[4];
+    int t = 0, m = 0;
+    auto slab = [&](int buf) {
+        f32x4 pr[5];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) p[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < 5; ++w) pr[w] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int S = 0; S < NS; ++S)
+        for (int S = 0; S < NS; ++S) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(&s_x[buf][i * ROW + 16 * S + 4 * g]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    p[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(Wf[t][S][e], X[u][S][e], p[t], 0, 0, 0);
-        {   // this buffer is free again: request the slab PD steps ahead (clamped to the last step)
-            const int sn = min(st + PD, n_steps - 1);
-            load_x(tile0 + sn / nl, sn % nl, X[u]);
+                for (int w = 0; w < 4; ++w) pr[w] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[w][S][e], x[e], pr[w], 0, 0, 0);
+                pr[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], W[4][S][e], pr[4], 0, 0, 0);
+            }
         }
-        // accumulator layout: lane (g, j) holds output channels 4g .. 4g + 3 of atom j
-        if (value_wave) {
-            if (slot < N) {
-                float* dst = v + ((size_t)slot * n + l * l + m) * C + ct0 * 16 + 4 * g;
+        qacc += pr[0] * pr[1];
+        kacc += pr[2] * pr[3];
+        const int slot0 = (tile0 + t) * 16, comp = l * l + m;
+        // v: atoms 4g + r, channel i
 #pragma unroll
-                for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(dst + 16 * t) = p[t];
+        for (int r = 0; r < 4; ++r)
+            if (slot0 + 4 * g + r < N) v[((size_t)(slot0 + 4 * g + r) * n + comp) * C + ct * 16 + i] = pr[4][r];
+        if (vf && slot0 + 4 * g < N) {
+            f32x4 four;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) four[r] = slot0 + 4 * g + r < N ? pr[4][r] : 0.0f;
+            *reinterpret_cast<f32x4*>(vf + (((size_t)(slot0 / 4 + g) * H + ct) * n + comp) * 64 + i * 4) = four;
+        }
+        if (++m == nl) {   // the tile's last order: q and k, channels 4g .. 4g + 3 of atom i
+            const int slot = slot0 + i;
+            const size_t at = ((size_t)slot * (L + 1) + l) * C + ct * 16 + 4 * g;
+            if (slot < N) {
+                *reinterpret_cast<f32x4*>(q + at) = qacc;
+                *reinterpret_cast<f32x4*>(k + at) = kacc;
+                if (qf) *reinterpret_cast<f32x4*>(qf + ((size_t)slot * H + ct) * (16 * (L + 1)) + l * 16 + 4 * g) = qacc * qscale;
             }
-        } else {
-            qacc += p[0] * p[1];
-            kacc += p[2] * p[3];
-            if (m == nl - 1) {   // last order of this atom tile: q and k of the degree go out
-                if (slot < N) {
-                    *reinterpret_cast<f32x4*>(q + ((size_t)slot * (L + 1) + l) * C + ct0 * 16 + 4 * g) = qacc;
-                    *reinterpret_cast<f32x4*>(k + ((size_t)slot * (L + 1) + l) * C + ct0 * 16 + 4 * g) = kacc;
-                }
-                qacc = (f32x4){0.f, 0.f, 0.f, 0.f};
-                kacc = (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
+            if (kf && slot < (N + 3) / 4 * 4)
+                *reinterpret_cast<f32x4*>(kf + (((size_t)(slot >> 2) * H + ct) * 4 + (slot & 3)) * (16 * (L + 1)) + l * 16 + 4 * g) =
+                    slot < N ? kacc : (f32x4){0.f, 0.f, 0.f, 0.f};
+            qacc = kacc = (f32x4){0.f, 0.f, 0.f, 0.f};
+            m = 0;
+            ++t;
         }
     };
-    int s0 = 0;
-    for (; s0 + PD <= n_steps; s0 += PD) {
-#pragma unroll
-        for (int u = 0; u < PD; ++u) step(s0 + u, u);
+    put(0, fetch());
+    f32x4 next = fetch();
+    __syncthreads();
+    for (int s = 0; s < slabs; ++s) {
+        put((s + 1) & 1, next);
+        next = fetch();
+        slab(s & 1);
+        __syncthreads();
     }
-#pragma unroll
-    for (int u = 0; u < PD; ++u)
-        if (s0 + u < n_steps) step(s0 + u, u);
 }
 
 // Workgroup variant of the weight-stationary projection for the tiled v layout.  Global stores inside the
@@ -992,34 +994,46 @@ bool launch_ws(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const 
     }
 }
 
+// Tiles per workgroup by degree: as many slabs to every workgroup as the estimate likes best (a workgroup costs its slabs and
+// about one more for its weights; up to one round of workgroups the longest decides, beyond it the sum and half a tail).
 template <int C>
-bool launch_ws_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                   hipStream_t st) {
-    const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16;
-    // more tiles per wave fetch the weights less often; keep two rounds of waves for the chip (2048 fit at a time)
-    const int per_group = (L + 1) * (C / 16 + C / 64);
-    int tpw = 4;
-    while (tpw > 1 && (n_tiles + tpw - 1) / tpw * per_group < 4096) tpw >>= 1;
-    const int groups = (n_tiles + tpw - 1) / tpw;
-    const int blocks = ((groups + 7) / 8) * per_group * 8;
-    k_project_ws_f32<C><<<blocks, 64, 0, st>>>(cv, (const float*)h, (const float*)w->WQ1, (const float*)w->WQ2,
-                                               (const float*)w->WK1, (const float*)w->WK2, (const float*)w->WV, L, tpw,
-                                               ws.q, ws.k, (float*)ws.v);
-    return true;
-}
-bool dispatch_ws_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                     hipStream_t st) {
-    // While the features fit the caches the per-tile kernel, which fetches its weights per wave, is a little faster
-    // (0.29 against 0.33 ms at 6000 atoms, 128 channels, L = 4: 77 MB of features).  The line was drawn where its four-tile
-    // form fell off (0.93 against 0.42 ms at 8000 atoms), for the scratch memory it used then; without that it takes 0.34
-    // against 0.39 at 8000 and 0.80 against 0.87 at 20 000, so there is no longer a size here where this one is ahead at 128
-    // channels; at 64 it is from 20 000 atoms on (0.250 / 0.257).
-    if ((long long)cv.N * ctx->n * ctx->cfg.C * 4 < (80ll << 20)) return false;
-    switch (ctx->cfg.C) {
-        case 64: return launch_ws_f32<64>(ctx, cv, h, w, ws, st);
-        case 128: return launch_ws_f32<128>(ctx, cv, h, w, ws, st);
+void launch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts) {
+    const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16, at_once = 256 * 128 / C;
+    RowsF32Plan best;
+    float least = 0.0f;
+    for (int want = 1; want <= 40; ++want) {
+        RowsF32Plan plan;
+        int first = 0, longest = 0;
+        float sum = 0.0f;
+        for (int p = 0; p <= L; ++p) {
+            const int nl = 2 * (L - p) + 1;
+            int tpw = want / nl > 1 ? want / nl : 1;
+            if (tpw > ROWS_TPW) tpw = ROWS_TPW;
+            if (tpw > n_tiles) tpw = n_tiles;
+            const int wgs = (n_tiles + tpw - 1) / tpw;
+            plan.first[p] = first;
+            plan.tpw[p] = tpw;
+            first += wgs;
+            if (tpw * nl > longest) longest = tpw * nl;
+            sum += (float)n_tiles * nl + wgs;
+        }
+        plan.first[L + 1] = first;
+        const float cost = first <= at_once ? longest + 1.0f : sum / at_once + 0.5f * (longest + 1);
+        if (want == 1 || cost < least) {
+            least = cost;
+            best = plan;
+        }
     }
-    return false;
+    k_project_rows_f32<C><<<best.first[L + 1], 4 * C, 0, st>>>(cv, (const float*)h, (const float*)w->WQ1, (const float*)w->WQ2, (const float*)w->WK1,
+                                                              (const float*)w->WK2, (const float*)w->WV, L, best, ws.q, ws.k, (float*)ws.v,
+                                                              tile_layouts ? ws.qf : nullptr, tile_layouts ? ws.kf : nullptr,
+                                                              tile_layouts ? ws.vf : nullptr, ctx->tau * 1.44269504088896341f);
+}
+bool dispatch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts) {
+    if (!e2f_f32_layouts_direct(ctx->cfg.C, cv.N)) return false;
+    if (ctx->cfg.C == 64) launch_rows_f32<64>(ctx, cv, h, w, ws, st, tile_layouts);
+    else launch_rows_f32<128>(ctx, cv, h, w, ws, st, tile_layouts);
+    return true;
 }
 
 // 256 channels into the tile layouts: four workgroups of four computing waves per (atom tiles, degree).
@@ -1189,7 +1203,7 @@ e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, c
         ok = (tiled_v && dispatch_wg(ctx, cv, h, w, ws, st, 1)) || dispatch_ws(ctx, cv, h, w, ws, st, tiled_v) ||
              dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, tiled_v);
     else
-        ok = dispatch_ws_f32(ctx, cv, h, w, ws, st) || dispatch_mfma<float>(ctx, cv, h, w, ws, st, false);
+        ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3) || dispatch_mfma<float>(ctx, cv, h, w, ws, st, false);
     if (!ok) return E2F_ERR_UNSUPPORTED;
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;

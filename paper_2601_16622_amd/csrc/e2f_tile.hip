@@ -515,21 +515,7 @@ __device__ __forceinline__ void tile_item(const TileParams& P, const int tile, c
                         const float f = move ? __builtin_amdgcn_exp2f(m_ref - gmax) : 1.0f;
                         m_ref = move ? gmax : m_ref;
                         z *= f;
-                        // Rows of the accumulators are targets: T <- diag(f) T on the matrix cores in fp32.  Slice r
-                        // pairs A_r[i][g] = f_i [i == 4g + r] with B_r[g][j] = T[4g + r][j], register r of lane (j, g).
-                        float ar[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) ar[r] = tn == 4 * g + r ? f : 0.0f;
-#pragma unroll
-                        for (int mu = 0; mu < 3; ++mu)
-#pragma unroll
-                            for (int x = 0; x < NS; ++x) {
-                                f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                                for (int r = 0; r < 4; ++r)
-                                    d = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[r], acc[mu][x][r], d, 0, 0, 0);
-                                acc[mu][x] = d;
-                            }
+                        rescale_rows(acc, f, g);
                     }
                     // ---- weights of this wave's chunk -> LDS
                     {
@@ -882,16 +868,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const float f = move ? __builtin_amdgcn_exp2f(m_ref - gmax) : 1.0f;
                 m_ref = move ? gmax : m_ref;
                 z *= f;
-                // Rows of the accumulators are targets: register r of lane (j, g) is row 4g + r.  (A quarter of the items move a
-                // reference; as a product with diag(f) on the fp32 matrix instruction a move took 336 instructions of 32 cycles.)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float fr = __shfl(f, 4 * g + r);
-#pragma unroll
-                    for (int mu = 0; mu < 3; ++mu)
-#pragma unroll
-                        for (int x = 0; x < NS; ++x) acc[mu][x][r] *= fr;
-                }
+                rescale_rows(acc, f, g);
             }
             // ---- weights of this wave's chunk -> LDS
             {
@@ -958,14 +935,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             first_rows(head + 1);
         }
         // ---- epilogue: out = (1/z) sum_mu G_mu T_mu.  For one mu at a time the waves put their T_mu components into
-        // LDS and every wave forms the output components x_out = wave (mod NW) from the non-zero entries of G_mu.  The
+        // LDS and every wave forms the output components of its class (axis_class) from the non-zero entries of G_mu.  The
         // code exists once per wave index, so that a wave's components and the pattern are compile-time facts.
         z += __shfl_xor(z, 16);
         z += __shfl_xor(z, 32);
         if (lane < 16) s_z[wave][lane] = z;
         auto finish = [&](auto wv_tag) {
             constexpr int WV = decltype(wv_tag)::value;
-            constexpr uint32_t XO = E2F_AXIS_WAVES[L - 1][WV];               // this wave's output components
+            constexpr uint32_t XO = axis_class(n, WV);                       // this wave's output components
             constexpr int RO = __builtin_popcount(XO);
             constexpr int X0 = WV * (n / NW) + (WV < n % NW ? WV : n % NW);  // this wave's accumulator components
             constexpr int NXW = n / NW + (WV < n % NW ? 1 : 0);

@@ -250,20 +250,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             const float f = move ? __builtin_amdgcn_exp2f(m_ref - gmax) : 1.0f;
             m_ref = move ? gmax : m_ref;
             z *= f;
-            // rows of the accumulators are targets: T <- diag(f) T, slice r pairs A_r[i][g] = f_i [i == 4g + r] with
-            // B_r[g][j] = T[4g + r][j]
-            float ar[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ar[r] = tn == 4 * g + r ? f : 0.0f;
-#pragma unroll
-            for (int mu = 0; mu < 3; ++mu)
-#pragma unroll
-                for (int x = 0; x < NX; ++x) {
-                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) d = mfma32(ar[r], acc[mu][x][r], d);
-                    acc[mu][x] = d;
-                }
+            rescale_rows(acc, f, g);
         }
         // ---- weights of this wave's chunk -> LDS
 #pragma unroll
@@ -373,7 +360,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int L>
 void launch_L(const TileF32Params& P, hipStream_t st) {
     const int grid = tile_grid(P.n_tiles, P.blk, P.H);
-    k_f32_relayout<L><<<(P.cv.N + 3) / 4, 256, 0, st>>>(P);
+    if (!e2f_f32_layouts_direct(P.C, P.cv.N)) k_f32_relayout<L><<<(P.cv.N + 3) / 4, 256, 0, st>>>(P);
 #ifndef E2F_F32_NW
 #define E2F_F32_NW 4
 #endif

@@ -105,6 +105,21 @@ __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
+// T <- diag(f) T for accumulators whose rows are targets: register r of lane (j, g) is row 4g + r, f the factor of target
+// lane % 16.  (A quarter of the bf16 kernel's items move a reference; as products with diag(f) on the fp32 matrix instruction
+// a move took 336 instructions of 32 cycles, 10 000 atoms 312 -> 294 us a forward pass without them.)
+template <int NS>
+__device__ __forceinline__ void rescale_rows(f32x4 (&acc)[3][NS], float f, int g) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float fr = __shfl(f, 4 * g + r);
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu)
+#pragma unroll
+            for (int x = 0; x < NS; ++x) acc[mu][x][r] *= fr;
+    }
+}
+
 // Radial bias of a head, b(d) = sum_b Wb[b] exp(-gamma (d - b step)^2), in base-2 units, evaluated per pair from NB
 // coefficients that every lane holds (uniform).  Up to 8 basis functions: a polynomial in u = e^{2 gamma step d},
 //     b(d) = e^{-gamma d^2} sum_b cb[b] u^b ,       cb[b] = Wb[b] e^{-gamma (b step)^2} log2 e .
@@ -227,6 +242,19 @@ constexpr AxisIndex AXIS_INDEX{};
 constexpr int AXIS_NNZ = AXIS_INDEX.count;
 static_assert(AXIS_NNZ == 216, "the pattern of the degree-1 axis operators at L_max = 4");
 constexpr int AXIS_PACKED_AT = 3 * E2F_MAX_N * E2F_MAX_N;   // the packed list follows the full operators
+
+// Output components dealt to four waves by the parity of |m| and by whether m < 0 goes with an even or an odd degree: each of
+// the three axis operators takes one of these classes to exactly one other, so that no two waves read the same row of T_mu
+// (75 rows in all at L = 4; dealt out in turn the waves read 142).
+constexpr uint32_t axis_class(int n, int cls) {
+    uint32_t set = 0;
+    for (int x = 0, l = 0; x < n; ++x) {
+        if (x == (l + 1) * (l + 1)) ++l;
+        const int m = x - l * l - l;
+        if (2 * (m & 1 ? 1 : 0) + ((m < 0) != ((l & 1) != 0) ? 1 : 0) == cls) set |= 1u << x;
+    }
+    return set;
+}
 
 // The axis operators with unit path weights, packed (e2f_ctx::axis_unit): an argument of the kernels that need them.  An
 // entry belongs to one path, so the operators of a call are these numbers times its path weights.
