@@ -93,6 +93,10 @@ struct MapWeights {
 
 // WT[k][l][ci][co] = W_k[l][co][ci], so that the transposed products of bf16 features read their weights by rows too (a
 // fragment is eight of them); one workgroup per (k, l, 16 x 16 tile).
+// FRAG: the elements of a map and degree in the order in which k_bwd_rows takes them, block [32 rows][16 columns] by block, a
+// block as the 64 lanes' eight elements one behind the other: a fragment is then 1 KB in one piece, where by rows it is 32
+// pieces of 32 bytes, each in a cache line of its own.
+template <bool FRAG>
 __global__ __launch_bounds__(256) void k_transpose_weights(MapWeights<uint16_t> mw, int L1, int C, uint16_t* __restrict__ WT) {
     __shared__ uint16_t s[16][17];
     const int tiles = C / 16, t = blockIdx.x % (tiles * tiles), kl = blockIdx.x / (tiles * tiles);
@@ -101,7 +105,13 @@ __global__ __launch_bounds__(256) void k_transpose_weights(MapWeights<uint16_t> 
     const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     s[r][c] = W[((size_t)l * C + 16 * tr + r) * C + 16 * tc + c];
     __syncthreads();
-    WT[(((size_t)k * L1 + l) * C + 16 * tc + r) * C + 16 * tr + c] = s[c][r];
+    uint16_t* out = WT + ((size_t)k * L1 + l) * C * C;
+    if constexpr (FRAG) {   // row 16 tc + r', columns 16 tr ..: thread -> (half of the columns, row, column)
+        const int hf = threadIdx.x >> 7, rr = (threadIdx.x >> 3) & 15, x = threadIdx.x & 7;
+        out[(((size_t)(tc >> 1) * tiles + tr) * 64 + hf * 32 + (tc & 1) * 16 + rr) * 8 + x] = s[8 * hf + x][rr];
+    } else {
+        out[(size_t)(16 * tc + r) * C + 16 * tr + c] = s[c][r];
+    }
 }
 
 // Workgroups [first[d], first[d + 1]) own the rows of degree L - d, the degree with the most rows first.
@@ -119,7 +129,7 @@ struct DegreeMap {
 // Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
 // the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
 // one-thread-per-channel kernel on the vector ALUs in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4
-// x 256: 349 us (2 818; one bf16 a factor would take 189 us, at the loss stated at H_PARTS).  Up to 128 bf16 channels it
+// x 256: 271 us (2 818; one bf16 a factor would take less, at the loss stated at H_PARTS).  Up to 128 bf16 channels it
 // has the smaller calls, see k_bwd_rows_stationary.
 // CP: channels padded up to a multiple of 32 (PAD: C < CP; the missing ones read as zero).
 template <typename T, int CP, int RT, bool PAD>
@@ -158,6 +168,11 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
         const int kt = st == 0 ? 4 : (st - 2) / 2, row = 32 * w + i;
         const bool transposed = !(st & 1);
         const T* base = !transposed ? mw.W[((st - 1) / 2) ^ 1] + wl : EPF == 8 ? WT + kt * kstride + wl : mw.W[kt] + wl;
+        if (EPF == 8 && transposed) {   // in the order of the fragments (k_transpose_weights; bf16 features come in whole 32 channels)
+#pragma unroll
+            for (int f = 0; f < CF; ++f) dst[f] = *reinterpret_cast<const u32x4*>(base + ((size_t)(w * NF + c * CF + f) * 64 + lane) * 8);
+            return;
+        }
 #pragma unroll
         for (int f = 0; f < CF; ++f) {
             const int col = (c * CF + f) * 2 * EPF + EPF * hf;
@@ -204,33 +219,52 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
     auto frag = [&](const T* s, int rt, int f) {
         return *reinterpret_cast<const u32x4*>(s + (32 * rt + i) * ROW + 2 * EPF * f + EPF * hf);
     };
+    // The fragments of rows are read from LDS while those before them are multiplied (left to itself the compiler reads one, waits
+    // for it and multiplies: 345 us at 3 840 atoms, L = 4, 256 bf16 channels, where this takes 325, and 271 with the transposes in order).
+    u32x4 fr[2][PARTS][RT];
+    auto get = [&](const T* src, int parts, int f) {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p)
+            if (p < parts)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) fr[f & 1][p][rt] = frag(src + p * ROWS * ROW, rt, f);
+    };
 #pragma unroll
     for (int st = 0; st < 9; ++st) {
         if (st == 0 || !(st & 1)) {   // dx[row][channel 32 w + i] += sum over co of t[row][co] W[co][ci]
+            get(s_T, PARTS, 0);
 #pragma unroll
             for (int c = 0; c < CPS; ++c) {
                 const int q = st * CPS + c;
                 if (q + 1 < 9 * CPS) load_chunk(q + 1, buf[(q + 1) & 1]);
 #pragma unroll
-                for (int f = 0; f < CF; ++f)
+                for (int f = 0; f < CF; ++f) {
+                    const int at = c * CF + f;
+                    if (at + 1 < NF) get(s_T, PARTS, at + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int p = 0; p < PARTS; ++p)
 #pragma unroll
-                        for (int rt = 0; rt < RT; ++rt)
-                            dx[rt] = Mat<T>::mma32(frag(s_T + p * ROWS * ROW, rt, c * CF + f), buf[q & 1][f], dx[rt]);
+                        for (int rt = 0; rt < RT; ++rt) dx[rt] = Mat<T>::mma32(fr[at & 1][p][rt], buf[q & 1][f], dx[rt]);
+                }
             }
         } else {   // p[channel][row] of the map, then t
             f32x16 p[RT];
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) p[rt] = (f32x16)(0.0f);
+            get(s_X, 1, 0);
 #pragma unroll
             for (int c = 0; c < CPS; ++c) {
                 const int q = st * CPS + c;
                 if (q + 1 < 9 * CPS) load_chunk(q + 1, buf[(q + 1) & 1]);
 #pragma unroll
-                for (int f = 0; f < CF; ++f)
+                for (int f = 0; f < CF; ++f) {
+                    const int at = c * CF + f;
+                    if (at + 1 < NF) get(s_X, 1, at + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) p[rt] = Mat<T>::mma32(buf[q & 1][f], frag(s_X, rt, c * CF + f), p[rt]);
+                    for (int rt = 0; rt < RT; ++rt) p[rt] = Mat<T>::mma32(buf[q & 1][f], fr[at & 1][0][rt], p[rt]);
+                }
             }
             const float* g = st < 4 ? gq : gk;   // stages 1, 3: dq; 5, 7: dk
             __syncthreads();   // the factors of the map before have been read
@@ -370,12 +404,14 @@ __global__ __launch_bounds__(64 * (C / 16)) void k_bwd_rows_stationary(
         f32x4 p[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) p[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        bf16x8 X[NS];
 #pragma unroll
-        for (int S = 0; S < NS; ++S) {
-            const bf16x8 X = frag(&s_X[s & 1][i][32 * S + 8 * g]);
+        for (int S = 0; S < NS; ++S) X[S] = frag(&s_X[s & 1][i][32 * S + 8 * g]);
+        __builtin_amdgcn_sched_barrier(0);   // (all requested before any is waited for; see second_stage)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) p[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1[k][S], X, p[k], 0, 0, 0);
-        }
+        for (int S = 0; S < NS; ++S)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1[k][S], X[S], p[k], 0, 0, 0);
         // p[k][r] = (W_k x)[channel 16 ct + 4 g + r] of atom i
         f32x4 t[5];
         t[0] = dq * p[1];
@@ -422,13 +458,23 @@ __global__ __launch_bounds__(64 * (C / 16)) void k_bwd_rows_stationary(
             const int buf = s & 1;
             // (two partial sums: one accumulator would chain all the matrix instructions one after the other)
             f32x4 dp[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            // (the factors of a map are read from LDS while those of the map before are multiplied; left to itself the compiler
+            // reads one operand, waits for it and multiplies, 20 times a slab)
+            bf16x8 T[2][NS];
 #pragma unroll
-            for (int k = 0; k < 5; ++k)
+            for (int S = 0; S < NS; ++S) T[0][S] = frag(&s_T[buf][0][i][32 * S + 8 * g]);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                if (k < 4)
+#pragma unroll
+                    for (int S = 0; S < NS; ++S) T[(k + 1) & 1][S] = frag(&s_T[buf][k + 1][i][32 * S + 8 * g]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int S = 0; S < NS; ++S) {
                     const int j = (k * NS + S) & 1;
-                    dp[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[k][S], frag(&s_T[buf][k][i][32 * S + 8 * g]), dp[j], 0, 0, 0);
+                    dp[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[k][S], T[k & 1][S], dp[j], 0, 0, 0);
                 }
+            }
             const f32x4 dx = dp[0] + dp[1];
             // dx[r] = dL/dh[atom i][component][channel 16 ct + 4 g + r]
             const int atom = co.a0 + i;
@@ -684,11 +730,12 @@ template <typename T, int CP, bool PAD>
 void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const float* gk, const float* gv, float* gh,
               float* grad_W, float* part, int L, int C, int N, hipStream_t st) {
     if (gh) {
+        const long long rows = (long long)N * (L + 1) * (L + 1);
         if constexpr (sizeof(T) == 2) {
             const int t16 = C / 16;
-            k_transpose_weights<<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
+            if (CP <= 128 && rows * C >= STATIONARY_WORK) k_transpose_weights<false><<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
+            else k_transpose_weights<true><<<5 * (L + 1) * t16 * t16, 256, 0, st>>>(mw, L + 1, C, WT);
         }
-        const long long rows = (long long)N * (L + 1) * (L + 1);
         if constexpr (sizeof(T) == 2 && CP <= 128) {
             if (rows * C >= STATIONARY_WORK) launch_rows_stationary<CP>(mw, WT, h, gq, gk, gv, gh, L, N, st);
             else launch_rows<T, CP, 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
