@@ -458,9 +458,13 @@ static e2f_status forward_impl(e2f_ctx* ctx, const e2f_cells* cells, const float
     hipEvent_t* ev = (ctx->prof_events && ctx->prof_calls < ctx->prof_capacity)
                          ? ctx->prof_events + ctx->prof_calls * (E2F_N_STAGES + 1) : nullptr;
     if (ev) E2F_HIP_CHECK(hipEventRecord(ev[0], st));
-    if ((rc = e2f_launch_prepare(ctx, cells->view, pos, w, L, st)) != E2F_OK) return rc;
-    if (ev) E2F_HIP_CHECK(hipEventRecord(ev[1], st));
-    if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, v_layout, st)) != E2F_OK) return rc;
+    if (ev) {   // (the stages apart, to be timed)
+        if ((rc = e2f_launch_prepare(ctx, cells->view, pos, w, L, st)) != E2F_OK) return rc;
+        E2F_HIP_CHECK(hipEventRecord(ev[1], st));
+        if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, v_layout, st)) != E2F_OK) return rc;
+    } else if ((rc = e2f_launch_prepare_project(ctx, cells->view, pos, h, w, L, v_layout, st)) != E2F_OK) {
+        return rc;
+    }
     if (ev) E2F_HIP_CHECK(hipEventRecord(ev[2], st));
     if (tile_f32) {
         // candidate lists, the fp32 tile kernel for the tiles whose list fits, the ALU kernel for the atoms of the others
@@ -681,8 +685,7 @@ static e2f_status backward_impl(e2f_ctx* ctx, const e2f_cells* cells, const floa
     // (the forward pass of a configuration whose backward pass runs in tile form used the same layout of ws)
     const bool reuse = saved && tile && ctx->use_tile_attn && !(ctx->cfg.flags & E2F_FLAG_TILE_LISTS_PER_HEAD);
     if (!reuse) {
-        if ((rc = e2f_launch_prepare(ctx, cells->view, pos, w, L, st)) != E2F_OK) return rc;
-        if ((rc = e2f_launch_project_mfma(ctx, cells->view, h, w, L, v_layout, st)) != E2F_OK) return rc;
+        if ((rc = e2f_launch_prepare_project(ctx, cells->view, pos, h, w, L, v_layout, st)) != E2F_OK) return rc;
     }
     return e2f_launch_backward(ctx, cells->view, w, L, Bw, out, grad_out, grad_pos, grad_q, grad_k, grad_v, h, grad_h,
                                grad_Wb, grad_w_path, grad_W, tile ? &Tw : nullptr, st, reuse);

@@ -182,6 +182,9 @@ e2f_status e2f_launch_prepare(const e2f_ctx* ctx, const E2fCellsView& cv, const 
                               const E2fAttnWs& ws, hipStream_t st);
 e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
                                    const E2fAttnWs& ws, int v_layout, hipStream_t st);
+// The two together, in one launch where the projection kernel of the call takes the preparation along.
+e2f_status e2f_launch_prepare_project(const e2f_ctx* ctx, const E2fCellsView& cv, const float* pos, const void* h, const e2f_weights* w,
+                                      const E2fAttnWs& ws, int v_layout, hipStream_t st);
 bool e2f_factorized_supported(const e2f_ctx* ctx);
 e2f_status e2f_launch_factorized(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, const E2fFactWs& fw,
                                  float* out, hipStream_t st);

@@ -27,37 +27,46 @@ struct CoefTable {
     float c[E2F_MAX_N][E2F_NP];
 };
 
-// spos[slot] = position of the atom in that slot (w carries its index in the caller's order); cw[comp][t] = P coefficient times its path weight.
-__global__ void k_prepare(E2fCellsView cv, const float* __restrict__ pos, const float* __restrict__ w_path, int L,
-                          int lf, CoefTable tab, float4* __restrict__ spos, float* __restrict__ cw,
-                          const float* __restrict__ Wb, int H, int B, float* __restrict__ wbT, AxisTable axis, float* __restrict__ G) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// What a call prepares beside the projections: spos[slot] = position of the atom in that slot (w carries its index in the caller's
+// order), cw[comp][t] = P coefficient times its path weight, the transposed radial weights, the axis operators.  Nothing of it
+// depends on the projections or they on it, so that it rides in extra workgroups of their launch (first_block: the first of
+// them), 4 to 5 us a call; a launch of its own (k_prepare) where the projection kernel has none.
+struct PrepareArgs {
+    const float *pos, *w_path, *Wb;
+    float4* spos;
+    float *cw, *wbT, *G;
+    int lf, H, B, items;   // items 0: nothing to prepare here
+    CoefTable tab;
+    AxisTable axis;
+};
+__device__ __forceinline__ void prepare_item(const E2fCellsView& cv, const PrepareArgs& A, int L, int t) {
     // the axis operators of the tile kernels (one workgroup of the list kernel once formed them by the rotations, 17 us
     // at L = 4, longer than the lists of a small system)
-    if (G && t < AXIS_PACKED_AT + AXIS_NNZ) G[t] = axis_full_entry(axis, w_path, L, t);
-    if (t < H * B) wbT[(t % B) * H + t / B] = Wb[t];
+    if (A.G && t < AXIS_PACKED_AT + AXIS_NNZ) A.G[t] = axis_full_entry(A.axis, A.w_path, L, t);
+    if (t < A.H * A.B) A.wbT[(t % A.B) * A.H + t / A.B] = A.Wb[t];
     if (t < cv.N) {
         const int a = cv.perm[t];
-        float x = pos[3 * a], y = pos[3 * a + 1], z = pos[3 * a + 2];
+        float x = A.pos[3 * a], y = A.pos[3 * a + 1], z = A.pos[3 * a + 2];
         if (cv.periodic) {   // folded into the segment's box on its periodic axes
             const E2fSegGrid g = cv.grid[cv.sseg[t]];
             x = e2f::fold_coord(x, g.lx, g.rx);
             y = e2f::fold_coord(y, g.ly, g.ry);
             z = e2f::fold_coord(z, g.lz, g.rz);
         }
-        spos[t] = make_float4(x, y, z, __int_as_float(a));   // w: the atom index
+        A.spos[t] = make_float4(x, y, z, __int_as_float(a));   // w: the atom index
     }
     const int n = (L + 1) * (L + 1);
     if (t < n * E2F_NP) {
         const int comp = t / E2F_NP, kk = t % E2F_NP;
         int lo = 0;
         while ((lo + 1) * (lo + 1) <= comp) ++lo;
-        const int li = lo - lf + kk;
+        const int li = lo - A.lf + kk;
         float w = 0.0f;
-        if (kk <= 2 * lf && li >= 0 && li <= L) w = w_path[li * (L + 1) + lo];
-        cw[t] = w * tab.c[comp][kk];
+        if (kk <= 2 * A.lf && li >= 0 && li <= L) w = A.w_path[li * (L + 1) + lo];
+        A.cw[t] = w * A.tab.c[comp][kk];
     }
 }
+__global__ void k_prepare(E2fCellsView cv, int L, PrepareArgs A) { prepare_item(cv, A, L, blockIdx.x * blockDim.x + threadIdx.x); }
 
 template <typename T>
 struct Frag;
@@ -124,7 +133,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
-                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first) {
+                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first, PrepareArgs prep) {
+    if ((int)blockIdx.x >= (cv.N + 15) / 16) {   // (whole workgroup)
+        if (blockIdx.y == 0 && blockIdx.z == 0) prepare_item(cv, prep, L, ((int)blockIdx.x - (cv.N + 15) / 16) * 64 + threadIdx.x);
+        return;
+    }
     typedef Frag<T> F;
     constexpr int NS = C / F::KSTEP;
     const int tile = blockIdx.x, cg = longest_first ? blockIdx.y : blockIdx.z, l = longest_first ? L - (int)blockIdx.z : blockIdx.y;
@@ -402,7 +415,11 @@ template <int C>
 __global__ __launch_bounds__(4 * C) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_rows_f32(
     E2fCellsView cv, const float* __restrict__ h, const float* __restrict__ WQ1, const float* __restrict__ WQ2, const float* __restrict__ WK1,
     const float* __restrict__ WK2, const float* __restrict__ WV, int L, RowsF32Plan plan, float* __restrict__ q, float* __restrict__ k,
-    float* __restrict__ v, float* __restrict__ qf, float* __restrict__ kf, float* __restrict__ vf, float qscale) {
+    float* __restrict__ v, float* __restrict__ qf, float* __restrict__ kf, float* __restrict__ vf, float qscale, PrepareArgs prep) {
+    if ((int)blockIdx.x >= plan.first[L + 1]) {   // (whole workgroup)
+        prepare_item(cv, prep, L, ((int)blockIdx.x - plan.first[L + 1]) * 4 * C + threadIdx.x);
+        return;
+    }
     constexpr int NS = C / 16, ROW = C + 4;   // (rows four floats apart from each other's banks)
     __shared__ __attribute__((aligned(16))) float s_x[2][16 * ROW];
     __shared__ int s_atom[16 * ROWS_TPW];
@@ -703,7 +720,11 @@ __global__ __launch_bounds__(64 * (CW + 1)) void k_project_sh(E2fCellsView cv, c
                                                                  const uint16_t* __restrict__ WK1,
                                                                  const uint16_t* __restrict__ WK2,
                                                                  const uint16_t* __restrict__ WV, int L, int n_groups,
-                                                                 int tpw, WgGroupOut go) {
+                                                                 int tpw, WgGroupOut go, int first_block, PrepareArgs prep) {
+    if ((int)blockIdx.x >= first_block) {   // (whole workgroup)
+        prepare_item(cv, prep, L, ((int)blockIdx.x - first_block) * 64 * (CW + 1) + threadIdx.x);
+        return;
+    }
     typedef Frag<uint16_t> F;
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -930,7 +951,7 @@ __global__ void k_project_simple(E2fCellsView cv, const T* __restrict__ h, const
 
 template <typename T, int C>
 bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                 hipStream_t st, bool tiled) {
+                 hipStream_t st, bool tiled, const PrepareArgs& prep) {
     if constexpr (C % Frag<T>::KSTEP != 0) {
         return false;
     } else {
@@ -948,15 +969,16 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
             // waiting for weights, would have the chip to themselves at the end (128 channels, L = 2, 9 000 atoms 203 us
             // against 183; the four-tile form gains by the first order at every size it has).
             const bool longest_first = ct > 1 || C < 128 || few;
-            const dim3 grid = longest_first ? dim3(tiles, C / 16 / ct, L1) : dim3(tiles, L1, C / 16 / ct);
+            const int all = tiles + (prep.items + 63) / 64;
+            const dim3 grid = longest_first ? dim3(all, C / 16 / ct, L1) : dim3(all, L1, C / 16 / ct);
             if (tiled)
                 k_project_mfma<T, C, mg, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
+                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, prep);
             else
                 k_project_mfma<T, C, mg, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first);
+                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, prep);
         };
         // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2: 500 atoms 21 us
         // against 22.4, 2 286 atoms 61.7 / 63.5, but 9 000 atoms 199 / 185 and L = 4, 4 000 atoms 240 / 206)
@@ -997,7 +1019,8 @@ bool launch_ws(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const 
 // Tiles per workgroup by degree: as many slabs to every workgroup as the estimate likes best (a workgroup costs its slabs and
 // about one more for its weights; up to one round of workgroups the longest decides, beyond it the sum and half a tail).
 template <int C>
-void launch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts) {
+void launch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts,
+                     const PrepareArgs& prep) {
     const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16, at_once = 256 * 128 / C;
     RowsF32Plan best;
     float least = 0.0f;
@@ -1024,21 +1047,22 @@ void launch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, 
             best = plan;
         }
     }
-    k_project_rows_f32<C><<<best.first[L + 1], 4 * C, 0, st>>>(cv, (const float*)h, (const float*)w->WQ1, (const float*)w->WQ2, (const float*)w->WK1,
+    k_project_rows_f32<C><<<best.first[L + 1] + (prep.items + 4 * C - 1) / (4 * C), 4 * C, 0, st>>>(cv, (const float*)h, (const float*)w->WQ1, (const float*)w->WQ2, (const float*)w->WK1,
                                                               (const float*)w->WK2, (const float*)w->WV, L, best, ws.q, ws.k, (float*)ws.v,
                                                               tile_layouts ? ws.qf : nullptr, tile_layouts ? ws.kf : nullptr,
-                                                              tile_layouts ? ws.vf : nullptr, ctx->tau * 1.44269504088896341f);
+                                                              tile_layouts ? ws.vf : nullptr, ctx->tau * 1.44269504088896341f, prep);
 }
-bool dispatch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts) {
+bool dispatch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts,
+                       const PrepareArgs& prep) {
     if (!e2f_f32_layouts_direct(ctx->cfg.C, cv.N)) return false;
-    if (ctx->cfg.C == 64) launch_rows_f32<64>(ctx, cv, h, w, ws, st, tile_layouts);
-    else launch_rows_f32<128>(ctx, cv, h, w, ws, st, tile_layouts);
+    if (ctx->cfg.C == 64) launch_rows_f32<64>(ctx, cv, h, w, ws, st, tile_layouts, prep);
+    else launch_rows_f32<128>(ctx, cv, h, w, ws, st, tile_layouts, prep);
     return true;
 }
 
 // 256 channels into the tile layouts: four workgroups of four computing waves per (atom tiles, degree).
 bool launch_sh256(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                  hipStream_t st) {
+                  hipStream_t st, const PrepareArgs& prep) {
     const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16;
     WgGroupOut go;
     go.q16 = ws.q16; go.k16 = ws.k16; go.v4 = ws.v4;
@@ -1047,15 +1071,16 @@ bool launch_sh256(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, con
     int tpw = SH_TPW;
     while (tpw > 4 && (n_tiles + tpw - 1) / tpw * (L + 1) < 384) tpw >>= 1;
     const int n_groups = (n_tiles + tpw - 1) / tpw;
-    k_project_sh<256, 4><<<(n_groups + 7) / 8 * 8 * 4 * (L + 1), 64 * 5, 0, st>>>(
+    const int blocks = (n_groups + 7) / 8 * 8 * 4 * (L + 1);
+    k_project_sh<256, 4><<<blocks + (prep.items + 64 * 5 - 1) / (64 * 5), 64 * 5, 0, st>>>(
         cv, (const uint16_t*)h, (const uint16_t*)w->WQ1, (const uint16_t*)w->WQ2, (const uint16_t*)w->WK1,
-        (const uint16_t*)w->WK2, (const uint16_t*)w->WV, L, n_groups, tpw, go);
+        (const uint16_t*)w->WK2, (const uint16_t*)w->WV, L, n_groups, tpw, go, blocks, prep);
     return true;
 }
 
 template <int C>
 bool launch_wg(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-               hipStream_t st, int v_layout) {
+               hipStream_t st, int v_layout, const PrepareArgs& prep) {
     if constexpr (C % 32 != 0 || C > 128) {
         return false;
     } else {
@@ -1085,9 +1110,10 @@ bool launch_wg(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const 
             int tpw = SH_TPW;
             while (tpw > 4 && (n_tiles + tpw - 1) / tpw * (L + 1) < 384) tpw >>= 1;
             const int n_groups = (n_tiles + tpw - 1) / tpw;
-            k_project_sh<C><<<n_groups * (L + 1), 64 * (C / 16 + 1), 0, st>>>(
+            constexpr int THREADS = 64 * (C / 16 + 1);
+            k_project_sh<C><<<n_groups * (L + 1) + (prep.items + THREADS - 1) / THREADS, THREADS, 0, st>>>(
                 cv, (const uint16_t*)h, (const uint16_t*)w->WQ1, (const uint16_t*)w->WQ2, (const uint16_t*)w->WK1,
-                (const uint16_t*)w->WK2, (const uint16_t*)w->WV, L, n_groups, tpw, go);
+                (const uint16_t*)w->WK2, (const uint16_t*)w->WV, L, n_groups, tpw, go, n_groups * (L + 1), prep);
         } else if (v_layout == 2)
             k_project_wg<C, 2><<<blocks, 64 * WG_WAVES, 0, st>>>(cv, (const uint16_t*)h, (const uint16_t*)w->WQ1,
                                                                 (const uint16_t*)w->WQ2, (const uint16_t*)w->WK1,
@@ -1103,11 +1129,11 @@ bool launch_wg(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const 
 }
 
 bool dispatch_wg(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                 hipStream_t st, int v_layout) {
+                 hipStream_t st, int v_layout, const PrepareArgs& prep) {
     switch (ctx->cfg.C) {
-        case 32: return launch_wg<32>(ctx, cv, h, w, ws, st, v_layout);
-        case 64: return launch_wg<64>(ctx, cv, h, w, ws, st, v_layout);
-        case 128: return launch_wg<128>(ctx, cv, h, w, ws, st, v_layout);
+        case 32: return launch_wg<32>(ctx, cv, h, w, ws, st, v_layout, prep);
+        case 64: return launch_wg<64>(ctx, cv, h, w, ws, st, v_layout, prep);
+        case 128: return launch_wg<128>(ctx, cv, h, w, ws, st, v_layout, prep);
     }
     return false;
 }
@@ -1125,31 +1151,39 @@ bool dispatch_ws(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
 
 template <typename T>
 bool dispatch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
-                   const E2fAttnWs& ws, hipStream_t st, bool tiled) {
+                   const E2fAttnWs& ws, hipStream_t st, bool tiled, const PrepareArgs& prep) {
     switch (ctx->cfg.C) {
-        case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, tiled);
-        case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, tiled);
-        case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, tiled);
-        case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled);
-        case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, tiled);
-        case 192: return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, tiled);
-        case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, tiled);
+        case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 192: return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, tiled, prep);
     }
     return false;
 }
 
 }  // namespace
 
+static PrepareArgs prepare_args(const e2f_ctx* ctx, const E2fCellsView& cv, const float* pos, const e2f_weights* w, const E2fAttnWs& ws) {
+    PrepareArgs A;
+    A.pos = pos; A.w_path = w->w_path; A.Wb = w->Wb;
+    A.spos = ws.spos; A.cw = ws.cw; A.wbT = ws.wbT; A.G = ws.G;
+    A.lf = ctx->cfg.lf; A.H = ctx->cfg.H; A.B = ctx->cfg.B;
+    for (int x = 0; x < E2F_MAX_N; ++x)
+        for (int t = 0; t < E2F_NP; ++t) A.tab.c[x][t] = ctx->coefP[x][t];
+    A.axis = axis_table(ctx);
+    A.items = cv.N > ctx->n * E2F_NP ? cv.N : ctx->n * E2F_NP;
+    if (A.H * A.B > A.items) A.items = A.H * A.B;
+    if (ws.G && AXIS_PACKED_AT + AXIS_NNZ > A.items) A.items = AXIS_PACKED_AT + AXIS_NNZ;
+    return A;
+}
+
 e2f_status e2f_launch_prepare(const e2f_ctx* ctx, const E2fCellsView& cv, const float* pos, const e2f_weights* w,
                               const E2fAttnWs& ws, hipStream_t st) {
-    CoefTable tab;
-    for (int x = 0; x < E2F_MAX_N; ++x)
-        for (int t = 0; t < E2F_NP; ++t) tab.c[x][t] = ctx->coefP[x][t];
-    int work = cv.N > ctx->n * E2F_NP ? cv.N : ctx->n * E2F_NP;
-    if (ctx->cfg.H * ctx->cfg.B > work) work = ctx->cfg.H * ctx->cfg.B;
-    if (ws.G && AXIS_PACKED_AT + AXIS_NNZ > work) work = AXIS_PACKED_AT + AXIS_NNZ;
-    k_prepare<<<(work + 255) / 256, 256, 0, st>>>(cv, pos, w->w_path, ctx->cfg.L_max, ctx->cfg.lf, tab, ws.spos, ws.cw,
-                                                 w->Wb, ctx->cfg.H, ctx->cfg.B, ws.wbT, axis_table(ctx), ws.G);
+    const PrepareArgs A = prepare_args(ctx, cv, pos, w, ws);
+    k_prepare<<<(A.items + 255) / 256, 256, 0, st>>>(cv, ctx->cfg.L_max, A);
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;
 }
@@ -1185,28 +1219,47 @@ __global__ __launch_bounds__(256) void k_tile_relayout(int N, int L, int C, cons
     }
 }
 
-e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
-                                   const E2fAttnWs& ws, int v_layout, hipStream_t st) {
+// Whether the projection of this call runs in a kernel that takes the preparation along.
+static bool projection_prepares(const e2f_ctx* ctx, int v_layout) {
+    if (ctx->cfg.feat_dtype != E2F_BF16) return true;   // k_project_rows_f32, k_project_mfma
+    return v_layout == 2 && e2f_tile_layouts_direct(ctx) && (ctx->cfg.C == 256 || !(ctx->cfg.flags & E2F_FLAG_PROJECT_PER_CHANNEL_TILE));   // k_project_sh
+}
+
+static e2f_status project(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, int v_layout,
+                          const PrepareArgs& prep, hipStream_t st) {
     if (cv.N == 0) return E2F_OK;
     bool ok;
     const bool tiled_v = v_layout == 1;
     if (v_layout == 2 && !e2f_tile_layouts_direct(ctx)) {
         // channel counts the tile-layout projection kernels are not built for: plain layouts, then a relayout
         if (ctx->cfg.feat_dtype != E2F_BF16 || !ws.q || !ws.k || !ws.v) return E2F_ERR_UNSUPPORTED;
-        ok = dispatch_ws(ctx, cv, h, w, ws, st, false) || dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, false);
+        ok = dispatch_ws(ctx, cv, h, w, ws, st, false) || dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, false, prep);
         if (ok)
             k_tile_relayout<<<(cv.N + 3) / 4, 256, 0, st>>>(cv.N, ctx->cfg.L_max, ctx->cfg.C, ws.q, ws.k, (const uint16_t*)ws.v,
                                                          ctx->tau * 1.44269504088896341f, ws.q16, ws.k16, ws.v4);
     } else if (v_layout == 2)
-        ok = ctx->cfg.feat_dtype == E2F_BF16 && (ctx->cfg.C == 256 ? launch_sh256(ctx, cv, h, w, ws, st) : dispatch_wg(ctx, cv, h, w, ws, st, 2));
+        ok = ctx->cfg.feat_dtype == E2F_BF16 && (ctx->cfg.C == 256 ? launch_sh256(ctx, cv, h, w, ws, st, prep) : dispatch_wg(ctx, cv, h, w, ws, st, 2, prep));
     else if (ctx->cfg.feat_dtype == E2F_BF16)
-        ok = (tiled_v && dispatch_wg(ctx, cv, h, w, ws, st, 1)) || dispatch_ws(ctx, cv, h, w, ws, st, tiled_v) ||
-             dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, tiled_v);
+        ok = (tiled_v && dispatch_wg(ctx, cv, h, w, ws, st, 1, prep)) || dispatch_ws(ctx, cv, h, w, ws, st, tiled_v) ||
+             dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, tiled_v, prep);
     else
-        ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3) || dispatch_mfma<float>(ctx, cv, h, w, ws, st, false);
+        ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3, prep) || dispatch_mfma<float>(ctx, cv, h, w, ws, st, false, prep);
     if (!ok) return E2F_ERR_UNSUPPORTED;
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;
+}
+
+e2f_status e2f_launch_project_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
+                                   const E2fAttnWs& ws, int v_layout, hipStream_t st) {
+    PrepareArgs none = {};
+    return project(ctx, cv, h, w, ws, v_layout, none, st);
+}
+
+e2f_status e2f_launch_prepare_project(const e2f_ctx* ctx, const E2fCellsView& cv, const float* pos, const void* h, const e2f_weights* w,
+                                      const E2fAttnWs& ws, int v_layout, hipStream_t st) {
+    if (cv.N > 0 && projection_prepares(ctx, v_layout)) return project(ctx, cv, h, w, ws, v_layout, prepare_args(ctx, cv, pos, w, ws), st);
+    const e2f_status rc = e2f_launch_prepare(ctx, cv, pos, w, ws, st);
+    return rc != E2F_OK ? rc : e2f_launch_project_mfma(ctx, cv, h, w, ws, v_layout, st);
 }
 
 // The plain layouts and W_Q1 h (q1, v's plain layout).  Where the weight-stationary kernel runs it stores the product that
