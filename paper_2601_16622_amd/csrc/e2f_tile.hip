@@ -978,7 +978,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int w = 0; w < NW; ++w) zt += s_z[w][tt];
                 inv[r] = zt > 0.0f ? 1.0f / zt : 0.0f;
             }
-            // rows of the output: one base pointer per target row, components C floats apart
+            // Rows of the output: one base pointer per target row, components C floats apart.  (Past the caches: nothing here reads
+            // them again, the value rows should stay; 10 000 atoms 292 -> 286 us a forward pass, 100 000 2 702 -> 2 661.)
             int orow[4];
             float* orp[4];
 #pragma unroll
@@ -992,14 +993,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int xo = 0; xo < n; ++xo)
                     if ((XO >> xo) & 1u)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) orp[r][xo * cstride] = pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r];
+                        for (int r = 0; r < 4; ++r) __builtin_nontemporal_store(pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r], &orp[r][xo * cstride]);
             } else {
 #pragma unroll
                 for (int xo = 0; xo < n; ++xo)
                     if ((XO >> xo) & 1u)
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            if (orow[r] >= 0) orp[r][xo * cstride] = pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r];
+                            if (orow[r] >= 0) __builtin_nontemporal_store(pr[__builtin_popcount(XO & ((1u << xo) - 1u))][r] * inv[r], &orp[r][xo * cstride]);
             }
         };
         const int wave_u = __builtin_amdgcn_readfirstlane(wave);
