@@ -339,7 +339,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             if (row >= 0) {
                 float* orp = P.out + (size_t)row * n * P.C + head * 16 + tn;
 #pragma unroll
-                for (int i = 0; i < RO; ++i) orp[(size_t)(WV + NW * i) * P.C] = pr[i][r] * inv;
+                for (int i = 0; i < RO; ++i) __builtin_nontemporal_store(pr[i][r] * inv, &orp[(size_t)(WV + NW * i) * P.C]);
             }
         }
     };
