@@ -980,15 +980,15 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
                                                                         ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, prep);
         };
-        // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2: 500 atoms 21 us
-        // against 22.4, 2 286 atoms 61.7 / 63.5, but 9 000 atoms 199 / 185 and L = 4, 4 000 atoms 240 / 206)
+        // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us
+        // against 22.4); from 900 atoms on those calls are k_project_rows_f32's
         constexpr bool CAN_THREE = sizeof(T) == 4 && C == 128;
         if (CAN_THREE && few && L1 <= 3)
             go(std::integral_constant<int, 1>{}, std::integral_constant<int, CAN_THREE ? 3 : MG>{});
-        else if (CT > 1 && waves_ct < 4096)
+        else if (CAN_THREE || (CT > 1 && waves_ct < 4096))   // (fp32 128 channels: fewer than 900 atoms come here)
             go(std::integral_constant<int, 1>{}, std::integral_constant<int, MG>{});
         else
-            go(std::integral_constant<int, CT>{}, std::integral_constant<int, MG>{});
+            go(std::integral_constant<int, CAN_THREE ? 1 : CT>{}, std::integral_constant<int, MG>{});
         return true;
     }
 }
@@ -1156,7 +1156,9 @@ bool dispatch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, co
         case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, tiled, prep);
         case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, tiled, prep);
         case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
+        case 64:   // (fp32: k_project_rows_f32)
+            if constexpr (sizeof(T) == 2) return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
+            break;
         case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, tiled, prep);
         case 192: return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, tiled, prep);
         case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, tiled, prep);
