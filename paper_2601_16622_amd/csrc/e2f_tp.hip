@@ -58,12 +58,11 @@ __global__ __launch_bounds__(64) void k_eaas_tp(const T* __restrict__ h, const f
             }
         e2f::eaas_accumulate<L, LF, CPL>(v, s_D + p * DSP, s_cw, s_w[p], acc);
         if (active) {
-            // (past the caches, nothing here reads it again: 32 000 products of 3 degrees, 128 channels, 61.6 -> 60.0 us)
             float* op = out + (size_t)(t0 + p) * n * C + c0;
 #pragma unroll
             for (int x = 0; x < n; ++x)
 #pragma unroll
-                for (int u = 0; u < CPL; ++u) __builtin_nontemporal_store(acc[x][u], op + x * C + u);
+                for (int u = 0; u < CPL; ++u) op[x * C + u] = acc[x][u];
         }
     }
 }
