@@ -133,14 +133,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
-                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first, PrepareArgs prep) {
-    if ((int)blockIdx.x >= (cv.N + 15) / 16) {   // (whole workgroup)
-        if (blockIdx.y == 0 && blockIdx.z == 0) prepare_item(cv, prep, L, ((int)blockIdx.x - (cv.N + 15) / 16) * 64 + threadIdx.x);
+                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first, int first_block, PrepareArgs prep) {
+    if ((int)blockIdx.x >= first_block) {   // (whole workgroup)
+        prepare_item(cv, prep, L, ((int)blockIdx.x - first_block) * 64 + threadIdx.x);
         return;
     }
     typedef Frag<T> F;
-    constexpr int NS = C / F::KSTEP;
-    const int tile = blockIdx.x, cg = longest_first ? blockIdx.y : blockIdx.z, l = longest_first ? L - (int)blockIdx.z : blockIdx.y;
+    constexpr int NS = C / F::KSTEP, NCG = C / 16 / CT;
+    const int tiles = (cv.N + 15) / 16, rest = blockIdx.x / tiles, tile = blockIdx.x % tiles;
+    const int cg = longest_first ? rest % NCG : rest / (L + 1), l = longest_first ? L - rest / NCG : rest % (L + 1);
     const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
     const int N = cv.N, n = (L + 1) * (L + 1), nl = 2 * l + 1;
     const int slot_i = min(tile * 16 + i, N - 1);            // clamped rows are computed and not stored
@@ -969,16 +970,18 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
             // waiting for weights, would have the chip to themselves at the end (128 channels, L = 2, 9 000 atoms 203 us
             // against 183; the four-tile form gains by the first order at every size it has).
             const bool longest_first = ct > 1 || C < 128 || few;
-            const int all = tiles + (prep.items + 63) / 64;
-            const dim3 grid = longest_first ? dim3(all, C / 16 / ct, L1) : dim3(all, L1, C / 16 / ct);
+            // (one dimension, the preparation behind the rest: as extra columns of a grid of tiles, channel tiles and degrees it was
+            // repeated for each of those, and 1 551 of the 1 776 workgroups of a call of 60 atoms, L = 2, 256 fp32 channels, did
+            // nothing: 87 us a forward pass, 81 with a launch of its own)
+            const int blocks = tiles * (C / 16 / ct) * L1, grid = blocks + (prep.items + 63) / 64;
             if (tiled)
                 k_project_mfma<T, C, mg, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, prep);
+                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, blocks, prep);
             else
                 k_project_mfma<T, C, mg, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, prep);
+                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, blocks, prep);
         };
         // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us
         // against 22.4); from 900 atoms on those calls are k_project_rows_f32's
