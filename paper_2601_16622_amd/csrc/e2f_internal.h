@@ -205,6 +205,8 @@ bool e2f_tile_f32_supported(const e2f_ctx* ctx);
 // against 96 / 126 (L = 4); 1 000 atoms 105 against 105 and 187 against 168; 2 000, L = 2, 173 against 154.  At 64 channels it is
 // ahead from 60 atoms (45 against 43) to 20 000 (1 031 against 958, L = 4).
 static inline bool e2f_f32_layouts_direct(int C, int N) { return C == 64 || (C == 128 && N >= 900); }
+// q, k, v from the plain layouts into the fp32 tile kernel's (qf, kf, vf), all of ws.
+e2f_status e2f_launch_f32_relayout(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, hipStream_t st);
 e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out, hipStream_t st);
 // The fused call with the non-linear pair feature in the logit; q1 = W_Q1 h in v's plain layout and type.
 bool e2f_nonlinear_supported(const e2f_ctx* ctx);

@@ -1247,8 +1247,13 @@ static e2f_status project(const e2f_ctx* ctx, const E2fCellsView& cv, const void
     else if (ctx->cfg.feat_dtype == E2F_BF16)
         ok = (tiled_v && dispatch_wg(ctx, cv, h, w, ws, st, 1, prep)) || dispatch_ws(ctx, cv, h, w, ws, st, tiled_v) ||
              dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, tiled_v, prep);
-    else
-        ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3, prep) || dispatch_mfma<float>(ctx, cv, h, w, ws, st, false, prep);
+    else if (!(ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3, prep))) {
+        ok = dispatch_mfma<float>(ctx, cv, h, w, ws, st, false, prep);
+        if (ok && v_layout == 3) {   // (the kernel above writes the tile layouts itself)
+            const e2f_status rc = e2f_launch_f32_relayout(ctx, cv, ws, st);
+            if (rc != E2F_OK) return rc;
+        }
+    }
     if (!ok) return E2F_ERR_UNSUPPORTED;
     E2F_HIP_CHECK(hipGetLastError());
     return E2F_OK;

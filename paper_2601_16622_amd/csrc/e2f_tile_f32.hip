@@ -360,7 +360,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int L>
 void launch_L(const TileF32Params& P, hipStream_t st) {
     const int grid = tile_grid(P.n_tiles, P.blk, P.H);
-    if (!e2f_f32_layouts_direct(P.C, P.cv.N)) k_f32_relayout<L><<<(P.cv.N + 3) / 4, 256, 0, st>>>(P);
 #ifndef E2F_F32_NW
 #define E2F_F32_NW 4
 #endif
@@ -376,11 +375,7 @@ bool e2f_tile_f32_supported(const e2f_ctx* ctx) {
            ctx->cfg.B <= 16 && C % 16 == 0 && C <= 256;
 }
 
-// The fp32 tile kernel for every tile whose candidate list fits; q, k, v in the plain layouts and the candidate lists
-// (e2f_launch_tile_lists) must be in `ws`.  Crowded tiles are left untouched: the caller runs the vector-ALU kernel
-// for them.
-e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out, hipStream_t st) {
-    if (cv.N == 0) return E2F_OK;
+static TileF32Params params_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out) {
     TileF32Params P;
     P.cv = cv;
     P.spos = ws.spos; P.q = ws.q; P.k = ws.k; P.v = static_cast<const float*>(ws.v);
@@ -389,6 +384,30 @@ e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const
     P.C = ctx->cfg.C; P.H = ctx->cfg.H; P.B = ctx->cfg.B; P.n_tiles = (cv.N + 15) / 16; P.blk = tile_blk(P.n_tiles);
     P.qscale = ctx->tau * 1.44269504088896341f;   // logits in base-2 units
     P.rc2 = ctx->rc2; P.cutoff = ctx->cfg.cutoff; P.rbf_step = ctx->rbf_step; P.rbf_gamma = ctx->rbf_gamma;
+    return P;
+}
+
+e2f_status e2f_launch_f32_relayout(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, hipStream_t st) {
+    if (cv.N == 0) return E2F_OK;
+    const TileF32Params P = params_f32(ctx, cv, ws, nullptr);
+    const int groups = (cv.N + 3) / 4;
+    switch (ctx->cfg.L_max) {
+        case 1: k_f32_relayout<1><<<groups, 256, 0, st>>>(P); break;
+        case 2: k_f32_relayout<2><<<groups, 256, 0, st>>>(P); break;
+        case 3: k_f32_relayout<3><<<groups, 256, 0, st>>>(P); break;
+        case 4: k_f32_relayout<4><<<groups, 256, 0, st>>>(P); break;
+        default: return E2F_ERR_UNSUPPORTED;
+    }
+    E2F_HIP_CHECK(hipGetLastError());
+    return E2F_OK;
+}
+
+// The fp32 tile kernel for every tile whose candidate list fits: qf, kf, vf (a projection with v_layout 3), what the preparation
+// writes and the candidate lists (e2f_launch_tile_lists) must be in `ws`.  Crowded tiles are left untouched: the caller runs the
+// vector-ALU kernel, which reads the plain layouts, for them.
+e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out, hipStream_t st) {
+    if (cv.N == 0) return E2F_OK;
+    const TileF32Params P = params_f32(ctx, cv, ws, out);
     switch (ctx->cfg.L_max) {
         case 1: launch_L<1>(P, st); break;
         case 2: launch_L<2>(P, st); break;
