@@ -199,12 +199,6 @@ e2f_status e2f_launch_fused(const e2f_ctx* ctx, const E2fCellsView& cv, const e2
 e2f_status e2f_launch_fused_crowded(const e2f_ctx* ctx, const E2fCellsView& cv, const e2f_weights* w, const E2fAttnWs& ws,
                                     float* out, hipStream_t st);
 bool e2f_tile_f32_supported(const e2f_ctx* ctx);
-// Whether the fp32 projection runs with the weights in registers and writes the fp32 tile kernel's layouts itself (k_project_rows_f32;
-// elsewhere the per-tile kernel, then a relayout).  At 128 channels a wave loads 40 KB of weights before it starts, which few
-// atoms do not pay for: forward passes of 60 / 500 atoms 60 / 81 us with the per-tile kernel against 69 / 87 (L = 2), 85 / 122
-// against 96 / 126 (L = 4); 1 000 atoms 105 against 105 and 187 against 168; 2 000, L = 2, 173 against 154.  At 64 channels it is
-// ahead from 60 atoms (45 against 43) to 20 000 (1 031 against 958, L = 4).
-static inline bool e2f_f32_layouts_direct(int C, int N) { return C == 64 || (C == 128 && N >= 900); }
 // q, k, v from the plain layouts into the fp32 tile kernel's (qf, kf, vf), all of ws.
 e2f_status e2f_launch_f32_relayout(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, hipStream_t st);
 e2f_status e2f_launch_tile_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const E2fAttnWs& ws, float* out, hipStream_t st);

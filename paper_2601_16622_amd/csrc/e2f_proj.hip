@@ -983,15 +983,15 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
                                                                         (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
                                                                         ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, blocks, prep);
         };
-        // At 128 fp32 channels and degrees up to 2 in few waves: three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us
-        // against 22.4); from 900 atoms on those calls are k_project_rows_f32's
-        constexpr bool CAN_THREE = sizeof(T) == 4 && C == 128;
-        if (CAN_THREE && few && L1 <= 3)
+        // fp32, 64 and 128 channels: at most 2 600 atoms come here (rows_f32_ahead), fewer waves than four channel tiles to a wave are
+        // for.  At 128 and degrees up to 2 three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us against 22.4).
+        constexpr bool SMALL = sizeof(T) == 4 && (C == 64 || C == 128), CAN_THREE = SMALL && C == 128;
+        if (CAN_THREE && L1 <= 3)
             go(std::integral_constant<int, 1>{}, std::integral_constant<int, CAN_THREE ? 3 : MG>{});
-        else if (CAN_THREE || (CT > 1 && waves_ct < 4096))   // (fp32 128 channels: fewer than 900 atoms come here)
+        else if (SMALL || (CT > 1 && waves_ct < 4096))
             go(std::integral_constant<int, 1>{}, std::integral_constant<int, MG>{});
         else
-            go(std::integral_constant<int, CAN_THREE ? 1 : CT>{}, std::integral_constant<int, MG>{});
+            go(std::integral_constant<int, SMALL ? 1 : CT>{}, std::integral_constant<int, MG>{});
         return true;
     }
 }
@@ -1055,9 +1055,22 @@ void launch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, 
                                                               tile_layouts ? ws.qf : nullptr, tile_layouts ? ws.kf : nullptr,
                                                               tile_layouts ? ws.vf : nullptr, ctx->tau * 1.44269504088896341f, prep);
 }
+// From how many atoms on k_project_rows_f32 takes the call, by degree; the per-tile kernel has the smaller ones, since here every
+// wave loads 20 KB (64 channels) or 40 KB of weights before it starts.  Measured over 20 to 5 000 atoms with either kernel (the
+// whole call, this one over the per-tile one): with the tile layouts, which the other needs a relayout launch for, 64 channels
+// 0.92 to 0.97 at every size; 128 channels, L = 1, 1 050 / 1 400 / 1 700 atoms 1.02 / 1.01 / 0.98, L = 2, 900 / 1 050 1.01 / 0.97,
+// L = 3 900 0.98, L = 4 900 0.95.  Plain layouts alone (capped and non-linear calls, heads of 32 channels, L = 0, the backward
+// pass): 64 channels 60 atoms 1.03 (non-linear 1.05), L = 0 and 1, 800 / 1 200 1.01 / 0.99, L = 2 1 000 0.99, L = 3, 1 700 / 2 500
+// 1.01 / 0.97, L = 4, 1 200 / 2 000 1.015 / 0.97; 128 channels, L = 0, 2 000 / 2 800 1.06 / 0.99, L = 1, 2 000 / 2 200 1.05 / 0.98,
+// L = 2, 1 000 / 1 300 / 1 600 1.08 / 1.015 / 0.99, L = 3, 1 050 / 1 300 1.03 / 0.96, L = 4, 950 to 1 900 even, 2 000 1.02, 2 400 0.97.
+constexpr int ROWS_F32_TILED[2][E2F_MAX_L + 1] = {{0, 0, 0, 0, 0}, {0, 1500, 950, 900, 900}};   // (L = 0 has no tile layouts)
+constexpr int ROWS_F32_PLAIN[2][E2F_MAX_L + 1] = {{1100, 1100, 1000, 2200, 1500}, {2600, 2200, 1500, 1300, 2049}};
+bool rows_f32_ahead(int C, int L, int N, bool tile_layouts) {
+    return (C == 64 || C == 128) && N >= (tile_layouts ? ROWS_F32_TILED : ROWS_F32_PLAIN)[C == 128][L];
+}
 bool dispatch_rows_f32(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws, hipStream_t st, bool tile_layouts,
                        const PrepareArgs& prep) {
-    if (!e2f_f32_layouts_direct(ctx->cfg.C, cv.N)) return false;
+    if (!rows_f32_ahead(ctx->cfg.C, ctx->cfg.L_max, cv.N, tile_layouts)) return false;
     if (ctx->cfg.C == 64) launch_rows_f32<64>(ctx, cv, h, w, ws, st, tile_layouts, prep);
     else launch_rows_f32<128>(ctx, cv, h, w, ws, st, tile_layouts, prep);
     return true;
@@ -1159,9 +1172,7 @@ bool dispatch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, co
         case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, tiled, prep);
         case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, tiled, prep);
         case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 64:   // (fp32: k_project_rows_f32)
-            if constexpr (sizeof(T) == 2) return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
-            break;
+        case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
         case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, tiled, prep);
         case 192: return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, tiled, prep);
         case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, tiled, prep);
