@@ -101,34 +101,12 @@ struct Frag<float> {
 
 // C is the channel count (compile time so that fragments stay in registers), MG the number of orders m
 // whose A fragments are held at once, CT the number of 16-wide output tiles per wave.
-// Stores cnt consecutive bf16 values val[0..cnt) at row[pos0..pos0+cnt): 4-byte stores wherever two neighbours
-// share an aligned word, 2-byte stores at the ragged ends.  row is 4-byte aligned; pos0 and cnt are wave-uniform.
-template <int MAXN>
-__device__ __forceinline__ void store_run_bf16(uint16_t* row, int pos0, const float (&val)[MAXN], int cnt) {
-    const int lead = pos0 & 1;
-    if (lead && cnt > 0) row[pos0] = e2f::float_to_bf16_bits(val[0]);
-#pragma unroll
-    for (int k = 0; k + 1 < MAXN; ++k) {
-        // pairs start at k = lead, lead + 2, ...
-        if (((k - lead) & 1) == 0 && k >= lead && k + 1 < cnt) {
-            const uint32_t w = (uint32_t)e2f::float_to_bf16_bits(val[k]) | ((uint32_t)e2f::float_to_bf16_bits(val[k + 1]) << 16);
-            *reinterpret_cast<uint32_t*>(row + pos0 + k) = w;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < MAXN; ++k)
-        if (k == cnt - 1 && k >= lead && ((k - lead) & 1) == 0) row[pos0 + k] = e2f::float_to_bf16_bits(val[k]);
-}
-
-// TILED: store v for the MFMA attention kernel, bf16 [slot][head][tile][16 channels][16 tile rows] with the
-// components in tile order (HI: l=4 rows 0..8, l=3 rows 9..15; LO: l=2 rows 0..4, l=1 rows 5..7, l=0 row 8,
-// rows 9..15 zero), heads of 16 channels.
 // Two waves to a SIMD where a wave's rows and weights leave the registers for it (fp32 up to 64 channels, L = 4, 2 000 atoms
 // 36 -> 33 us; bf16 192 channels, L = 4, 1 000 atoms 38 us against 48 with the weights loaded again in every pass), and for
 // fp32 128 channels in the instance of three orders.
 template <typename T, int C, int MG>
 constexpr bool THREE_ORDERS = sizeof(T) == 4 && C == 128 && MG == 3;
-template <typename T, int C, int MG, int CT, bool TILED>
+template <typename T, int C, int MG, int CT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (C <= (sizeof(T) == 2 ? 192 : 64) || THREE_ORDERS<T, C, MG>) ? 2 : 1))) void k_project_mfma(E2fCellsView cv, const T* __restrict__ h,
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
@@ -215,29 +193,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
             for (int r = 0; r < 4; ++r) {
                 const int slot = tile * 16 + 4 * g + r;
                 if (slot >= N) continue;
-                if constexpr (!TILED) {
 #pragma unroll
-                    for (int mm = 0; mm < MG; ++mm)
-                        if (m0 + mm < nl) e2f::store_from_float(v + ((size_t)slot * n + l * l + m0 + mm) * C + co, pv[mm][r]);
-                } else {
-                    const int NT = L >= 3 ? 2 : 1;
-                    const int TI = l >= 3 ? 0 : NT - 1;
-                    const int pos_l = l == 4 ? 0 : (l == 3 ? 9 : (l == 2 ? 0 : (l == 1 ? 5 : 8)));
-                    uint16_t* row = reinterpret_cast<uint16_t*>(v) +
-                                    ((((size_t)slot * (C / 16) + (co >> 4)) * NT + TI) * 16 + (co & 15)) * 16;
-                    float val[MG];
-#pragma unroll
-                    for (int mm = 0; mm < MG; ++mm) val[mm] = pv[mm][r];
-                    store_run_bf16<MG>(row, pos_l + m0, val, min(MG, nl - m0));
-                    if (l == 0) {  // rows 9..15 of the LO tile are padding and must read as zero
-                        const float zero[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                        store_run_bf16<7>(row, 9, zero, 7);
-                    }
-                    if (l == 3 && L == 3 && m0 == 0) {  // without l = 4 the first nine HI rows are padding
-                        const float zero[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                        store_run_bf16<9>(row, 0, zero, 9);
-                    }
-                }
+                for (int mm = 0; mm < MG; ++mm)
+                    if (m0 + mm < nl) e2f::store_from_float(v + ((size_t)slot * n + l * l + m0 + mm) * C + co, pv[mm][r]);
             }
         }
     }
@@ -259,12 +217,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
 // degree l and one 16-channel output tile in registers as MFMA A operands and streams atoms through as B
 // operands, 16 atoms x one order m at a time, with the next slab of h requested before the current one is used.
 // Accumulator layout: lane (g, j) holds output channels 16*ct + 4g..4g+3 of atom j, so q and k go out as 16-byte
-// stores and v as runs of consecutive orders.  All (l, channel tile) waves of one group of TPW atom tiles are
-// dispatched back to back onto the same XCD, so that the partial rows they write (q, k rows are shared by the
-// channel tiles, tiled v rows by two degrees) merge in that XCD's L2 before they reach memory, and the h rows
-// they all read are fetched once.  q1 (or null; plain layout only): W_Q1 h as well, in v's layout.
-template <int C, bool TILED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && !TILED ? 2 : 1))) void k_project_ws(E2fCellsView cv, const uint16_t* __restrict__ h,
+// stores and v as 8-byte stores.  All (l, channel tile) waves of one group of TPW atom tiles are
+// dispatched back to back onto the same XCD, so that the partial rows they write (those of q, k and v are shared by the
+// channel tiles) merge in that XCD's L2 before they reach memory, and the h rows they all read are fetched once.
+// q1 (or null): W_Q1 h as well, in v's layout.
+template <int C>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 ? 2 : 1))) void k_project_ws(E2fCellsView cv, const uint16_t* __restrict__ h,
                                                    const uint16_t* __restrict__ WQ1, const uint16_t* __restrict__ WQ2,
                                                    const uint16_t* __restrict__ WK1, const uint16_t* __restrict__ WK2,
                                                    const uint16_t* __restrict__ WV, int L, int tpw,
@@ -324,7 +282,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && 
         load_x(tile0 + su / nl, su % nl, X[u]);
     }
     f32x4 qacc = {0.f, 0.f, 0.f, 0.f}, kacc = {0.f, 0.f, 0.f, 0.f};
-    float vrun[4][2 * E2F_MAX_L + 1];
     // (full groups of PD steps without a check per step: the compiler sets its waits on the ring's loads by the fewest
     // memory instructions on any path from a request to its use, and a path that skips steps would make that one)
     auto step = [&](int st, int u) __attribute__((always_inline)) {
@@ -345,14 +302,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && 
         }
         qacc += p[0] * p[1];
         kacc += p[2] * p[3];
-        if constexpr (TILED) {
-#pragma unroll
-            for (int mm = 0; mm < 2 * E2F_MAX_L + 1; ++mm)
-                if (mm == m) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) vrun[r][mm] = p[4][r];
-                }
-        } else if (slot < N) {
+        if (slot < N) {
             const size_t at = ((size_t)slot * n + l * l + m) * C + ct * 16 + 4 * g;
             auto store = [&](uint16_t* dst, const f32x4& x) {
                 const uint32_t w0 = (uint32_t)e2f::float_to_bf16_bits(x[0]) | ((uint32_t)e2f::float_to_bf16_bits(x[1]) << 16);
@@ -362,28 +312,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C <= 128 && 
             store(v, p[4]);
             if (q1) store(q1, p[0]);
         }
-        if (m == nl - 1) {  // last order of this atom tile: q, k (and the tiled v rows) go out
+        if (m == nl - 1) {  // last order of this atom tile: q and k go out
             if (slot < N) {
                 *reinterpret_cast<f32x4*>(q + ((size_t)slot * (L + 1) + l) * C + ct * 16 + 4 * g) = qacc;
                 *reinterpret_cast<f32x4*>(k + ((size_t)slot * (L + 1) + l) * C + ct * 16 + 4 * g) = kacc;
-                if constexpr (TILED) {
-                    const int NT = L >= 3 ? 2 : 1;
-                    const int TI = l >= 3 ? 0 : NT - 1;
-                    const int pos_l = l == 4 ? 0 : (l == 3 ? 9 : (l == 2 ? 0 : (l == 1 ? 5 : 8)));
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        uint16_t* row = v + ((((size_t)slot * NCT + ct) * NT + TI) * 16 + 4 * g + r) * 16;
-                        store_run_bf16<2 * E2F_MAX_L + 1>(row, pos_l, vrun[r], nl);
-                        if (l == 0) {
-                            const float zero[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                            store_run_bf16<7>(row, 9, zero, 7);
-                        }
-                        if (l == 3 && L == 3) {
-                            const float zero[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                            store_run_bf16<9>(row, 0, zero, 9);
-                        }
-                    }
-                }
             }
             qacc = (f32x4){0.f, 0.f, 0.f, 0.f};
             kacc = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -952,12 +884,12 @@ __global__ void k_project_simple(E2fCellsView cv, const T* __restrict__ h, const
 
 template <typename T, int C>
 bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                 hipStream_t st, bool tiled, const PrepareArgs& prep) {
+                 hipStream_t st, const PrepareArgs& prep) {
     if constexpr (C % Frag<T>::KSTEP != 0) {
         return false;
     } else {
         // orders m held in registers at once: bounded by the A fragments (C/KSTEP registers-quads per order)
-        constexpr int MG = sizeof(T) == 2 ? (C <= 128 ? 9 : 4) : (C <= 64 ? 9 : (C <= 128 ? 5 : 2));
+        constexpr int MG = sizeof(T) == 2 ? 4 : (C <= 64 ? 9 : (C <= 128 ? 5 : 2));
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
         const int tiles = (cv.N + 15) / 16, L1 = ctx->cfg.L_max + 1, waves_ct = tiles * L1 * (C / 16 / CT);
@@ -974,14 +906,9 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
             // repeated for each of those, and 1 551 of the 1 776 workgroups of a call of 60 atoms, L = 2, 256 fp32 channels, did
             // nothing: 87 us a forward pass, 81 with a launch of its own)
             const int blocks = tiles * (C / 16 / ct) * L1, grid = blocks + (prep.items + 63) / 64;
-            if (tiled)
-                k_project_mfma<T, C, mg, ct, true><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
-                                                                       (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                       ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, blocks, prep);
-            else
-                k_project_mfma<T, C, mg, ct, false><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2,
-                                                                        (const T*)w->WK1, (const T*)w->WK2, (const T*)w->WV,
-                                                                        ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v, longest_first, blocks, prep);
+            k_project_mfma<T, C, mg, ct><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2, (const T*)w->WK1,
+                                                              (const T*)w->WK2, (const T*)w->WV, ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v,
+                                                              longest_first, blocks, prep);
         };
         // fp32, 64 and 128 channels: at most 2 600 atoms come here (rows_f32_ahead), fewer waves than four channel tiles to a wave are
         // for.  At 128 and degrees up to 2 three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us against 22.4).
@@ -998,25 +925,14 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
 
 template <int C>
 bool launch_ws(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-               hipStream_t st, bool tiled, uint16_t* q1) {
-    if constexpr (C % 32 != 0 || C > 256) {
-        return false;   // five stationary weight tiles must fit the register file
-    } else {
-        const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16;
-        const int tpw = 4;
-        const int groups = (n_tiles + tpw - 1) / tpw;
-        const int blocks = ((groups + 7) / 8) * (L + 1) * (C / 16) * 8;
-        const uint16_t* hh = (const uint16_t*)h;
-        if (tiled)
-            k_project_ws<C, true><<<blocks, 64, 0, st>>>(cv, hh, (const uint16_t*)w->WQ1, (const uint16_t*)w->WQ2,
-                                                         (const uint16_t*)w->WK1, (const uint16_t*)w->WK2,
-                                                         (const uint16_t*)w->WV, L, tpw, ws.q, ws.k, (uint16_t*)ws.v, nullptr);
-        else
-            k_project_ws<C, false><<<blocks, 64, 0, st>>>(cv, hh, (const uint16_t*)w->WQ1, (const uint16_t*)w->WQ2,
-                                                          (const uint16_t*)w->WK1, (const uint16_t*)w->WK2,
-                                                          (const uint16_t*)w->WV, L, tpw, ws.q, ws.k, (uint16_t*)ws.v, q1);
-        return true;
-    }
+               hipStream_t st, uint16_t* q1) {
+    const int L = ctx->cfg.L_max, n_tiles = (cv.N + 15) / 16;
+    const int tpw = 4;
+    const int groups = (n_tiles + tpw - 1) / tpw;
+    const int blocks = ((groups + 7) / 8) * (L + 1) * (C / 16) * 8;
+    k_project_ws<C><<<blocks, 64, 0, st>>>(cv, (const uint16_t*)h, (const uint16_t*)w->WQ1, (const uint16_t*)w->WQ2, (const uint16_t*)w->WK1,
+                                           (const uint16_t*)w->WK2, (const uint16_t*)w->WV, L, tpw, ws.q, ws.k, (uint16_t*)ws.v, q1);
+    return true;
 }
 
 // Tiles per workgroup by degree: as many slabs to every workgroup as the estimate likes best (a workgroup costs its slabs and
@@ -1155,27 +1071,30 @@ bool dispatch_wg(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
 }
 
 bool dispatch_ws(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w, const E2fAttnWs& ws,
-                 hipStream_t st, bool tiled, uint16_t* q1 = nullptr) {
-    switch (ctx->cfg.C) {
-        case 32: return launch_ws<32>(ctx, cv, h, w, ws, st, tiled, q1);
-        case 64: return launch_ws<64>(ctx, cv, h, w, ws, st, tiled, q1);
-        case 128: return launch_ws<128>(ctx, cv, h, w, ws, st, tiled, q1);
-        case 256: return tiled ? false : launch_ws<256>(ctx, cv, h, w, ws, st, false, q1);
+                 hipStream_t st, uint16_t* q1 = nullptr) {
+    switch (ctx->cfg.C) {   // (five stationary weight tiles must fit the register file)
+        case 32: return launch_ws<32>(ctx, cv, h, w, ws, st, q1);
+        case 64: return launch_ws<64>(ctx, cv, h, w, ws, st, q1);
+        case 128: return launch_ws<128>(ctx, cv, h, w, ws, st, q1);
+        case 256: return launch_ws<256>(ctx, cv, h, w, ws, st, q1);
     }
     return false;
 }
 
+// bf16: what k_project_ws is not built for.
 template <typename T>
 bool dispatch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
-                   const E2fAttnWs& ws, hipStream_t st, bool tiled, const PrepareArgs& prep) {
-    switch (ctx->cfg.C) {
-        case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 192: return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, tiled, prep);
-        case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, tiled, prep);
+                   const E2fAttnWs& ws, hipStream_t st, const PrepareArgs& prep) {
+    if (ctx->cfg.C == 192) return launch_mfma<T, 192>(ctx, cv, h, w, ws, st, prep);
+    if constexpr (sizeof(T) == 4) {
+        switch (ctx->cfg.C) {
+            case 16: return launch_mfma<T, 16>(ctx, cv, h, w, ws, st, prep);
+            case 32: return launch_mfma<T, 32>(ctx, cv, h, w, ws, st, prep);
+            case 48: return launch_mfma<T, 48>(ctx, cv, h, w, ws, st, prep);
+            case 64: return launch_mfma<T, 64>(ctx, cv, h, w, ws, st, prep);
+            case 128: return launch_mfma<T, 128>(ctx, cv, h, w, ws, st, prep);
+            case 256: return launch_mfma<T, 256>(ctx, cv, h, w, ws, st, prep);
+        }
     }
     return false;
 }
@@ -1245,21 +1164,20 @@ static e2f_status project(const e2f_ctx* ctx, const E2fCellsView& cv, const void
                           const PrepareArgs& prep, hipStream_t st) {
     if (cv.N == 0) return E2F_OK;
     bool ok;
-    const bool tiled_v = v_layout == 1;
     if (v_layout == 2 && !e2f_tile_layouts_direct(ctx)) {
         // channel counts the tile-layout projection kernels are not built for: plain layouts, then a relayout
         if (ctx->cfg.feat_dtype != E2F_BF16 || !ws.q || !ws.k || !ws.v) return E2F_ERR_UNSUPPORTED;
-        ok = dispatch_ws(ctx, cv, h, w, ws, st, false) || dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, false, prep);
+        ok = dispatch_ws(ctx, cv, h, w, ws, st) || dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, prep);
         if (ok)
             k_tile_relayout<<<(cv.N + 3) / 4, 256, 0, st>>>(cv.N, ctx->cfg.L_max, ctx->cfg.C, ws.q, ws.k, (const uint16_t*)ws.v,
                                                          ctx->tau * 1.44269504088896341f, ws.q16, ws.k16, ws.v4);
     } else if (v_layout == 2)
         ok = ctx->cfg.feat_dtype == E2F_BF16 && (ctx->cfg.C == 256 ? launch_sh256(ctx, cv, h, w, ws, st, prep) : dispatch_wg(ctx, cv, h, w, ws, st, 2, prep));
     else if (ctx->cfg.feat_dtype == E2F_BF16)
-        ok = (tiled_v && dispatch_wg(ctx, cv, h, w, ws, st, 1, prep)) || dispatch_ws(ctx, cv, h, w, ws, st, tiled_v) ||
-             dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, tiled_v, prep);
+        ok = v_layout == 1 ? dispatch_wg(ctx, cv, h, w, ws, st, 1, prep)
+                           : dispatch_ws(ctx, cv, h, w, ws, st) || dispatch_mfma<uint16_t>(ctx, cv, h, w, ws, st, prep);
     else if (!(ok = dispatch_rows_f32(ctx, cv, h, w, ws, st, v_layout == 3, prep))) {
-        ok = dispatch_mfma<float>(ctx, cv, h, w, ws, st, false, prep);
+        ok = dispatch_mfma<float>(ctx, cv, h, w, ws, st, prep);
         if (ok && v_layout == 3) {   // (the kernel above writes the tile layouts itself)
             const e2f_status rc = e2f_launch_f32_relayout(ctx, cv, ws, st);
             if (rc != E2F_OK) return rc;
@@ -1289,7 +1207,7 @@ e2f_status e2f_launch_prepare_project(const e2f_ctx* ctx, const E2fCellsView& cv
 e2f_status e2f_launch_project_q1(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, const e2f_weights* w,
                                  const E2fAttnWs& ws, void* q1, hipStream_t st) {
     if (cv.N == 0) return E2F_OK;
-    if (ctx->cfg.feat_dtype == E2F_BF16 && dispatch_ws(ctx, cv, h, w, ws, st, false, (uint16_t*)q1)) {
+    if (ctx->cfg.feat_dtype == E2F_BF16 && dispatch_ws(ctx, cv, h, w, ws, st, (uint16_t*)q1)) {
         E2F_HIP_CHECK(hipGetLastError());
         return E2F_OK;
     }

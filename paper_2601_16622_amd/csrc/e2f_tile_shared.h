@@ -82,15 +82,6 @@ struct VRows {
     __device__ __forceinline__ bf16x8 swapped_second(int p) const { return __builtin_bit_cast(bf16x8, pb[p]); }
 };
 
-// A value the optimizer knows nothing about: what is computed from it is not moved out of a loop.
-__device__ __forceinline__ int opaque(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-__device__ __forceinline__ int opaque_uniform(int x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
 __device__ __forceinline__ float read_lane(float x, int src_lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src_lane));
 }
