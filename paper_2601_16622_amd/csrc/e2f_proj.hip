@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
                                                      const T* __restrict__ WQ1, const T* __restrict__ WQ2,
                                                      const T* __restrict__ WK1, const T* __restrict__ WK2,
                                                      const T* __restrict__ WV, int L, float* __restrict__ q,
-                                                     float* __restrict__ k, T* __restrict__ v, bool longest_first, int first_block, PrepareArgs prep) {
+                                                     float* __restrict__ k, T* __restrict__ v, int first_block, PrepareArgs prep) {
     if ((int)blockIdx.x >= first_block) {   // (whole workgroup)
         prepare_item(cv, prep, L, ((int)blockIdx.x - first_block) * 64 + threadIdx.x);
         return;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
     typedef Frag<T> F;
     constexpr int NS = C / F::KSTEP, NCG = C / 16 / CT;
     const int tiles = (cv.N + 15) / 16, rest = blockIdx.x / tiles, tile = blockIdx.x % tiles;
-    const int cg = longest_first ? rest % NCG : rest / (L + 1), l = longest_first ? L - rest / NCG : rest % (L + 1);
+    const int cg = rest % NCG, l = L - rest / NCG;
     const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
     const int N = cv.N, n = (L + 1) * (L + 1), nl = 2 * l + 1;
     const int slot_i = min(tile * 16 + i, N - 1);            // clamped rows are computed and not stored
@@ -893,22 +893,19 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
         constexpr int CT = (C / 16) % 4 == 0 ? 4 : ((C / 16) % 2 == 0 ? 2 : 1);
         // few atoms: one channel tile per wave gives CT times the waves (each h slab is then fetched C/16 times)
         const int tiles = (cv.N + 15) / 16, L1 = ctx->cfg.L_max + 1, waves_ct = tiles * L1 * (C / 16 / CT);
-        const bool few = (long long)tiles * L1 * (C / 16) <= 5 * 1024;   // one-tile waves in up to five rounds of one wave per SIMD
         auto go = [&](auto ct_tag, auto mg_tag) {
             constexpr int ct = decltype(ct_tag)::value, mg = decltype(mg_tag)::value;
-            // The degrees with the most orders start first, so that the launch does not end on its longest waves (fp32, 1 000
-            // atoms: 128 channels, L = 2, 30 us against 37; 192, L = 4, 118 against 134).  From 128 channels on a SIMD holds one
-            // wave, and beyond five rounds of them the degrees are better mixed, since the short waves of the low degrees, mostly
-            // waiting for weights, would have the chip to themselves at the end (128 channels, L = 2, 9 000 atoms 203 us
-            // against 183; the four-tile form gains by the first order at every size it has).
-            const bool longest_first = ct > 1 || C < 128 || few;
+            // The degrees with the most orders start first, so that the launch does not end on its longest waves.  Kernel, us, this way
+            // / mixed: fp32 128 channels, L = 2, 900 atoms 29 / 37, L = 4, 800 47 / 67; 192 channels, L = 4, 1 000 atoms 117 / 134, 2 000
+            // 213 / 227, L = 2, 9 000 361 / 395; 256 channels, L = 4, 1 000 atoms 196 / 216, 1 600 294 / 311, L = 2, 3 000 228 / 236; bf16
+            // 192 channels, L = 4, 1 000 atoms 36.4 / 39.8, 4 000 125 / 127.
             // (one dimension, the preparation behind the rest: as extra columns of a grid of tiles, channel tiles and degrees it was
             // repeated for each of those, and 1 551 of the 1 776 workgroups of a call of 60 atoms, L = 2, 256 fp32 channels, did
             // nothing: 87 us a forward pass, 81 with a launch of its own)
             const int blocks = tiles * (C / 16 / ct) * L1, grid = blocks + (prep.items + 63) / 64;
             k_project_mfma<T, C, mg, ct><<<grid, 64, 0, st>>>(cv, (const T*)h, (const T*)w->WQ1, (const T*)w->WQ2, (const T*)w->WK1,
                                                               (const T*)w->WK2, (const T*)w->WV, ctx->cfg.L_max, ws.q, ws.k, (T*)ws.v,
-                                                              longest_first, blocks, prep);
+                                                              blocks, prep);
         };
         // fp32, 64 and 128 channels: at most 2 600 atoms come here (rows_f32_ahead), fewer waves than four channel tiles to a wave are
         // for.  At 128 and degrees up to 2 three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us against 22.4).
