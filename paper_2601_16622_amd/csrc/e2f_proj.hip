@@ -101,9 +101,9 @@ struct Frag<float> {
 
 // C is the channel count (compile time so that fragments stay in registers), MG the number of orders m
 // whose A fragments are held at once, CT the number of 16-wide output tiles per wave.
-// Two waves to a SIMD where a wave's rows and weights leave the registers for it (fp32 up to 64 channels, L = 4, 2 000 atoms
-// 36 -> 33 us; bf16 192 channels, L = 4, 1 000 atoms 38 us against 48 with the weights loaded again in every pass), and for
-// fp32 128 channels in the instance of three orders.
+// Two waves to a SIMD where a wave's rows and weights leave the registers for it: fp32 up to 64 channels (kernel, us, two waves / one:
+// 64 channels, L = 3, 2 000 atoms 24.4 / 27.8, L = 4, 1 400 atoms 31.5 / 29.8; 48 channels even), bf16 192 channels (L = 4, 1 000 atoms
+// 36.7 / 37.7, 4 000 127 / 132), and fp32 128 channels in the instance of three orders, which needs no more registers.
 template <typename T, int C, int MG>
 constexpr bool THREE_ORDERS = sizeof(T) == 4 && C == 128 && MG == 3;
 template <typename T, int C, int MG, int CT>
@@ -135,8 +135,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CT == 1 && (
     for (int m0 = 0; m0 < nl; m0 += MG) {
         // Several channel tiles: an offset of zero that the compiler cannot see through.  The weights are the same for every
         // pass over the orders, and it would load those of all maps and tiles before the loop, into scratch memory (fp32, L = 2,
-        // 9 000 atoms, 192 channels 1 314 us with them, 388 without).  Those of one tile fit the registers and stay there
-        // (4 000 atoms, 190 us; loaded again in every pass 254), but not beside a second wave (THREE_ORDERS: 60 us without, 55 with).
+        // 9 000 atoms, 192 channels 1 314 us with them, 361 without).  Those of one tile fit the registers and stay there (192 channels,
+        // L = 4, 1 000 atoms 116 us, loaded again in every pass 170; 256 channels 195 / 223; bf16 192 channels 36.7 / 47.4), but not beside
+        // a second wave (THREE_ORDERS, L = 2, 500 / 900 / 1 400 atoms 26 / 35 / 45 us with them, 23 / 29 / 40 without).
         int fresh = 0;
         if constexpr (CT > 1 || THREE_ORDERS<T, C, MG>) asm volatile("" : "+s"(fresh));
         typename F::type A[MG][NS];
@@ -908,7 +909,8 @@ bool launch_mfma(const e2f_ctx* ctx, const E2fCellsView& cv, const void* h, cons
                                                               blocks, prep);
         };
         // fp32, 64 and 128 channels: at most 2 600 atoms come here (rows_f32_ahead), fewer waves than four channel tiles to a wave are
-        // for.  At 128 and degrees up to 2 three orders at a time, two waves to a SIMD (L = 2, 500 atoms 21 us against 22.4).
+        // for.  At 128 and degrees up to 2 three orders at a time, two waves to a SIMD (kernel, us, three / five: L = 2, 500 atoms 23.1 /
+        // 24.8, 900 28.8 / 28.0, 1 400 40.0 / 41.6; L = 1, 2 000 atoms 25.6 / 32.0).
         constexpr bool SMALL = sizeof(T) == 4 && (C == 64 || C == 128), CAN_THREE = SMALL && C == 128;
         if (CAN_THREE && L1 <= 3)
             go(std::integral_constant<int, 1>{}, std::integral_constant<int, CAN_THREE ? 3 : MG>{});
