@@ -128,8 +128,8 @@ struct DegreeMap {
 // degrees are 0.8 MB, 1.5 with the transposes that bf16 features read), and no channel count is too wide for the registers.
 // Bound: fp32 by the matrix cores (nine products, 6 GFLOP at 2 240 atoms, L = 2, 128 channels: 38 us at the fp32 peak), bf16 by
 // the fp32 rows of dv and dh (0.13 GB at 4 000 atoms, L = 4, 128 channels: 25 us at the rate of a copy).  Measured, with the
-// one-thread-per-channel kernel on the vector ALUs in brackets: fp32 2 240 atoms L = 2 x 128: 78 us (442); bf16 4 000 atoms L = 4
-// x 256: 271 us (2 818; one bf16 a factor would take less, at the loss stated at H_PARTS).  Up to 128 bf16 channels it
+// one-thread-per-channel kernel on the vector ALUs in brackets: fp32 2 240 atoms L = 2 x 128: 75 us (442); bf16 3 840 atoms L = 4
+// x 256: 271 us (2 818 at 4 000; one bf16 a factor would take less, at the loss stated at H_PARTS).  Up to 128 bf16 channels it
 // has the smaller calls, see k_bwd_rows_stationary.
 // CP: channels padded up to a multiple of 32 (PAD: C < CP; the missing ones read as zero).
 template <typename T, int CP, int RT, bool PAD>
@@ -306,10 +306,13 @@ __global__ __launch_bounds__(2 * CP) __attribute__((amdgpu_waves_per_eu(2))) voi
 // through LDS as [atom][channel] rows, rounded to bf16 as in k_bwd_rows.  The feature rows of a slab are fetched once per
 // workgroup and shared through LDS as well.
 // It takes a call from STATIONARY_WORK row elements on: a load of the weights is shared by more rows the more rows there are, and
-// below that its workgroups do not fill the chip.  Measured, us, this kernel / k_bwd_rows with 64 rows a workgroup (with 128):
-// 128 channels, L = 4: 1 000 atoms 38 / 31, 1 500 39 / 42, 2 000 40 / 59, 3 000 43 / 83 (62), 4 000 55 / 106 (80), 6 000 76 / 152
-// (101), 9 000 115 / 219 (139); 64 channels, L = 3: 2 000 atoms 20 / 13, 4 000 21 / 21, 6 000 26 / 28, 9 000 30 / 45 (43); 32 channels,
-// L = 1: 9 000 atoms 12 / 8, 20 000 14 / 12, 40 000 18 / 19.
+// below that its workgroups do not fill the chip.  Measured, us, this kernel / k_bwd_rows: 128 channels, L = 4: 500 atoms 35 / 17,
+// 1 000 37 / 24, 1 311 (the line) 37 / 31, 1 500 37 / 31.5, 2 000 38 / 40, 3 000 40 / 50, 4 000 51 / 70, 6 000 68 / 99, 9 000 101 / 134; L = 2:
+// 3 640 (the line) 35 / 30, 5 000 36 / 32, 7 000 38 / 42; L = 1: 8 192 (the line) 32 / 25, 12 000 33 / 33; 64 channels, L = 3: 2 000 18.3 / 13.1,
+// 4 000 19.0 / 18.9, 5 000 20 / 22, 9 000 28 / 43; L = 2: 5 000 17.9 / 16.0, 7 282 (the line) 18.6 / 20.1; 32 channels, L = 4: 5 243 (the line)
+// 15.8 / 14.2, 9 000 19.3 / 20.0; L = 1: 20 000 14 / 11, 40 000 17 / 18.  The line was drawn where the two met before k_bwd_rows read its
+// fragments a step ahead; at 64 channels they still meet there, at 128 from the line up to 6 million elements k_bwd_rows is
+// ahead by up to 7 us of a call of some 250.
 constexpr long long STATIONARY_WORK = 1ll << 22;
 constexpr int SLABS_MIN = 18, SLABS_MAX = 36;   // slabs a workgroup walks with one load of its weights
 // Workgroups [first[d], first[d + 1]) own degree L - d (the highest degree, with the most slabs per tile, first) and
@@ -740,8 +743,11 @@ void launch_C(const MapWeights<T>& mw, T* WT, const T* h, const float* gq, const
             if (rows * C >= STATIONARY_WORK) launch_rows_stationary<CP>(mw, WT, h, gq, gk, gv, gh, L, N, st);
             else launch_rows<T, CP, 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
         } else {
-            // 64 rows a workgroup while that leaves two workgroups per CU, else 32 (256 bf16 channels, 4 000 atoms: 64 rows
-            // 349 us, 32 rows 473 us; the weights pass through every workgroup)
+            // 64 rows a workgroup while that leaves two workgroups per CU, else 32: the weights pass through every workgroup.  Measured,
+            // us, 32 / 64 rows: 256 bf16 channels, L = 4, 300 atoms 35 / 43, 700 90 / 81, 1 311 (the line) 144 / 120, 4 000 380 / 300; fp32 256
+            // channels, L = 4, 700 atoms 248 / 310, 1 311 392 / 449, 3 000 815 / 772; fp32 128 channels, L = 4, 500 to 1 300 atoms 1.0 to 1.08,
+            // 1 600 117 / 128, 3 000 218 / 200, L = 2, 2 240 71 / 86, 3 641 (the line) 106 / 122, 6 000 155 / 162; fp32 64 channels, L = 2, 2 240
+            // 27 / 41, 3 641 38 / 43, 6 000 53 / 52; 16 channels, L = 1, 9 000 17 / 28: bf16 would take 64 rows earlier, fp32 later.
             if (rows >= 512 * 64) launch_rows<T, CP, 2, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
             else launch_rows<T, CP, 1, PAD>(mw, WT, h, gq, gk, gv, gh, L, C, N, st);
         }

@@ -4,9 +4,9 @@
 //     S^T = K Q^T          logits of 16 targets x 32 candidates
 //     T_mu += W_mu V       W_mu[i][j] = e^{s_ij - m_i} phi(d_ij) (r_ij)_mu
 //     out_i = (1/z_i) sum_mu G_mu T_i,mu
-// A workgroup of eight waves owns (tile of 16 targets, head).  Candidate chunks are taken eight at a time: wave w
-// scores chunk 8G + w (logits, pair geometry, softmax weights -> LDS), then every wave applies all eight chunks'
-// weights to its own eighth of the components.  The candidate lists are those of the bf16 kernel (k_tile's list
+// A workgroup of four waves owns (tile of 16 targets, head).  Candidate chunks are taken four at a time: wave w
+// scores chunk 4G + w (logits, pair geometry, softmax weights -> LDS), then every wave applies all four chunks'
+// weights to its own quarter of the components.  The candidate lists are those of the bf16 kernel (k_tile's list
 // form); tiles whose list does not fit are left to the vector-ALU kernel.
 // Register layout of v_mfma_f32_16x16x4_f32 (lane = 16 g + i): A operand: A[i][g]; B operand: B[g][i]; result:
 // C[4g..4g+3][i].  The contraction index of a step is free to choose as long as both operands agree: the logits take

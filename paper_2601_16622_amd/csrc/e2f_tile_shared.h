@@ -97,8 +97,9 @@ __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) {
 }
 
 // T <- diag(f) T for accumulators whose rows are targets: register r of lane (j, g) is row 4g + r, f the factor of target
-// lane % 16.  (A quarter of the bf16 kernel's items move a reference; as products with diag(f) on the fp32 matrix instruction
-// a move took 336 instructions of 32 cycles, 10 000 atoms 312 -> 294 us a forward pass without them.)
+// lane % 16.  (A quarter of the bf16 kernel's items move a reference; as products with diag(f) a move took a wave 84 fp32 matrix
+// instructions of 32 cycles at L = 4, here 84 multiplications and four lane exchanges.  10 000 atoms 312 -> 294 us a forward pass,
+// together with cheaper row addresses and operands and the epilogue's components by axis_class.)
 template <int NS>
 __device__ __forceinline__ void rescale_rows(f32x4 (&acc)[3][NS], float f, int g) {
 #pragma unroll
