@@ -183,8 +183,9 @@ def main():
     t_roof, work, peak, unit = roofs[bound]
     achieved = work / (attn_ms * 1e-3) if attn_ms > 0 else 0.0
     roofline = {"bound": bound, "kernel": kernel, "achieved": round(achieved, 3), "peak": peak, "unit": unit,
-                "frac": round(achieved / peak, 4), "traffic": read_traffic(),
-                "traffic_source": TRAFFIC_FILE + " (rocprofv3 FETCH_SIZE + WRITE_SIZE runs; not measured in this run)",
+                "frac": round(achieved / peak, 4), "traffic": read_traffic() if args.workload == "scaling" else None,
+                "traffic_source": TRAFFIC_FILE + " (rocprofv3 FETCH_SIZE + WRITE_SIZE runs of the workload `scaling`; "
+                                  "not measured in this run)",
                 "kernel_ms": round(attn_ms, 4), "kernel_ms_median": round(attn_ms_median, 4),
                 "achieved_is": "the method's per-pair work of the bound (model) over the measured time of the "
                                "attention stage, not executed instructions",
@@ -196,9 +197,9 @@ def main():
                 "stage_ms": {k: round(v, 4) for k, v in stage_ms.items()}}
     if bound == "alu":
         roofline["frac_of_plain_fma_peak"] = round(achieved / PEAK_ALU_PLAIN_FMA_TFLOPS, 4)
-    if kernel == "k_tile_heads":
+    if kernel == "k_tile_heads" and args.workload == "scaling":
         # what the kernel executes (matrix-core instructions over all candidate slots, masked ones included), from the
-        # committed counter summary of the same workload
+        # committed counter summary of the same workload (there is none of the others)
         sq = read_counters("k_tile_heads<4, 8>")
         useful = E * cfg["H"] * (2 * (Lm + 1) * 16 + 3 * n * 16 * 2)
         if sq.get("SQ_INSTS_MFMA"):
